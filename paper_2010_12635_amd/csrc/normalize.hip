@@ -2,17 +2,22 @@
 // CSR (rows ascending, columns ascending and unique), plus the heavy-row
 // schedule used by the sparse aggregation.
 //
-// Steps (all integer work is order-independent, so the CSR is bit-identical
-// from run to run even though the scatter uses atomics):
-//   count    per-row counts of both directions of every u != v pair
-//   scan     segment offsets (count + 1 slot for the self-loop)
-//   scatter  neighbour ids into per-row segments (+ the self-loop)
-//   sort     each segment: wave bitonic (<= 64), LDS bitonic (<= 4096),
-//            global-memory bitonic (larger hubs)
-//   unique   per-row count of distinct neighbours -> degree
-//   scan     row pointers; compact; dinv = fp32(1 / sqrt(fp64(deg)))
-//   values   dinv[row] * dinv[col] in the value precision; optional dense
-#include "internal.h"
+// Steps (all integer, so the CSR is bit-identical from run to run):
+//  * both directions of every pair, and (i, i) for every vertex, become keys
+//    row << b | column, b the bits of a vertex id; a pair (v, v) and a repeat
+//    become repeats of a key that is there anyway;
+//  * a radix sort of the keys (radix.h): 32-bit keys up to n = 65536, else
+//    64-bit ones.  Its time does not depend on how the entries are spread
+//    over the rows: sorting row segments instead left the hubs of a power-law
+//    graph to one workgroup each, and counting them took atomics on few
+//    addresses (R-MAT scale 18, 8.7 M keys: 6.3 ms in all before, the
+//    numbers now are at normalize_run);
+//  * the distinct keys of every tile are counted and scanned, then written
+//    out in order: columns, row pointers (where a row begins; no row is
+//    empty) and the entry's row, which the values need;
+//  * degrees and dinv = fp32(1 / sqrt(fp64(deg))); values dinv[row] *
+//    dinv[col] in the value precision, one thread per entry; optional dense.
+#include "radix.h"
 
 #include <algorithm>
 #include <vector>
@@ -22,7 +27,6 @@ namespace gcn {
 namespace {
 
 constexpr int SCAN_BLOCK = 1024;   // elements per scan block (256 threads x 4)
-constexpr int64_t SORT_LDS_MAX = 4096;
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -88,16 +92,6 @@ __global__ void fill_zero_kernel(uint32_t* p, int64_t words) {
     p[i] = 0u;
 }
 
-// Workgroups for one wave per row, 4 rows per workgroup of 256 threads; the
-// kernels loop over rows, so the grid is capped (a dispatch may not exceed
-// 2^32 work-items per dimension).
-unsigned wave_rows_grid(int64_t rows) {
-  int64_t g = (rows + 3) / 4;
-  if (g < 1) g = 1;
-  if (g > (1 << 20)) g = 1 << 20;
-  return (unsigned)g;
-}
-
 unsigned grid_for(int64_t items, int per_block = 256, int64_t cap = 65536) {
   int64_t g = (items + per_block - 1) / per_block;
   if (g < 1) g = 1;
@@ -106,209 +100,156 @@ unsigned grid_for(int64_t items, int per_block = 256, int64_t cap = 65536) {
 }
 
 // ---------------------------------------------------------------- kernels ----
-__global__ void count_kernel(int64_t n, int64_t E, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                             int32_t* __restrict__ cnt, int32_t* __restrict__ bad) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < E; k += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t u = src[k], v = dst[k];
-    if (u < 0 || v < 0 || u >= n || v >= n) { *reinterpret_cast<volatile int32_t*>(bad) = 1; continue; }
-    if (u == v) continue;
-    atomicAdd(&cnt[u], 1);
-    atomicAdd(&cnt[v], 1);
-  }
-}
-
-// seg[r] = cnt[r] + 1 (self-loop slot), seg[n] = 0
-__global__ void seglen_kernel(int64_t n, const int32_t* __restrict__ cnt, int64_t* __restrict__ seg) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= n; r += (int64_t)gridDim.x * blockDim.x)
-    seg[r] = r < n ? (int64_t)cnt[r] + 1 : 0;
-}
-
 // out[r] = in[r], out[n] = 0
 __global__ void widen_kernel(int64_t n, const int32_t* __restrict__ in, int64_t* __restrict__ out) {
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= n; r += (int64_t)gridDim.x * blockDim.x)
     out[r] = r < n ? (int64_t)in[r] : 0;
 }
 
-__global__ void scatter_kernel(int64_t n, int64_t E, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                               const int64_t* __restrict__ off, int32_t* __restrict__ cur, int32_t* __restrict__ tmp) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < E; k += (int64_t)gridDim.x * blockDim.x) {
+// Item i of the sort: pair i forwards, pair i - E backwards, then the
+// self-loops.  A pair with a vertex id outside [0, n) raises *bad and stands
+// for the self-loop of vertex 0.
+template <typename I>
+struct EdgeItems {
+  typedef I Item;
+  int64_t n, E;
+  const int32_t* src;
+  const int32_t* dst;
+  int b;
+  int32_t* bad;
+  __device__ __forceinline__ I load(int64_t i) const {
+    typedef decltype(I::k) K;
+    I x;
+    if (i >= 2 * E) {
+      const K r = (K)(i - 2 * E);
+      x.k = (K)(r << b) | r;
+      return x;
+    }
+    const int64_t k = i < E ? i : i - E;
     const int32_t u = src[k], v = dst[k];
-    if (u < 0 || v < 0 || u >= n || v >= n || u == v) continue;
-    const int32_t pu = atomicAdd(&cur[u], 1);
-    tmp[off[u] + pu] = v;
-    const int32_t pv = atomicAdd(&cur[v], 1);
-    tmp[off[v] + pv] = u;
+    const bool ok = u >= 0 && v >= 0 && u < n && v < n;
+    if (!ok) *reinterpret_cast<volatile int32_t*>(bad) = 1;
+    const K r = ok ? (K)(i < E ? u : v) : (K)0, c = ok ? (K)(i < E ? v : u) : (K)0;
+    x.k = (K)(r << b) | c;
+    return x;
   }
-}
+};
 
-__global__ void selfloop_kernel(int64_t n, const int64_t* __restrict__ off, const int32_t* __restrict__ cnt,
-                                int32_t* __restrict__ tmp) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x)
-    tmp[off[r] + cnt[r]] = (int32_t)r;
-}
+constexpr int UNIQ_IPT = 8;
+constexpr int UNIQ_TILE = 256 * UNIQ_IPT;
 
-// Segments of at most 64 entries: one wave, register bitonic sort.
-__global__ __launch_bounds__(256) void sort_small_kernel(int64_t n, const int64_t* __restrict__ off,
-                                                         int32_t* __restrict__ tmp, int32_t* __restrict__ ucnt) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n; r += (int64_t)gridDim.x * 4) {
-    const int64_t b = off[r], len = off[r + 1] - b;
-    if (len > 64) continue;
-    int x = lane < len ? tmp[b + lane] : INT32_MAX;
-    for (int k = 2; k <= 64; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        const int y = __shfl_xor(x, j);
-        const bool asc = (lane & k) == 0;
-        const bool lower = (lane & j) == 0;
-        x = (lower == asc) ? min(x, y) : max(x, y);
-      }
+// A wave's 64 * UNIQ_IPT sorted keys and, per round, the lanes whose key
+// differs from the one before it.
+template <typename I>
+struct UniqWave {
+  typedef decltype(I::k) K;
+  K k[UNIQ_IPT], prev[UNIQ_IPT];
+  uint64_t first[UNIQ_IPT];
+  __device__ __forceinline__ void load(const I* __restrict__ keys, int64_t w0, int64_t total) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < UNIQ_IPT; ++r) {
+      const int64_t i = w0 + r * 64 + lane;
+      k[r] = keys[i < total ? i : total - 1].k;
+      prev[r] = keys[i < total ? (i > 0 ? i - 1 : 0) : total - 1].k;
     }
-    const int prev = __shfl(x, lane == 0 ? 0 : lane - 1);
-    const bool flag = lane < len && (lane == 0 || x != prev);
-    const uint64_t bal = __ballot(flag);
-    if (lane < len) tmp[b + lane] = x;
-    if (lane == 0) ucnt[r] = __popcll(bal);
+#pragma unroll
+    for (int r = 0; r < UNIQ_IPT; ++r) {
+      const int64_t i = w0 + r * 64 + lane;
+      first[r] = __ballot(i < total && (i == 0 || k[r] != prev[r]));
+    }
   }
-}
+};
 
-__device__ int block_sum_int(int v, int* red) {
-  red[threadIdx.x] = v;
+// cnt[tile] = distinct keys that begin in the tile; cnt[tiles] = 0.
+template <typename I>
+__global__ __launch_bounds__(256) void uniq_count_kernel(const I* __restrict__ keys, int64_t total,
+                                                         int64_t* __restrict__ cnt) {
+  __shared__ int wsum[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  UniqWave<I> x;
+  x.load(keys, (int64_t)blockIdx.x * UNIQ_TILE + wave * (64 * UNIQ_IPT), total);
+  int a = 0;
+#pragma unroll
+  for (int r = 0; r < UNIQ_IPT; ++r) a += __popcll(x.first[r]);
+  if (lane == 0) wsum[wave] = a;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    cnt[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (blockIdx.x == 0) cnt[gridDim.x] = 0;
   }
-  const int out = red[0];
+}
+
+// Distinct keys in order: colidx, the row of every entry, and rowptr where a
+// row begins (each row holds its self-loop, so each begins somewhere).
+template <typename I, typename IdxT>
+__global__ __launch_bounds__(256) void uniq_write_kernel(const I* __restrict__ keys, int64_t total, int b, int64_t n,
+                                                         const int64_t* __restrict__ off, int32_t* __restrict__ colidx,
+                                                         int32_t* __restrict__ rows, IdxT* __restrict__ rowptr) {
+  typedef decltype(I::k) K;
+  __shared__ int wsum[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t w0 = (int64_t)blockIdx.x * UNIQ_TILE + wave * (64 * UNIQ_IPT);
+  UniqWave<I> x;
+  x.load(keys, w0, total);
+  int a = 0;
+#pragma unroll
+  for (int r = 0; r < UNIQ_IPT; ++r) a += __popcll(x.first[r]);
+  if (lane == 0) wsum[wave] = a;
   __syncthreads();
-  return out;
-}
-
-// Segments of 65..4096 entries: one workgroup, bitonic sort in LDS.
-__global__ __launch_bounds__(256) void sort_medium_kernel(int64_t n, const int64_t* __restrict__ off,
-                                                          int32_t* __restrict__ tmp, int32_t* __restrict__ ucnt) {
-  __shared__ int s[SORT_LDS_MAX];
-  __shared__ int red[256];
-  for (int64_t r = blockIdx.x; r < n; r += gridDim.x) {
-    const int64_t b = off[r], len = off[r + 1] - b;
-    if (len <= 64 || len > SORT_LDS_MAX) continue;
-    int P = 128;
-    while (P < len) P <<= 1;
-    for (int i = threadIdx.x; i < P; i += 256) s[i] = i < len ? tmp[b + i] : INT32_MAX;
-    __syncthreads();
-    for (int k = 2; k <= P; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int i = threadIdx.x; i < P; i += 256) {
-          const int ixj = i ^ j;
-          if (ixj > i) {
-            const int a = s[i], c = s[ixj];
-            const bool asc = (i & k) == 0;
-            if ((a > c) == asc) { s[i] = c; s[ixj] = a; }
-          }
-        }
-        __syncthreads();
-      }
+  int64_t run = off[blockIdx.x];
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+  const uint64_t lt = lane == 0 ? 0ull : ~0ull >> (64 - lane);
+  const K cmask = (K)(((K)1 << b) - 1);
+#pragma unroll
+  for (int r = 0; r < UNIQ_IPT; ++r) {
+    if (x.first[r] >> lane & 1) {
+      const int64_t pos = run + __popcll(x.first[r] & lt);
+      const K row = x.k[r] >> b;
+      colidx[pos] = (int32_t)(x.k[r] & cmask);
+      rows[pos] = (int32_t)row;
+      if (w0 + r * 64 + lane == 0 || row != x.prev[r] >> b) rowptr[row] = (IdxT)pos;
     }
-    int cntu = 0;
-    for (int i = threadIdx.x; i < len; i += 256) {
-      tmp[b + i] = s[i];
-      cntu += (i == 0 || s[i] != s[i - 1]) ? 1 : 0;
-    }
-    const int tot = block_sum_int(cntu, red);
-    if (threadIdx.x == 0) ucnt[r] = tot;
-    __syncthreads();
+    run += __popcll(x.first[r]);
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) rowptr[n] = (IdxT)off[gridDim.x];
 }
 
-// Segments above 4096 entries: one workgroup, bitonic network in global
-// memory in its "always ascending" form (the first step of each merge
-// compares i with its mirror in the block), so positions >= len act as +inf
-// and are never touched.
-__global__ __launch_bounds__(256) void sort_large_kernel(int64_t n, const int64_t* __restrict__ off,
-                                                         int32_t* __restrict__ tmp, int32_t* __restrict__ ucnt) {
-  __shared__ int red[256];
-  for (int64_t r = blockIdx.x; r < n; r += gridDim.x) {
-    const int64_t b = off[r], len = off[r + 1] - b;
-    if (len <= SORT_LDS_MAX) continue;
-    int32_t* a = tmp + b;
-    int64_t P = 1;
-    while (P < len) P <<= 1;
-    for (int64_t k = 2; k <= P; k <<= 1) {
-      // mirror step
-      for (int64_t t = threadIdx.x; t < P / 2; t += 256) {
-        const int64_t blk = t / (k / 2), w = t % (k / 2);
-        const int64_t i = blk * k + w, p = blk * k + (k - 1 - w);
-        if (p < len) {
-          const int32_t x = a[i], y = a[p];
-          if (x > y) { a[i] = y; a[p] = x; }
-        }
-      }
-      __syncthreads();
-      for (int64_t j = k / 4; j > 0; j >>= 1) {
-        for (int64_t t = threadIdx.x; t < P / 2; t += 256) {
-          const int64_t blk = t / j, w = t % j;
-          const int64_t i = blk * 2 * j + w, p = i + j;
-          if (p < len) {
-            const int32_t x = a[i], y = a[p];
-            if (x > y) { a[i] = y; a[p] = x; }
-          }
-        }
-        __syncthreads();
-      }
-    }
-    int cntu = 0;
-    for (int64_t i = threadIdx.x; i < len; i += 256) cntu += (i == 0 || a[i] != a[i - 1]) ? 1 : 0;
-    const int tot = block_sum_int(cntu, red);
-    if (threadIdx.x == 0) ucnt[r] = tot;
-    __syncthreads();
-  }
-}
-
-// Compact sorted segments to unique columns; write rowptr, deg, dinv.
 template <typename IdxT>
-__global__ __launch_bounds__(256) void compact_kernel(int64_t n, const int64_t* __restrict__ off,
-                                                      const int32_t* __restrict__ tmp, const int64_t* __restrict__ rp64,
-                                                      const int32_t* __restrict__ ucnt, IdxT* __restrict__ rowptr,
-                                                      int32_t* __restrict__ colidx, int32_t* __restrict__ deg,
-                                                      float* __restrict__ dinv) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r <= n; r += (int64_t)gridDim.x * 4) {
-    if (r == n) {
-      if (lane == 0) rowptr[n] = (IdxT)rp64[n];
-      continue;
-    }
-    const int64_t b = off[r], len = off[r + 1] - b;
-    const int64_t o = rp64[r];
-    int64_t run = 0;
-    for (int64_t base = 0; base < len; base += 64) {
-      const int64_t i = base + lane;
-      const int x = i < len ? tmp[b + i] : 0;
-      const bool flag = i < len && (i == 0 || x != tmp[b + i - 1]);
-      const uint64_t bal = __ballot(flag);
-      const int pre = __popcll(bal & __lanemask_lt());
-      if (flag) colidx[o + run + pre] = x;
-      run += __popcll(bal);
-    }
-    if (lane == 0) {
-      rowptr[r] = (IdxT)o;
-      const int32_t d = ucnt[r];
-      if (deg) deg[r] = d;
-      dinv[r] = (float)(1.0 / sqrt((double)d));
-    }
+__global__ void degree_kernel(int64_t n, const IdxT* __restrict__ rowptr, int32_t* __restrict__ deg,
+                              float* __restrict__ dinv) {
+  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t d = (int32_t)((int64_t)rowptr[r + 1] - (int64_t)rowptr[r]);
+    if (deg) deg[r] = d;
+    dinv[r] = (float)(1.0 / sqrt((double)d));
   }
 }
 
+// One thread per entry (four in flight each); *nnz entries.
 template <typename T>
-__global__ __launch_bounds__(256) void values_kernel(int64_t n, const int64_t* __restrict__ rp64,
+__global__ __launch_bounds__(256) void values_kernel(const int64_t* __restrict__ nnz, const int32_t* __restrict__ rows,
                                                      const int32_t* __restrict__ colidx, const float* __restrict__ dinv,
                                                      T* __restrict__ values, T* __restrict__ dense, int64_t ld_dense) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n; r += (int64_t)gridDim.x * 4) {
-    const float dr = dinv[r];
-    for (int64_t k = rp64[r] + lane; k < rp64[r + 1]; k += 64) {
-      const int32_t c = colidx[k];
-      const T v = from_f32<T>(dr * dinv[c]);
+  constexpr int U = 4;
+  const int64_t total = *nnz;
+  for (int64_t base = (int64_t)blockIdx.x * (256 * U); base < total; base += (int64_t)gridDim.x * (256 * U)) {
+    int32_t r[U], c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = base + u * 256 + threadIdx.x;
+      r[u] = rows[k < total ? k : total - 1];
+      c[u] = colidx[k < total ? k : total - 1];
+    }
+    float a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { a[u] = dinv[r[u]]; b[u] = dinv[c[u]]; }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = base + u * 256 + threadIdx.x;
+      if (k >= total) break;
+      const T v = from_f32<T>(a[u] * b[u]);
       if (values) values[k] = v;
-      if (dense) dense[r * ld_dense + c] = v;
+      if (dense) dense[(int64_t)r[u] * ld_dense + c[u]] = v;
     }
   }
 }
@@ -585,88 +526,132 @@ hipError_t fill_zero(void* p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-size_t normalize_workspace_bytes(int64_t n, int64_t E) {
-  size_t b = 0;
-  b += align256(sizeof(int32_t) * n);                         // cnt / ucnt
-  b += align256(sizeof(int32_t) * n);                         // cur
-  b += align256(sizeof(int64_t) * (n + 1));                   // off
-  b += align256(sizeof(int64_t) * (n + 1));                   // rp64
-  b += align256(sizeof(int32_t) * (2 * E + n));               // tmp
-  b += align256(sizeof(int64_t) * scan_scratch_elems(n + 1)); // scan scratch
-  b += align256(sizeof(int64_t) * 4);                         // misc
+namespace {
+int id_bits(int64_t n) {
+  int b = 1;
+  while (((int64_t)1 << b) < n) ++b;
   return b;
 }
+
+// Workspace of normalize_run: two key buffers, the sort's scratch, the
+// distinct keys per tile with their scan, the bad-id flag.
+struct NormLayout {
+  char *kA, *kB;
+  void* radix;
+  int64_t *off, *scr;
+  int32_t* bad;
+  size_t bytes;
+};
+NormLayout norm_layout(int64_t n, int64_t E, void* ws) {
+  const int64_t total = 2 * E + n, nu = (total + UNIQ_TILE - 1) / UNIQ_TILE;
+  const size_t kb = (2 * id_bits(n) <= 32 ? sizeof(Key32) : sizeof(Key64)) * (size_t)total;
+  NormLayout L;
+  char* base = static_cast<char*>(ws);
+  size_t o = 0;
+  auto take = [&](size_t bytes) { char* p = base ? base + o : nullptr; o += align256(bytes); return p; };
+  L.kA = take(kb);
+  L.kB = take(kb);
+  L.radix = take(radix_scratch_bytes(total));
+  L.off = (int64_t*)take(sizeof(int64_t) * (nu + 2));   // the scan's total (nnz), then the flag: read back together
+  L.scr = (int64_t*)take(sizeof(int64_t) * scan_scratch_elems(nu + 1));
+  L.bad = base ? (int32_t*)(L.off + nu + 1) : nullptr;
+  L.bytes = o;
+  return L;
+}
+
+struct NormOut {
+  void* rowptr;
+  bool idx64;
+  int32_t *colidx, *deg;
+  float* dinv;
+  int value_prec;
+  void *values, *dense;
+  int64_t ld_dense;
+};
+
+template <typename I>
+hipError_t normalize_keys(int64_t n, int64_t E, const int32_t* src, const int32_t* dst, const NormOut& o,
+                          const NormLayout& L, hipStream_t s) {
+  const int64_t total = 2 * E + n;
+  const int b = id_bits(n);
+  hipError_t e;
+#define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
+  int passes = 0, width = 0;
+  radix_plan(2 * b, &passes, &width);
+  ItemArray<I> bufA{(I*)L.kA}, bufB{(I*)L.kB}, in = bufB, out = bufA;
+  for (int ps = 0; ps < passes; ++ps) {
+    const int shift = ps * width, w = std::min(width, 2 * b - shift);
+    if (ps == 0) {
+      const EdgeItems<I> edges{n, E, src, dst, b, L.bad};
+      GCN_TRY(radix_pass(edges, out, total, shift, w, L.radix, s));
+    } else {
+      GCN_TRY(radix_pass(in, out, total, shift, w, L.radix, s));
+    }
+    std::swap(in, out);
+  }
+  const I* keys = in.p;
+  int32_t* rows = (int32_t*)out.p;                    // the other buffer is free now
+  const int64_t nu = (total + UNIQ_TILE - 1) / UNIQ_TILE;
+  const dim3 ug((unsigned)nu);
+  hipLaunchKernelGGL(uniq_count_kernel<I>, ug, dim3(256), 0, s, keys, total, L.off);
+  GCN_TRY(hipGetLastError());
+  GCN_TRY(scan_exclusive(L.off, nu + 1, L.scr, s));
+  if (o.idx64) {
+    hipLaunchKernelGGL((uniq_write_kernel<I, int64_t>), ug, dim3(256), 0, s, keys, total, b, n, L.off, o.colidx, rows,
+                       (int64_t*)o.rowptr);
+    GCN_TRY(hipGetLastError());
+    hipLaunchKernelGGL(degree_kernel<int64_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int64_t*)o.rowptr, o.deg,
+                       o.dinv);
+  } else {
+    hipLaunchKernelGGL((uniq_write_kernel<I, int32_t>), ug, dim3(256), 0, s, keys, total, b, n, L.off, o.colidx, rows,
+                       (int32_t*)o.rowptr);
+    GCN_TRY(hipGetLastError());
+    hipLaunchKernelGGL(degree_kernel<int32_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int32_t*)o.rowptr, o.deg,
+                       o.dinv);
+  }
+  GCN_TRY(hipGetLastError());
+  if (o.dense) GCN_TRY(fill_zero(o.dense, (size_t)n * (size_t)o.ld_dense * (o.value_prec == 0 ? 4 : 2), s));
+  if (o.values || o.dense) {
+    const dim3 g(grid_for(total, 1024, 8192));
+    const int64_t* nnz = L.off + nu;
+    switch (o.value_prec) {
+      case 0: hipLaunchKernelGGL(values_kernel<float>, g, dim3(256), 0, s, nnz, rows, o.colidx, o.dinv, (float*)o.values, (float*)o.dense, o.ld_dense); break;
+      case 1: hipLaunchKernelGGL(values_kernel<f16>, g, dim3(256), 0, s, nnz, rows, o.colidx, o.dinv, (f16*)o.values, (f16*)o.dense, o.ld_dense); break;
+      case 2: hipLaunchKernelGGL(values_kernel<bf16>, g, dim3(256), 0, s, nnz, rows, o.colidx, o.dinv, (bf16*)o.values, (bf16*)o.dense, o.ld_dense); break;
+      default: return hipErrorInvalidValue;
+    }
+    GCN_TRY(hipGetLastError());
+  }
+#undef GCN_TRY
+  return hipSuccess;
+}
+}  // namespace
+
+// Measured (MI355X, R-MAT scale 18, 8.65 M keys of 36 bits, four passes of 9
+// bits): gcn_normalize + gcn_schedule 6.33 -> 0.74 ms; a pass 64 us (counts
+// 14, scan 12, scatter 38: 3.5 TB/s of keys read and written), distinct keys
+// 32 us, values 36 us.
+size_t normalize_workspace_bytes(int64_t n, int64_t E) { return norm_layout(n, E, nullptr).bytes; }
 
 hipError_t normalize_run(int64_t n, int64_t E, const int32_t* src, const int32_t* dst, bool idx64,
                          void* rowptr, int32_t* colidx, int32_t* deg, float* dinv, int value_prec,
                          void* values, void* dense, int64_t ld_dense, int64_t* nnz_out, int32_t* bad_ids,
                          void* ws, size_t ws_bytes, hipStream_t s) {
-  char* w = static_cast<char*>(ws);
-  auto take = [&](size_t bytes) { char* p = w; w += align256(bytes); return p; };
-  int32_t* cnt = (int32_t*)take(sizeof(int32_t) * n);
-  int32_t* cur = (int32_t*)take(sizeof(int32_t) * n);
-  int64_t* off = (int64_t*)take(sizeof(int64_t) * (n + 1));
-  int64_t* rp64 = (int64_t*)take(sizeof(int64_t) * (n + 1));
-  int32_t* tmp = (int32_t*)take(sizeof(int32_t) * (2 * E + n));
-  int64_t* scr = (int64_t*)take(sizeof(int64_t) * scan_scratch_elems(n + 1));
-  int64_t* misc = (int64_t*)take(sizeof(int64_t) * 4);
-  if ((size_t)(w - static_cast<char*>(ws)) > ws_bytes) return hipErrorInvalidValue;
-
+  const NormLayout L = norm_layout(n, E, ws);
+  if (L.bytes > ws_bytes) return hipErrorInvalidValue;
+  const int64_t nu = (2 * E + n + UNIQ_TILE - 1) / UNIQ_TILE;
+  const NormOut o{rowptr, idx64, colidx, deg, dinv, value_prec, values, dense, ld_dense};
   hipError_t e;
 #define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-  GCN_TRY(fill_zero(cnt, sizeof(int32_t) * n, s));
-  GCN_TRY(fill_zero(cur, sizeof(int32_t) * n, s));
-  GCN_TRY(fill_zero(misc, sizeof(int64_t) * 4, s));
-  int32_t* bad = reinterpret_cast<int32_t*>(misc + 1);
-  if (E > 0) {
-    hipLaunchKernelGGL(count_kernel, dim3(grid_for(E)), dim3(256), 0, s, n, E, src, dst, cnt, bad);
-    GCN_TRY(hipGetLastError());
-  }
-  hipLaunchKernelGGL(seglen_kernel, dim3(grid_for(n + 1)), dim3(256), 0, s, n, cnt, off);
-  GCN_TRY(hipGetLastError());
-  GCN_TRY(scan_exclusive(off, n + 1, scr, s));
-  if (E > 0) {
-    hipLaunchKernelGGL(scatter_kernel, dim3(grid_for(E)), dim3(256), 0, s, n, E, src, dst, off, cur, tmp);
-    GCN_TRY(hipGetLastError());
-  }
-  hipLaunchKernelGGL(selfloop_kernel, dim3(grid_for(n)), dim3(256), 0, s, n, off, cnt, tmp);
-  GCN_TRY(hipGetLastError());
-  int32_t* ucnt = cnt;   // counts are no longer needed after the self-loop slots are placed
-  hipLaunchKernelGGL(sort_small_kernel, dim3(wave_rows_grid(n)), dim3(256), 0, s, n, off, tmp, ucnt);
-  GCN_TRY(hipGetLastError());
-  hipLaunchKernelGGL(sort_medium_kernel, dim3(grid_for(n, 1, 4096)), dim3(256), 0, s, n, off, tmp, ucnt);
-  GCN_TRY(hipGetLastError());
-  hipLaunchKernelGGL(sort_large_kernel, dim3(grid_for(n, 1, 1024)), dim3(256), 0, s, n, off, tmp, ucnt);
-  GCN_TRY(hipGetLastError());
-  hipLaunchKernelGGL(widen_kernel, dim3(grid_for(n + 1)), dim3(256), 0, s, n, ucnt, rp64);
-  GCN_TRY(hipGetLastError());
-  GCN_TRY(scan_exclusive(rp64, n + 1, scr, s));
-  if (idx64)
-    hipLaunchKernelGGL(compact_kernel<int64_t>, dim3(wave_rows_grid(n + 1)), dim3(256), 0, s, n, off, tmp, rp64,
-                       ucnt, (int64_t*)rowptr, colidx, deg, dinv);
-  else
-    hipLaunchKernelGGL(compact_kernel<int32_t>, dim3(wave_rows_grid(n + 1)), dim3(256), 0, s, n, off, tmp, rp64,
-                       ucnt, (int32_t*)rowptr, colidx, deg, dinv);
-  GCN_TRY(hipGetLastError());
-  if (dense) GCN_TRY(fill_zero(dense, (size_t)n * (size_t)ld_dense * (value_prec == 0 ? 4 : 2), s));
-  if (values || dense) {
-    const dim3 g(wave_rows_grid(n));
-    switch (value_prec) {
-      case 0: hipLaunchKernelGGL(values_kernel<float>, g, dim3(256), 0, s, n, rp64, colidx, dinv, (float*)values, (float*)dense, ld_dense); break;
-      case 1: hipLaunchKernelGGL(values_kernel<f16>, g, dim3(256), 0, s, n, rp64, colidx, dinv, (f16*)values, (f16*)dense, ld_dense); break;
-      case 2: hipLaunchKernelGGL(values_kernel<bf16>, g, dim3(256), 0, s, n, rp64, colidx, dinv, (bf16*)values, (bf16*)dense, ld_dense); break;
-      default: return hipErrorInvalidValue;
-    }
-    GCN_TRY(hipGetLastError());
-  }
+  GCN_TRY(fill_zero(L.bad, sizeof(int64_t), s));
+  if (2 * id_bits(n) <= 32) GCN_TRY(normalize_keys<Key32>(n, E, src, dst, o, L, s));
+  else GCN_TRY(normalize_keys<Key64>(n, E, src, dst, o, L, s));
   // the one synchronisation: nnz and the bad-id flag back to the host
   int64_t host[2] = {0, 0};
-  GCN_TRY(hipMemcpyAsync(&host[0], rp64 + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  int32_t hbad = 0;
-  GCN_TRY(hipMemcpyAsync(&hbad, bad, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  GCN_TRY(hipMemcpyAsync(host, L.off + nu, sizeof(host), hipMemcpyDeviceToHost, s));
   GCN_TRY(hipStreamSynchronize(s));
   *nnz_out = host[0];
-  *bad_ids = hbad;
+  *bad_ids = (int32_t)host[1];
 #undef GCN_TRY
   return hipSuccess;
 }
