@@ -125,10 +125,14 @@ struct LayerPlan {
   int64_t cs_floats; // column-sum partial region (multiple of 64 floats)
   int64_t cb_floats; // column-sum partials of dZ_below (multiple of 64 floats)
   int64_t floats;    // total
+  bool ranges;       // the dense aggregation may cut its k range (partials in the scratch)
 };
 
-LayerPlan plan_layer(const gcn_adj* A, const gcn_layer* L, int32_t prec) {
+size_t plan_bytes(const LayerPlan& p) { return (size_t)p.floats * sizeof(float) + 256; }
+
+LayerPlan plan_layer_ranges(const gcn_adj* A, const gcn_layer* L, int32_t prec, bool ranges) {
   LayerPlan p;
+  p.ranges = ranges;
   const int64_t n = A->n;
   const bool ident = L->identity_input != 0;    // no product with H = I
   p.s_split = ident ? 1 : gemm_choose_splits(prec, n, L->f_out, L->f_in);
@@ -142,7 +146,7 @@ LayerPlan plan_layer(const gcn_adj* A, const gcn_layer* L, int32_t prec) {
   upd((int64_t)p.dw_split * L->f_in * L->f_out);
   int64_t cs = 0;
   if (A->format != GCN_CSR) {
-    upd((int64_t)(dense_agg_workspace_bytes(prec, n, L->f_out, A->format == GCN_DENSE_TILED) / sizeof(float)) + 1);
+    upd((int64_t)(dense_agg_workspace_bytes(prec, n, L->f_out, A->format == GCN_DENSE_TILED, ranges) / sizeof(float)) + 1);
     cs = dense_agg_colsum_rows(prec, n) * L->f_out;
   } else {
     upd(spmm_partials_floats(view_of(A), prec, L->f_out));
@@ -157,7 +161,15 @@ LayerPlan plan_layer(const gcn_adj* A, const gcn_layer* L, int32_t prec) {
   return p;
 }
 
-size_t plan_bytes(const LayerPlan& p) { return (size_t)p.floats * sizeof(float) + 256; }
+// The k ranges of the streaming dense aggregation are an option: a layer that
+// fits the fixed scratch of gcn_layer_bwd_noalloc only without their partials
+// goes without them, in every call alike.
+LayerPlan plan_layer(const gcn_adj* A, const gcn_layer* L, int32_t prec) {
+  const LayerPlan p = plan_layer_ranges(A, L, prec, true);
+  if (plan_bytes(p) <= (size_t)GCN_NOALLOC_SCRATCH_BYTES) return p;
+  const LayerPlan q = plan_layer_ranges(A, L, prec, false);
+  return plan_bytes(q) <= (size_t)GCN_NOALLOC_SCRATCH_BYTES ? q : p;
+}
 
 Epilogue base_epi(void* out, int64_t ldo, int64_t rows, int64_t cols, int mode, int32_t* flag) {
   Epilogue e{};
@@ -193,10 +205,10 @@ hipError_t row_product(int32_t prec, const void* A, int64_t lda, const void* B, 
 // Y = epilogue(A_hat X).  For dense A_hat, colsum (may be NULL) receives the
 // column-sum partials of X computed during its transposition.
 hipError_t aggregate(const gcn_adj* A, int32_t prec, const void* X, int64_t ldx, int64_t F, const Epilogue& epi,
-                     float* ws, float* colsum, hipStream_t s) {
+                     float* ws, float* colsum, hipStream_t s, bool ranges = true) {
   if (A->format != GCN_CSR)
     return dense_agg_launch(prec, A->dense, A->ld_dense, A->format == GCN_DENSE_TILED, A->n, X, ldx, F, epi, ws,
-                            colsum, s);
+                            colsum, s, ranges);
   return spmm_launch(view_of(A), prec, X, ldx, F, epi, ws, s);
 }
 
@@ -402,7 +414,7 @@ gcn_status gcn_layer_fwd(const gcn_adj* A, const gcn_layer* L, int32_t prec, int
 
   Epilogue ea = agg_epi(H_out, L->ld_out, n, L->f_out, bias, L->act, L->dropout_p, training, seed, L->layer_id,
                         epoch, overflow, L->epoch_from);
-  GCN_HIP(aggregate(A, prec, Sx, L->ld_out, L->f_out, ea, ws, nullptr, s));
+  GCN_HIP(aggregate(A, prec, Sx, L->ld_out, L->f_out, ea, ws, nullptr, s, plan.ranges));
   return finish(hipSuccess, s);
 }
 
@@ -506,7 +518,7 @@ gcn_status layer_bwd_run(const gcn_adj* A, const gcn_layer* L, int32_t prec, con
   // G_S = A_hat^T dZ = A_hat dZ (A_hat symmetric); for dense A_hat the
   // transposition of dZ also yields the column-sum partials for dbias
   Epilogue eg = base_epi(GS, L->ld_out, n, L->f_out, EPI_STORE, overflow);
-  GCN_HIP(aggregate(A, prec, dZ, L->ld_out, L->f_out, eg, ws, dbias && dense ? cs : nullptr, s));
+  GCN_HIP(aggregate(A, prec, dZ, L->ld_out, L->f_out, eg, ws, dbias && dense ? cs : nullptr, s, plan.ranges));
   RedJob jb{};
   if (dbias) {
     Epilogue eb = base_epi(dbias, L->ld_out, 1, L->f_out, EPI_F32, overflow);

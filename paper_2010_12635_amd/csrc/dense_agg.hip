@@ -27,6 +27,8 @@
 #include "internal.h"
 #include "xpose.h"
 
+#include <algorithm>
+
 namespace gcn {
 
 namespace {
@@ -329,6 +331,145 @@ __global__ __launch_bounds__(64 * DA_WAVES) void dense_agg_kernel(DaParams p) {
       v[j] += red[3][r * LDR + cc];
     }
     epi_store_vec<T>(p.epi, row, col, v);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Tiled A_hat, F <= 64.  What bounds the product is, in
+// 16-bit storage, the stream of A_hat from HBM and, beside it, the X^T
+// fragments that every workgroup re-reads from L2 (F / rows of its bytes); in
+// fp32 the matrix units.  So:
+//  * a workgroup owns 128 rows and all columns (16 TN <= 64);
+//    its 4 waves (one per SIMD, up to 512 registers) split the k range, each
+//    with the whole 128 x 16 TN accumulator tile, ST_DEPTH - 1 chunks of
+//    loads in flight, the loads spread among the MFMAs;
+//  * where the row blocks alone would leave compute units idle, or a last
+//    round of workgroups nearly empty, the k range is also cut over `ksplit`
+//    workgroups per row block (rule at stream_plan), whose fp32 partial tiles
+//    mm_reduce_kernel adds in order;
+//  * the four waves' tiles are added through LDS in a fixed order.
+// ---------------------------------------------------------------------------
+struct StreamParams {
+  const void* A;      // tiled A_hat
+  const void* Xt;     // tiled X^T
+  int64_t n, F, nc;   // vertices, features, k chunks
+  int64_t rblocks;    // 64-row blocks of A_hat
+  int64_t rowb;       // 128-row blocks
+  int64_t ksplit;
+  float* part;        // ksplit > 1: fp32 partial products [ksplit][n][ldp]
+  int64_t ldp;
+  Epilogue epi;
+};
+
+template <typename T, int TN, int DEPTH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void dense_stream_kernel(StreamParams p) {
+  constexpr int VE = Vec<T>::N, KC = 4 * VE, PIECE = 16 * KC;
+  constexpr int TM = 8;                            // 16-row tiles per wave
+  constexpr int NC = 16 * TN;                      // columns
+  constexpr int LDR = NC + 4;                      // LDS row stride (floats)
+  __shared__ float red[2][16 * TM * LDR];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t rbk = blockIdx.x % p.rowb, split = blockIdx.x / p.rowb;   // k ranges outermost
+  const int64_t blk = p.nc * 4 * PIECE;            // elements of one 64-row block
+  const T* __restrict__ A = reinterpret_cast<const T*>(p.A);
+  const T* __restrict__ Xt = reinterpret_cast<const T*>(p.Xt);
+  // blocks past the padded extent read the last one (never stored)
+  const T* abase[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) abase[i] = A + min(rbk * 2 + i, p.rblocks - 1) * blk + lane * VE;
+  const T* bbase = Xt + lane * VE;
+  const int64_t s0 = p.nc * split / p.ksplit, s1 = p.nc * (split + 1) / p.ksplit;
+  const int64_t cb = s0 + (s1 - s0) * wave / 4, ce = s0 + (s1 - s0) * (wave + 1) / 4;
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  struct Fr { uint4 a[TM]; uint4 b[TN]; };
+  const int64_t clast = ce > cb ? ce - 1 : (cb < p.nc ? cb : p.nc - 1);
+  auto load = [&](Fr& f, int64_t c) {
+    const int64_t off = (c < clast ? c : clast) * (4 * PIECE);   // past the end: in bounds, unused
+#pragma unroll
+    for (int i = 0; i < TM; ++i) f.a[i] = ldg16_nt(abase[i / 4] + off + (i % 4) * PIECE);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) f.b[t] = ldg16(bbase + off + t * PIECE);
+  };
+  auto compute = [&](const Fr& f) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = DaMfma<T>::run(f.a[i], f.b[j], acc[i][j]);
+  };
+  // a step's loads are spread among its MFMAs
+  constexpr int NL = TM + TN, NM = TM * TN * (sizeof(T) == 4 ? 4 : 1), PER = NM / NL;
+#define ST_STEP(FL, CL, FC)                                                          \
+  load(FL, CL); compute(FC);                                                         \
+  _Pragma("unroll") for (int q_ = 0; q_ < NL; ++q_) {                                \
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   /* vector-memory read */    \
+    __builtin_amdgcn_sched_group_barrier(0x008, PER > 0 ? PER : 1, 0);   /* MFMA */  \
+  }                                                                                  \
+  __builtin_amdgcn_sched_barrier(0);
+  Fr f[DEPTH];
+#pragma unroll
+  for (int d = 0; d < DEPTH - 1; ++d) load(f[d], cb + d);
+  __builtin_amdgcn_sched_barrier(0);
+  int64_t c = cb;
+  for (; c + DEPTH <= ce; c += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) { ST_STEP(f[(d + DEPTH - 1) % DEPTH], c + d + DEPTH - 1, f[d]) }
+  }
+#undef ST_STEP
+  // the last chunks (fewer than DEPTH) are in flight already
+#pragma unroll
+  for (int d = 0; d < DEPTH - 1; ++d)
+    if (c + d < ce) compute(f[d]);
+
+  auto lds_at = [&](int w, int i, int j, int v) -> float& {
+    return red[w][(i * 16 + (lane >> 4) * 4 + v) * LDR + j * 16 + (lane & 15)];
+  };
+  if (wave >= 2) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) lds_at(wave - 2, i, j, v) = acc[i][j][v];
+  }
+  __syncthreads();
+  if (wave < 2) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          float& r = lds_at(wave, i, j, v);        // this lane's own slot of the other wave's tile
+          r = acc[i][j][v] + r;
+        }
+  }
+  __syncthreads();
+
+  constexpr int OV = Vec<T>::N, VPR = NC / OV;     // output vectors per row of the block
+  float bv[OV];
+  const int64_t m0 = rbk * 128;
+  for (int idx = threadIdx.x; idx < 128 * VPR; idx += 256) {
+    const int r = idx / VPR, cv = idx % VPR;
+    const int64_t row = m0 + r, col = cv * OV;
+    if (row >= p.n || col >= p.F) continue;
+    float v[OV];
+#pragma unroll
+    for (int e = 0; e < OV; ++e) v[e] = red[0][r * LDR + cv * OV + e] + red[1][r * LDR + cv * OV + e];
+    if (p.ksplit > 1) {
+      float4* o = reinterpret_cast<float4*>(p.part + (split * p.n + row) * p.ldp + col);
+#pragma unroll
+      for (int e = 0; e < OV / 4; ++e) o[e] = make_float4(v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]);
+    } else {
+      epi_load_bias<T>(p.epi, col, bv);
+      epi_store_vec_b<T>(p.epi, row, col, v, bv);
+    }
   }
 }
 
@@ -647,9 +788,56 @@ MmPlan mm_plan(int prec, int64_t n, int64_t F) {
   return pl;
 }
 
+// Which streaming kernel, and how many k ranges.  A compute unit brings in at
+// most about 48 GB/s through its vector cache, A_hat and X^T together
+// (measured: 46-50 GB/s for 47 to 256 workgroups, F = 16 and 64 alike), so a
+// row block costs (rows + columns) n s / 48 GB/s there, or its flops at the
+// matrix rate; the chip as a whole is held to the stream rate of A_hat; a
+// round of workgroups costs as much as its longest.  Candidates: 64-row blocks
+// over the whole k range (dense_agg_kernel), 128-row blocks over S ranges
+// (dense_stream_kernel, about 4 us of start and end per unit), S > 1 with the
+// reduction launch (about 7 us) and the partials' traffic.  The least time
+// wins, where it is 7 % less; S is bounded by ST_MAX_SPLIT, eight chunks a
+// range and ST_PART_BYTES of partials.  Measured, one call with the
+// transposition (us, 64-row blocks alone -> with this rule; F = 64):
+// 16-bit n = 6001 33 -> 28, 9000 52 -> 42, 20000 202 -> 157, 32768 364 -> 321;
+// fp32 n = 2048 40 -> 24, 6001 99 -> 56, 9000 148 -> 111, 20000 610 -> 432;
+// where the rule keeps the 64-row blocks (16-bit n = 2048, 3000, 12000,
+// 16384) the other candidate took 0 to 30 % longer.
+constexpr int64_t ST_MAX_SPLIT = 16;
+constexpr int64_t ST_PART_BYTES = (int64_t)24 << 20;
+struct StreamPlan { bool wide; int64_t ksplit; int tn; };
+
+StreamPlan stream_plan(int prec, int64_t n, int64_t F, bool split) {
+  StreamPlan pl{false, 1, (int)std::min<int64_t>(4, (F + 15) / 16)};
+  if (F > 64) return pl;
+  const int64_t nc = (n + (prec == 0 ? 15 : 31)) / (prec == 0 ? 16 : 32);
+  const double es = prec == 0 ? 4 : 2, dn = (double)n, cols = 16.0 * pl.tn;
+  const double cu_bytes = 4.8e4, chip_bytes = 6.8e6, part_bytes = 3e6;             // per us
+  auto unit = [&](double rows, double cu_flops) {
+    return std::max((rows + cols) * dn * es / cu_bytes, 2 * rows * dn * cols / cu_flops);
+  };
+  const double chip = dn * dn * es / chip_bytes;
+  auto rounds = [&](int64_t units) { return (double)((units + 255) / 256); };
+  double best = std::max(rounds((n + 63) / 64) * unit(64, prec == 0 ? 4.8e5 : 4.8e6), chip);
+  const int64_t blocks = (n + 127) / 128, ldp = (F + 7) / 8 * 8;
+  for (int64_t S = 1; S <= ST_MAX_SPLIT; ++S) {
+    if (S > 1 && (!split || nc < 8 * S || S * n * ldp * 4 > ST_PART_BYTES)) break;
+    const double t = std::max(rounds(blocks * S) * (unit(128, prec == 0 ? 5.1e5 : 5.1e6) / S + 4.0), chip) +
+                     (S > 1 ? 7.0 + 8.0 * S * dn * F / part_bytes : 0.0);
+    if (t < 0.93 * best) { best = t; pl.ksplit = S; pl.wide = true; }
+  }
+  return pl;
+}
+
+template <typename T, int TN, int DEPTH>
+void stream_launch(const StreamParams& q, hipStream_t s) {
+  hipLaunchKernelGGL((dense_stream_kernel<T, TN, DEPTH>), dim3((unsigned)(q.rowb * q.ksplit)), dim3(256), 0, s, q);
+}
+
 template <typename T>
 hipError_t launch_t(const void* A, int64_t lda, bool tiled, int64_t n, const void* X, int64_t ldx, int64_t F,
-                    const Epilogue& epi, void* ws, float* colsum, hipStream_t s) {
+                    const Epilogue& epi, void* ws, float* colsum, bool split, hipStream_t s) {
   constexpr int KC = tile_kc<T>();
   const int64_t nc = (n + KC - 1) / KC;
   const int64_t fblocks = (F + 63) / 64;
@@ -683,6 +871,30 @@ hipError_t launch_t(const void* A, int64_t lda, bool tiled, int64_t n, const voi
     e = hipGetLastError();
     if (e != hipSuccess || pl.ksplit == 1) return e;
     // the k ranges' partials, added in range order, through the epilogue
+    const int64_t vecs = n * (q.ldp / Vec<T>::N);
+    hipLaunchKernelGGL(mm_reduce_kernel<T>, dim3((unsigned)((vecs + 255) / 256)), dim3(256), 0, s, q.part, pl.ksplit,
+                       n, F, q.ldp, epi);
+    return hipGetLastError();
+  }
+  const StreamPlan pl = stream_plan(sizeof(T) == 4 ? 0 : 1, n, F, split);
+  if (tiled && pl.wide) {
+    StreamParams q;
+    q.A = A; q.Xt = Xt; q.n = n; q.F = F; q.nc = nc;
+    q.rblocks = (n + 63) / 64;
+    q.rowb = (n + 127) / 128;
+    q.ksplit = pl.ksplit;
+    q.ldp = (F + Vec<T>::N - 1) / Vec<T>::N * Vec<T>::N;
+    q.part = pl.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + xt_bytes(sizeof(T) == 4 ? 0 : 1, n, F))
+                           : nullptr;
+    q.epi = epi;
+    switch (pl.tn) {
+      case 1: stream_launch<T, 1, 8>(q, s); break;
+      case 2: stream_launch<T, 2, 8>(q, s); break;
+      case 3: stream_launch<T, 3, 6>(q, s); break;
+      default: stream_launch<T, 4, 6>(q, s); break;
+    }
+    e = hipGetLastError();
+    if (e != hipSuccess || pl.ksplit == 1) return e;
     const int64_t vecs = n * (q.ldp / Vec<T>::N);
     hipLaunchKernelGGL(mm_reduce_kernel<T>, dim3((unsigned)((vecs + 255) / 256)), dim3(256), 0, s, q.part, pl.ksplit,
                        n, F, q.ldp, epi);
@@ -747,8 +959,12 @@ hipError_t densify_t(const CsrView& A, bool tiled, void* dense, int64_t ld, hipS
 
 }  // namespace
 
-size_t dense_agg_workspace_bytes(int prec, int64_t n, int64_t F, bool tiled) {
+size_t dense_agg_workspace_bytes(int prec, int64_t n, int64_t F, bool tiled, bool split) {
   size_t b = xt_bytes(prec, n, F);
+  if (tiled && !use_dense_mm(n, F)) {
+    const StreamPlan pl = stream_plan(prec, n, F, split);
+    if (pl.ksplit > 1) b += (size_t)pl.ksplit * (size_t)n * (size_t)((F + 7) / 8 * 8) * sizeof(float);
+  }
   if (tiled && use_dense_mm(n, F)) {
     const MmPlan pl = mm_plan(prec, n, F);
     const int64_t ve = prec == 0 ? 4 : 8;
@@ -763,11 +979,11 @@ int64_t dense_tiled_elems(int prec, int64_t n) {
 }
 
 hipError_t dense_agg_launch(int prec, const void* A, int64_t lda, bool tiled, int64_t n, const void* X, int64_t ldx,
-                            int64_t F, const Epilogue& epi, void* ws, float* colsum, hipStream_t s) {
+                            int64_t F, const Epilogue& epi, void* ws, float* colsum, hipStream_t s, bool split) {
   switch (prec) {
-    case 0: return launch_t<float>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, s);
-    case 1: return launch_t<f16>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, s);
-    case 2: return launch_t<bf16>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, s);
+    case 0: return launch_t<float>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, split, s);
+    case 1: return launch_t<f16>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, split, s);
+    case 2: return launch_t<bf16>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, split, s);
   }
   return hipErrorInvalidValue;
 }

@@ -128,10 +128,10 @@ hipError_t wgrad_launch(int prec, const void* H, int64_t ldh, const void* G, int
 // partials (dense_agg_workspace_bytes).  With colsum != NULL the
 // transposition also writes column-sum partials of X, [rows][F] floats with
 // rows = dense_agg_colsum_rows(); reduce with make_job(colsum, rows, 1, F, ..).
-size_t dense_agg_workspace_bytes(int prec, int64_t n, int64_t F, bool tiled);
+size_t dense_agg_workspace_bytes(int prec, int64_t n, int64_t F, bool tiled, bool split = true);
 int64_t dense_agg_colsum_rows(int prec, int64_t n);
 hipError_t dense_agg_launch(int prec, const void* A, int64_t lda, bool tiled, int64_t n, const void* X, int64_t ldx,
-                            int64_t F, const Epilogue& epi, void* ws, float* colsum, hipStream_t s);
+                            int64_t F, const Epilogue& epi, void* ws, float* colsum, hipStream_t s, bool split = true);
 // Elements of the tiled dense A_hat (rows padded to 64, columns to the chunk).
 int64_t dense_tiled_elems(int prec, int64_t n);
 // Dense A_hat from CSR: row-major (ld) or tiled operand order.
