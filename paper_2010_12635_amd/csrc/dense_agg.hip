@@ -345,7 +345,7 @@ __global__ __launch_bounds__(64 * DA_WAVES) void dense_agg_kernel(DaParams p) {
 //    loads in flight, the loads spread among the MFMAs;
 //  * where the row blocks alone would leave compute units idle, or a last
 //    round of workgroups nearly empty, the k range is also cut over `ksplit`
-//    workgroups per row block (rule at stream_plan), whose fp32 partial tiles
+//    workgroups per row block (rule at dense_plan), whose fp32 partial tiles
 //    mm_reduce_kernel adds in order;
 //  * the four waves' tiles are added through LDS in a fixed order.
 // ---------------------------------------------------------------------------
@@ -474,18 +474,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // ---------------------------------------------------------------------------
-// Wide features (F >= 128, the large model sizes of the paper's Table 1):
-// 2 n^2 F flops against s n^2 bytes of A_hat put the product far above the
-// ridge point, so this kernel is built around the matrix cores.
-//  * A workgroup of 4 waves owns a 256 x 256 output tile, each wave a
-//    128 x 128 quarter (8 x 8 MFMA 16x16 tiles, 256 fp32 accumulators per
-//    lane, one wave per SIMD).
-//  * Both operands come straight from global memory in MFMA operand order
-//    (tiled A_hat, tiled X^T): a fragment is one contiguous 1 KiB, 16 per
-//    k chunk per wave, with MM_DEPTH - 1 chunks in flight.  The two waves
-//    that share the rows (or the columns) of the tile read the same lines.
-//    (Staging the chunk through LDS, each fragment loaded once per
-//    workgroup, measured slower: 41 % against 54 % of the MFMA peak.)
+// Wide features (the large model sizes of the paper's Table 1): 2 n^2 F flops
+// against s n^2 bytes of A_hat put the product above the ridge point from
+// F of about 300 on, so this kernel is built around the matrix cores.
+//  * A workgroup of 4 waves (2 x 2, one per SIMD) owns up to a 256 x 256
+//    output tile, each wave a quarter of it (at most 8 x 8 MFMA 16x16 tiles,
+//    256 fp32 accumulators per lane).
+//  * Both operands are in MFMA operand order (tiled A_hat, tiled X^T), every
+//    fragment one contiguous 1 KiB.  Read straight into registers, each went
+//    through the vector cache twice per workgroup (two waves share it), and
+//    that path, 64 KB per chunk at 80-100 GB/s per compute unit, bound the
+//    kernel; so a chunk is now copied once, by global-to-LDS loads (up to 120
+//    GB/s per compute unit from L2, no registers held), into a ring of up to
+//    eight chunks in LDS, from which a wave reads its fragments one chunk
+//    ahead of the MFMAs (lane order: no bank conflicts).  One barrier per
+//    chunk.  n = 32768, F = 2048 fp16: 3.06 -> 2.49 ms (1.44 -> 1.77 PFLOP/s),
+//    same bits.  What bounds it now: LDS (96 KB per chunk read and written,
+//    0.31 us) beside 0.43 us of matrix instructions, issued by one wave.
 //  * Tiles are dealt out XCD by XCD: workgroup b runs on XCD b % 8, and each
 //    XCD takes a contiguous range of tiles in row-major order, so the column
 //    tiles of a row block run together and share A_hat in that XCD's L2
@@ -515,9 +520,9 @@ struct MmParams {
 };
 
 // Rows row0 .. row0 + 15, columns col0 .. col0 + W - 1 of the output from a
-// staged strip (16 x W fp32, stride MM_LDR), through the fused epilogue.  A
-// lane stores the same vector of columns in every row it takes (64 is a
-// multiple of W / Vec<T>::N), whose bias bv the caller loads once per tile.
+// staged strip (16 x W fp32, stride MM_LDR), through the fused epilogue.
+// Where 64 is a multiple of W / Vec<T>::N a lane stores the same vector of
+// columns in every row it takes, whose bias bv the caller loads once per tile.
 template <typename T, int W>
 __device__ __forceinline__ void mm_store_strip(const MmParams& p, const float* st, int lane, int64_t row0, int64_t col0,
                                                const float (&bv)[Vec<T>::N]) {
@@ -532,12 +537,12 @@ __device__ __forceinline__ void mm_store_strip(const MmParams& p, const float* s
     float v[OV];
 #pragma unroll
     for (int e = 0; e < OV; ++e) v[e] = st[r * MM_LDR + cv * OV + e];
-    epi_store_vec_b<T>(p.epi, row, col, v, bv);
+    // (three quarters of a power of two: the vector differs from row to row)
+    if constexpr (64 % VPR == 0) epi_store_vec_b<T>(p.epi, row, col, v, bv);
+    else epi_store_vec<T>(p.epi, row, col, v);
   }
 }
 
-// A wave owns WR x WC 64 x 64 blocks of the output (WR, WC in {1, 2}); the
-// workgroup's 2 x 2 waves own (128 WR) x (128 WC).
 // The same strip as fp32 partial products of k range `split`, for the
 // fixed-order reduction that applies the epilogue.
 template <int W, int OV>
@@ -583,11 +588,25 @@ __global__ __launch_bounds__(256) void mm_reduce_kernel(const float* __restrict_
   epi_store_vec<T>(epi, row, col0, acc);
 }
 
-template <typename T, int WR, int WC, int DEPTH>
+// 1 KiB from global memory straight into LDS (64 lanes x 16 bytes, lane order
+// kept): lane l's 16 bytes at base + voff go to lds + 16 l.  Counted by vmcnt;
+// written as asm because the compiler otherwise waits for every such load
+// before any LDS read.  No register is written.
+__device__ __forceinline__ void dma_1k(const void* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds) : "memory", "m0");
+}
+
+// A wave owns TM x TN 16 x 16 tiles, the workgroup's 2 x 2 waves (32 TM) x
+// (32 TN) of the output; S stages of one k chunk each in the LDS ring.
+template <typename T, int TM, int TN, int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void dense_mm_kernel(MmParams p) {
   constexpr int VE = Vec<T>::N, KC = 4 * VE, PIECE = 16 * KC;
-  constexpr int TM = 4 * WR, TN = 4 * WC;          // 16 x 16 MFMA tiles per wave
-  __shared__ float stage[4][16 * MM_LDR];
+  constexpr int RB = TM / 2, CB = TN / 2;          // 64-row blocks of A_hat and of X^T per workgroup
+  constexpr int NP = 4 * (RB + CB);                // 1 KiB pieces of a chunk
+  constexpr int LPW = NP / 4;                      // and per wave
+  static_assert(TM % 2 == 0 && TN % 2 == 0 && LPW <= TM && TN <= TM, "pieces and fragments spread over the TM tile rows");
+  constexpr int RING = S * NP * 1024, EPI = 4 * 16 * MM_LDR * 4;
+  __shared__ __align__(1024) unsigned char ring[RING > EPI ? RING : EPI];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t b = blockIdx.x;
@@ -598,20 +617,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int64_t split = u / p.tiles;
   const int64_t t = u - split * p.tiles;
   const int64_t tr = t / p.cb, tc = t - (t / p.cb) * p.cb;
-  const int64_t rb0 = (tr * 2 + (wave >> 1)) * WR;   // this wave's first 64-row block
-  const int64_t fb0 = (tc * 2 + (wave & 1)) * WC;    // and first 64-column block
   const int64_t c_lo = split * p.kc;                  // this workgroup's k chunks: [c_lo, c_lo + nc)
-  const int64_t nc = min(p.nc, c_lo + p.kc) - c_lo;   // >= 8 (the launch sizes the ranges so)
+  const int nc = (int)(min(p.nc, c_lo + p.kc) - c_lo);
   const int64_t blk = p.nc * 4 * PIECE;               // elements of one 64-row block
   const T* __restrict__ A = reinterpret_cast<const T*>(p.A);
   const T* __restrict__ Xt = reinterpret_cast<const T*>(p.Xt);
-  // blocks past the padded extent read the last one (never stored)
-  const T* abase[WR];
-  const T* bbase[WC];
+  // this wave's pieces of a chunk; blocks past the padded extent read the
+  // last one (never stored)
+  const T* src[LPW];
 #pragma unroll
-  for (int i = 0; i < WR; ++i) abase[i] = A + min(rb0 + i, p.rblocks - 1) * blk + c_lo * 4 * PIECE + lane * VE;
-#pragma unroll
-  for (int i = 0; i < WC; ++i) bbase[i] = Xt + min(fb0 + i, p.fblocks - 1) * blk + c_lo * 4 * PIECE + lane * VE;
+  for (int j = 0; j < LPW; ++j) {
+    const int pc = wave * LPW + j;
+    const bool isa = pc < 4 * RB;
+    const int q = isa ? pc : pc - 4 * RB;
+    const int64_t bi = isa ? min(tr * RB + q / 4, p.rblocks - 1) : min(tc * CB + q / 4, p.fblocks - 1);
+    src[j] = (isa ? A : Xt) + bi * blk + c_lo * 4 * PIECE + (q % 4) * PIECE;
+  }
+  const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
 
   f32x4 acc[TM][TN];
 #pragma unroll
@@ -620,93 +642,97 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   struct Fr { uint4 a[TM]; uint4 b[TN]; };
-  auto load = [&](Fr& f, int64_t c) {
-    c = c < nc ? c : nc - 1;                      // past the end: in bounds, unused
-    const int64_t off = c * 4 * PIECE;
-#pragma unroll
-    for (int i = 0; i < WR; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) f.a[i * 4 + q] = ldg16(abase[i] + off + q * PIECE);
-#pragma unroll
-    for (int i = 0; i < WC; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) f.b[i * 4 + q] = ldg16(bbase[i] + off + q * PIECE);
+  // fragments of this wave in a stage: its TM pieces of A_hat, its TN of X^T
+  const unsigned char* afrag = ring + (wave >> 1) * TM * 1024 + lane * 16;
+  const unsigned char* bfrag = ring + (4 * RB + (wave & 1) * TN) * 1024 + lane * 16;
+  auto issue = [&](int j, int c, int stage) {      // piece j of chunk c (past the end: in bounds, unused)
+    const int cc = c < nc ? c : nc - 1;
+    dma_1k(src[j], (uint32_t)cc * (4 * PIECE * sizeof(T)) + lane * 16, ring0 + stage * (NP * 1024) + (wave * LPW + j) * 1024);
   };
-  auto compute = [&](const Fr& f) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = DaMfma<T>::run(f.a[i], f.b[j], acc[i][j]);
+  auto read_a = [&](Fr& f, int i, int stage) {
+    f.a[i] = *reinterpret_cast<const uint4*>(afrag + stage * (NP * 1024) + i * 1024);
+  };
+  auto read_b = [&](Fr& f, int i, int stage) {
+    f.b[i] = *reinterpret_cast<const uint4*>(bfrag + stage * (NP * 1024) + i * 1024);
   };
 #define MM_FENCE() __builtin_amdgcn_sched_barrier(0)
-  // Loop steps of the 3-deep ring: the 4 (WR + WC) loads of one chunk are
-  // spread among the MFMAs of another, one load before every NM / NL MFMAs
-  // (the rest after the last load), instead of all loads first: the matrix
-  // pipe keeps issuing while the loads go out (measured 3.20 -> 2.99 ms at
-  // n = 32768, F = 2048, 1.60 -> 1.57 ms at F = 1024; for the 2-deep ring of
-  // the 256 x 128 tiles it was 2-4 % slower, so that loop keeps plain fences).
-  constexpr int NL = 4 * (WR + WC), NM = TM * TN * (sizeof(T) == 4 ? 4 : 1), PER = NM / NL;   // fp32: 4 MFMAs per pair
-#define MM_SCHED()                                                                   \
-  do {                                                                               \
-    _Pragma("unroll") for (int q_ = 0; q_ < NL; ++q_) {                              \
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   /* vector-memory read */  \
-      __builtin_amdgcn_sched_group_barrier(0x008, PER, 0); /* MFMA */                \
-    }                                                                                \
-    __builtin_amdgcn_sched_group_barrier(0x008, NM - PER * NL, 0);                   \
+  // every wave's loads but those of the newest `chunks` chunks have landed,
+  // and every wave holds what it read from LDS so far in registers
+#define MM_LANDED(chunks)                                                                    \
+  do {                                                                                       \
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((chunks) * LPW) : "memory");         \
+    __builtin_amdgcn_s_barrier();                                                            \
+    MM_FENCE();                                                                              \
   } while (0)
-  // The chunks that do not fill a whole trip of the unrolled loop are done
-  // first, so that nothing follows the loop: with a compute after it the
-  // register allocator rotates the accumulators on every trip.
-  // The launch guarantees n >= 256, i.e. nc >= 8 chunks, so each loop below
-  // runs at least once; written as do-while, it has no path that skips it
-  // (where such a path meets the loop exit the register allocator spills
-  // accumulators, and the reloads before the loop make the compiler wait
-  // for a whole chunk of loads more than the ring needs at the loop head).
-  if (DEPTH == 2) {
-    Fr f0, f1;
-    int64_t c = 0;
-    if (nc & 1) { load(f0, 0); compute(f0); c = 1; }
-    load(f0, c);
-    do {
-      load(f1, c + 1); MM_FENCE(); compute(f0); MM_FENCE();
-      load(f0, c + 2); MM_FENCE(); compute(f1); MM_FENCE();
-      c += 2;
-    } while (c + 2 <= nc);
+  // chunk c is in F; chunk c + 1 (stage s1) goes to G, chunk c + S into the
+  // stage s0 that chunk c was read from
+  auto step = [&](const Fr& F, Fr& G, int c, int s0, int s1) {
+    MM_LANDED(S - 2);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (i < LPW) issue(i, c + S, s0);
+      read_a(G, i, s1);
+      if (i < TN) read_b(G, i, s1);
+      MM_FENCE();
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = DaMfma<T>::run(F.a[i], F.b[j], acc[i][j]);
+      MM_FENCE();
+    }
+  };
+  auto next = [&](int s) { return s + 1 < S ? s + 1 : 0; };
+#pragma unroll
+  for (int d = 0; d < S; ++d)
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) issue(j, d, d);
+  MM_LANDED(S - 1);
+  Fr f0, f1;
+  // An odd chunk is done first, so that nothing follows the loop: with a
+  // compute after it the register allocator rotates the accumulators on
+  // every trip.  The launch guarantees nc >= 8, so the loop runs at least
+  // once (a path around it made the allocator spill accumulators).
+  int c = 0, s0 = 0;
+  if (nc & 1) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) read_a(f1, i, 0);
+#pragma unroll
+    for (int i = 0; i < TN; ++i) read_b(f1, i, 0);
+    step(f1, f0, 0, 0, 1);
+    c = 1;
+    s0 = 1;
   } else {
-    Fr f0, f1, f2;
-    int64_t c = 0;
-    const int64_t r3 = nc % 3;
-    if (r3 >= 1) { load(f0, 0); compute(f0); }
-    if (r3 >= 2) { load(f0, 1); compute(f0); }
-    c = r3;
-    load(f0, c);
-    load(f1, c + 1);
-    do {
-      load(f2, c + 2); compute(f0); MM_SCHED(); MM_FENCE();
-      load(f0, c + 3); compute(f1); MM_SCHED(); MM_FENCE();
-      load(f1, c + 4); compute(f2); MM_SCHED(); MM_FENCE();
-      c += 3;
-    } while (c + 3 <= nc);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) read_a(f0, i, 0);
+#pragma unroll
+    for (int i = 0; i < TN; ++i) read_b(f0, i, 0);
   }
+  do {
+    const int s1 = next(s0), s2 = next(s1);
+    step(f0, f1, c, s0, s1);
+    step(f1, f0, c + 1, s1, s2);
+    s0 = s2;
+    c += 2;
+  } while (c < nc);
+  MM_LANDED(0);                                    // the ring becomes the epilogue's staging area
 #undef MM_FENCE
-#undef MM_SCHED
+#undef MM_LANDED
 
   // epilogue: one 16-row strip of the wave's block at a time (the strip
   // index is spelled out so that every accumulator index is static); with
   // k ranges the strips go out as fp32 partials instead
-  float* st = stage[wave];
+  float* st = reinterpret_cast<float*>(ring) + wave * (16 * MM_LDR);
+  const int64_t row0 = (tr * 2 + (wave >> 1)) * (16 * TM), col0 = (tc * 2 + (wave & 1)) * (16 * TN);
   float bv[VE];
-  epi_load_bias<T>(p.epi, fb0 * 64 + (lane % (16 * TN / VE)) * VE, bv);
+  epi_load_bias<T>(p.epi, col0 + (lane % (16 * TN / VE)) * VE, bv);
   const bool partial = p.ksplit > 1;
-#define MM_STRIP(S)                                                                             \
-  if ((S) < TM) {                                                                               \
-    MM_SYNC();                                                                            \
+#define MM_STRIP(R)                                                                             \
+  if ((R) < TM) {                                                                               \
+    MM_SYNC();                                                                                  \
     _Pragma("unroll") for (int j = 0; j < TN; ++j)                                              \
       _Pragma("unroll") for (int v = 0; v < 4; ++v)                                             \
-        st[((lane >> 4) * 4 + v) * MM_LDR + j * 16 + (lane & 15)] = acc[(S) < TM ? (S) : 0][j][v]; \
-    MM_SYNC();                                                                            \
-    if (partial) mm_store_strip_part<16 * TN, VE>(p, st, lane, (rb0 + (S) / 4) * 64 + ((S) % 4) * 16, fb0 * 64, split); \
-    else mm_store_strip<T, 16 * TN>(p, st, lane, (rb0 + (S) / 4) * 64 + ((S) % 4) * 16, fb0 * 64, bv); \
+        st[((lane >> 4) * 4 + v) * MM_LDR + j * 16 + (lane & 15)] = acc[(R) < TM ? (R) : 0][j][v]; \
+    MM_SYNC();                                                                                  \
+    if (partial) mm_store_strip_part<16 * TN, VE>(p, st, lane, row0 + (R) * 16, col0, split);   \
+    else mm_store_strip<T, 16 * TN>(p, st, lane, row0 + (R) * 16, col0, bv);                    \
   }
   MM_STRIP(0) MM_STRIP(1) MM_STRIP(2) MM_STRIP(3) MM_STRIP(4) MM_STRIP(5) MM_STRIP(6) MM_STRIP(7)
 #undef MM_STRIP
@@ -723,109 +749,87 @@ size_t xt_bytes(int prec, int64_t n, int64_t F) {
   return ((size_t)xt_elems(prec, n, F) * (prec == 0 ? 4 : 2) + 255) / 256 * 256;
 }
 
-#ifndef MM_MIN_F
-#define MM_MIN_F 192
-#endif
-#ifndef MM_DEPTH
-#define MM_DEPTH 3
-#endif
-#ifndef MM_SMALL_TILES
-#define MM_SMALL_TILES 256
-#endif
-// The wide-feature kernel takes over from F >= MM_MIN_F (tiled A_hat):
-// 128 x 64 per wave up to F = 384, 128 x 128 above (measured on MI355X at
-// n = 32768: F = 256 0.72 ms against 0.92 ms, F = 2048 3.3 ms against
-// 4.8 ms; the streaming kernel takes 0.77 ms at F = 128, 1.5 ms at 256).
-bool use_dense_mm(int64_t n, int64_t F) { return F >= MM_MIN_F && n >= 256; }
-
-// Tile shape and k ranges of the wide kernel.  Fewer tiles than compute
-// units, 16-bit: first cut the k loop of every tile into 2, 4 or 8 ranges of
-// at least MM_SPLIT_MIN chunks each (their fp32 partials are added in range
-// order by a reduction that applies the epilogue), keeping the 128 x 128
-// accumulator tile per wave.  Where the k loop is too short for that, step
-// down to 256 x 128 or 128 x 128 workgroup tiles if that alone fills the
-// compute units, else cut the k loop into ranges of at least 8 chunks.
-// Measured in 16-bit: n = 16384, F = 512 (128 tiles): two ranges 0.29 ms,
-// 256 x 128 tiles 0.36 ms; n = 4096, F = 2048 (k loop of 128 chunks): two
-// ranges 0.108 ms, 256 x 128 tiles 0.10 ms; n = 4096, F = 512 (32 tiles):
-// eight ranges 0.054 ms, 128 x 128 tiles 0.061 ms.
-#ifndef MM_SPLIT_MIN
-#define MM_SPLIT_MIN 128
-#endif
-struct MmPlan { int wr, wc; int64_t ksplit, kc; };
-
-MmPlan mm_plan(int prec, int64_t n, int64_t F) {
-  const int64_t kcw = prec == 0 ? 16 : 32;
-  const int64_t nc = (n + kcw - 1) / kcw;
-  MmPlan pl{2, F > 384 ? 2 : 1, 1, nc};
-  auto tiles_of = [&](int wr, int wc) { return (n + 128 * wr - 1) / (128 * wr) * ((F + 128 * wc - 1) / (128 * wc)); };
-  auto split = [&](int64_t min_chunks) {
-    while (tiles_of(pl.wr, pl.wc) * pl.ksplit < MM_SMALL_TILES && pl.ksplit < 8) {
-      const int64_t k2 = pl.ksplit * 2, kc = (nc + k2 - 1) / k2;
-      if (kc < min_chunks || nc - (k2 - 1) * kc < 8) break;
-      pl.ksplit = k2;
-    }
-  };
-  if (prec == 0) {
-    // fp32 is bound by the matrix units at these widths, where smaller
-    // tiles cost only re-reads: step down first, then cut the k loop
-    // (n = 4096, F = 512: 885 epochs/s cutting the k loop of 256 x 256
-    // tiles, 1481 with 128 x 128 tiles)
-    if (tiles_of(pl.wr, pl.wc) < MM_SMALL_TILES) {
-      if (pl.wc == 2 && tiles_of(2, 1) >= MM_SMALL_TILES) pl.wc = 1;
-      else pl.wr = pl.wc = 1;
-    }
-    split(8);
-  } else {
-    split(MM_SPLIT_MIN);
-    if (pl.ksplit == 1 && tiles_of(pl.wr, pl.wc) < MM_SMALL_TILES) {
-      if (pl.wc == 2 && tiles_of(2, 1) >= MM_SMALL_TILES) pl.wc = 1;
-      else if (tiles_of(1, 1) >= MM_SMALL_TILES) pl.wr = pl.wc = 1;
-      else split(8);
-    }
-  }
-  pl.kc = (nc + pl.ksplit - 1) / pl.ksplit;
-  return pl;
-}
-
-// Which streaming kernel, and how many k ranges.  A compute unit brings in at
-// most about 48 GB/s through its vector cache, A_hat and X^T together
-// (measured: 46-50 GB/s for 47 to 256 workgroups, F = 16 and 64 alike), so a
-// row block costs (rows + columns) n s / 48 GB/s there, or its flops at the
-// matrix rate; the chip as a whole is held to the stream rate of A_hat; a
-// round of workgroups costs as much as its longest.  Candidates: 64-row blocks
-// over the whole k range (dense_agg_kernel), 128-row blocks over S ranges
-// (dense_stream_kernel, about 4 us of start and end per unit), S > 1 with the
-// reduction launch (about 7 us) and the partials' traffic.  The least time
-// wins, where it is 7 % less; S is bounded by ST_MAX_SPLIT, eight chunks a
-// range and ST_PART_BYTES of partials.  Measured, one call with the
-// transposition (us, 64-row blocks alone -> with this rule; F = 64):
-// 16-bit n = 6001 33 -> 28, 9000 52 -> 42, 20000 202 -> 157, 32768 364 -> 321;
-// fp32 n = 2048 40 -> 24, 6001 99 -> 56, 9000 148 -> 111, 20000 610 -> 432;
-// where the rule keeps the 64-row blocks (16-bit n = 2048, 3000, 12000,
-// 16384) the other candidate took 0 to 30 % longer.
-constexpr int64_t ST_MAX_SPLIT = 16;
+// How one product is cut: which kernel, its tile, its k ranges.  Every
+// candidate is priced in microseconds and the cheapest taken (one of the other
+// two kernels only where it is 7 % below the 64-row blocks).  What the prices
+// rest on, measured on MI355X:
+//  * a round of workgroups (one per compute unit) costs as much as its longest;
+//  * dense_agg_kernel and dense_stream_kernel, whose waves read fragments
+//    straight into registers: a compute unit brings in at most about 48 GB/s
+//    through its vector cache, A_hat and X^T together (46-50 GB/s for 47 to 256
+//    workgroups, F = 16 and 64 alike), or works at the matrix rate; the chip is
+//    held to the stream rate of A_hat, once per column block of 64;
+//  * dense_mm_kernel, 16-bit: a k chunk takes `near` us while A_hat fits the 256
+//    MB cache behind the L2s (up to NEAR_BYTES), else `far` + `s` / (column
+//    tiles), column tiles sharing a chunk of A_hat in L2, and at least `h` /
+//    (column tiles), the rate at which the bytes that the LDS ring keeps in
+//    flight come from HBM; fp32: `w32`, the matrix instructions;
+//  * a round costs its start and end (`fixed`; 4 to 7 us for 64-row blocks of several column blocks),
+//    k ranges the reduction launch and the partials' traffic; they are bounded
+//    by DP_MAX_SPLIT, eight chunks each and the bytes of the partials.
+// One call with the transposition (us, before -> with the LDS ring of
+// dense_mm_kernel, dense_stream_kernel and this rule), 16-bit: n = 16384 F =
+// 128 191 -> 124, F = 384 357 -> 190; n = 8192 F = 512 90 -> 64; n = 24000 F =
+// 256 539 -> 298; n = 32768 F = 160 1106 -> 406, F = 2048 3040 -> 2550; n =
+// 20000 F = 64 202 -> 157; fp32: n = 2048 F = 64 40 -> 23, n = 6001 99 -> 56, n
+// = 9000 F = 192 545 -> 245, n = 24000 F = 384 5598 -> 3261.
+constexpr int64_t DP_MAX_SPLIT = 16;
+constexpr int64_t DP_PART_BYTES = (int64_t)96 << 20;
 constexpr int64_t ST_PART_BYTES = (int64_t)24 << 20;
-struct StreamPlan { bool wide; int64_t ksplit; int tn; };
+enum DenseKind { DK_ROWS64, DK_STREAM, DK_MM };
+struct DensePlan {
+  DenseKind kind;
+  int tile;             // DK_MM: index of MM_TILES
+  int64_t ksplit, kc;   // k ranges, chunks per range
+};
+struct MmTile { int rows, cols; double near, far, s, h, w32, fixed; };
+constexpr MmTile MM_TILES[] = {
+    {256, 256, 0.56, 0.55, 0.12, 0.80, 3.55, 9.0},
+    {256, 192, 0.41, 0.45, 0.20, 0.72, 2.66, 8.5},
+    {256, 128, 0.30, 0.38, 0.30, 0.74, 1.78, 7.0},
+    {128, 128, 0.19, 0.24, 0.10, 0.39, 0.90, 5.5},
+};
+constexpr double NEAR_BYTES = 2e8;
 
-StreamPlan stream_plan(int prec, int64_t n, int64_t F, bool split) {
-  StreamPlan pl{false, 1, (int)std::min<int64_t>(4, (F + 15) / 16)};
-  if (F > 64) return pl;
+DensePlan dense_plan(int prec, int64_t n, int64_t F, bool tiled, bool split) {
   const int64_t nc = (n + (prec == 0 ? 15 : 31)) / (prec == 0 ? 16 : 32);
-  const double es = prec == 0 ? 4 : 2, dn = (double)n, cols = 16.0 * pl.tn;
-  const double cu_bytes = 4.8e4, chip_bytes = 6.8e6, part_bytes = 3e6;             // per us
-  auto unit = [&](double rows, double cu_flops) {
+  DensePlan pl{DK_ROWS64, 0, 1, nc};
+  if (!tiled) return pl;
+  const double es = prec == 0 ? 4 : 2, dn = (double)n;
+  const double cu_bytes = 4.8e4, chip = dn * dn * es / 6.8e6;                      // per us
+  auto rounds = [](int64_t units) { return (double)((units + 255) / 256); };
+  auto unit = [&](double rows, double cols, double cu_flops) {
     return std::max((rows + cols) * dn * es / cu_bytes, 2 * rows * dn * cols / cu_flops);
   };
-  const double chip = dn * dn * es / chip_bytes;
-  auto rounds = [&](int64_t units) { return (double)((units + 255) / 256); };
-  double best = std::max(rounds((n + 63) / 64) * unit(64, prec == 0 ? 4.8e5 : 4.8e6), chip);
-  const int64_t blocks = (n + 127) / 128, ldp = (F + 7) / 8 * 8;
-  for (int64_t S = 1; S <= ST_MAX_SPLIT; ++S) {
-    if (S > 1 && (!split || nc < 8 * S || S * n * ldp * 4 > ST_PART_BYTES)) break;
-    const double t = std::max(rounds(blocks * S) * (unit(128, prec == 0 ? 5.1e5 : 5.1e6) / S + 4.0), chip) +
-                     (S > 1 ? 7.0 + 8.0 * S * dn * F / part_bytes : 0.0);
-    if (t < 0.93 * best) { best = t; pl.ksplit = S; pl.wide = true; }
+  const int64_t cb64 = (F + 63) / 64, ldp = (F + 7) / 8 * 8;
+  const double cols = F > 64 ? 64.0 : 16.0 * ((F + 15) / 16);
+  const double ends = F <= 64 ? 0.0 : prec == 0 ? 7.0 : 4.0;
+  double best = 0.93 * std::max(rounds((n + 63) / 64 * cb64) * (unit(64, cols, prec == 0 ? 4.8e5 : 4.8e6) + ends), chip * cb64);
+  if (best < 8.0) return pl;                            // less than any other candidate's start and end
+  auto offer = [&](double t, DenseKind kind, int tile, int64_t S, int64_t kc) {
+    if (t < best) { best = t; pl = DensePlan{kind, tile, S, kc}; }
+  };
+  if (F <= 64) {
+    const int64_t blocks = (n + 127) / 128;
+    for (int64_t S = 1; S <= DP_MAX_SPLIT; ++S) {
+      if (S > 1 && (!split || nc < 8 * S || S * n * ldp * 4 > ST_PART_BYTES)) break;
+      offer(std::max(rounds(blocks * S) * (unit(128, cols, prec == 0 ? 5.1e5 : 5.1e6) / S + 4.0), chip) +
+                (S > 1 ? 7.0 + 8.0 * S * dn * F / 3e6 : 0.0),
+            DK_STREAM, 0, S, 0);
+    }
+    return pl;
+  }
+  for (int i = 0; nc >= 8 && i < 4; ++i) {
+    const MmTile& t = MM_TILES[i];
+    const int64_t ct = (F + t.cols - 1) / t.cols, tiles = (n + t.rows - 1) / t.rows * ct;
+    const double chunk = prec == 0 ? std::max(t.w32, t.h / ct)
+                         : dn * dn * es <= NEAR_BYTES ? t.near : std::max(t.far + t.s / ct, t.h / ct);
+    for (int64_t S = 1; S <= DP_MAX_SPLIT; ++S) {
+      const int64_t kc = (nc + S - 1) / S;
+      if (S > 1 && (!split || kc < 8 || S * n * ldp * 4 > DP_PART_BYTES)) break;
+      if (nc - (S - 1) * kc < 8) continue;
+      offer(rounds(tiles * S) * (kc * chunk + t.fixed) + (S > 1 ? 6.0 + 8.0 * S * dn * F / 9e6 : 0.0), DK_MM, i, S, kc);
+    }
   }
   return pl;
 }
@@ -847,57 +851,54 @@ hipError_t launch_t(const void* A, int64_t lda, bool tiled, int64_t n, const voi
                      colsum);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (tiled && use_dense_mm(n, F)) {
-    const MmPlan pl = mm_plan(sizeof(T) == 4 ? 0 : 1, n, F);
-    const int WR = pl.wr, WC = pl.wc;
+  const DensePlan pl = dense_plan(sizeof(T) == 4 ? 0 : 1, n, F, tiled, split);
+  const int64_t ldp = (F + Vec<T>::N - 1) / Vec<T>::N * Vec<T>::N;
+  float* part = pl.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + xt_bytes(sizeof(T) == 4 ? 0 : 1, n, F))
+                              : nullptr;
+  if (pl.kind == DK_MM) {
+    const MmTile& t = MM_TILES[pl.tile];
     MmParams q;
     q.A = A; q.Xt = Xt; q.n = n; q.F = F; q.nc = nc;
     q.rblocks = (n + 63) / 64;
     q.fblocks = fblocks;
-    const int64_t rt = (n + 128 * WR - 1) / (128 * WR);
-    q.cb = (F + 128 * WC - 1) / (128 * WC);
-    q.tiles = rt * q.cb;
+    q.cb = (F + t.cols - 1) / t.cols;
+    q.tiles = (n + t.rows - 1) / t.rows * q.cb;
     q.ksplit = pl.ksplit;
     q.kc = pl.kc;
-    q.part = pl.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + xt_bytes(sizeof(T) == 4 ? 0 : 1, n, F))
-                           : nullptr;
-    q.ldp = (F + Vec<T>::N - 1) / Vec<T>::N * Vec<T>::N;
+    q.part = part;
+    q.ldp = ldp;
     q.per_xcd = (q.tiles * q.ksplit + 7) / 8;
     q.epi = epi;
     const dim3 g((unsigned)(8 * q.per_xcd));
-    if (WR == 1) hipLaunchKernelGGL((dense_mm_kernel<T, 1, 1, MM_DEPTH>), g, dim3(256), 0, s, q);
-    else if (WC == 2) hipLaunchKernelGGL((dense_mm_kernel<T, 2, 2, MM_DEPTH>), g, dim3(256), 0, s, q);
-    else hipLaunchKernelGGL((dense_mm_kernel<T, 2, 1, 2>), g, dim3(256), 0, s, q);
-    e = hipGetLastError();
-    if (e != hipSuccess || pl.ksplit == 1) return e;
-    // the k ranges' partials, added in range order, through the epilogue
-    const int64_t vecs = n * (q.ldp / Vec<T>::N);
-    hipLaunchKernelGGL(mm_reduce_kernel<T>, dim3((unsigned)((vecs + 255) / 256)), dim3(256), 0, s, q.part, pl.ksplit,
-                       n, F, q.ldp, epi);
-    return hipGetLastError();
-  }
-  const StreamPlan pl = stream_plan(sizeof(T) == 4 ? 0 : 1, n, F, split);
-  if (tiled && pl.wide) {
+    switch (pl.tile) {
+      case 0: hipLaunchKernelGGL((dense_mm_kernel<T, 8, 8, 4>), g, dim3(256), 0, s, q); break;
+      case 1: hipLaunchKernelGGL((dense_mm_kernel<T, 8, 6, 5>), g, dim3(256), 0, s, q); break;
+      case 2: hipLaunchKernelGGL((dense_mm_kernel<T, 8, 4, 6>), g, dim3(256), 0, s, q); break;
+      default: hipLaunchKernelGGL((dense_mm_kernel<T, 4, 4, 8>), g, dim3(256), 0, s, q); break;
+    }
+  } else if (pl.kind == DK_STREAM) {
     StreamParams q;
     q.A = A; q.Xt = Xt; q.n = n; q.F = F; q.nc = nc;
     q.rblocks = (n + 63) / 64;
     q.rowb = (n + 127) / 128;
     q.ksplit = pl.ksplit;
-    q.ldp = (F + Vec<T>::N - 1) / Vec<T>::N * Vec<T>::N;
-    q.part = pl.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + xt_bytes(sizeof(T) == 4 ? 0 : 1, n, F))
-                           : nullptr;
+    q.ldp = ldp;
+    q.part = part;
     q.epi = epi;
-    switch (pl.tn) {
+    switch ((F + 15) / 16) {
       case 1: stream_launch<T, 1, 8>(q, s); break;
       case 2: stream_launch<T, 2, 8>(q, s); break;
       case 3: stream_launch<T, 3, 6>(q, s); break;
       default: stream_launch<T, 4, 6>(q, s); break;
     }
+  }
+  if (pl.kind != DK_ROWS64) {
     e = hipGetLastError();
     if (e != hipSuccess || pl.ksplit == 1) return e;
-    const int64_t vecs = n * (q.ldp / Vec<T>::N);
-    hipLaunchKernelGGL(mm_reduce_kernel<T>, dim3((unsigned)((vecs + 255) / 256)), dim3(256), 0, s, q.part, pl.ksplit,
-                       n, F, q.ldp, epi);
+    // the k ranges' partials, added in range order, through the epilogue
+    const int64_t vecs = n * (ldp / Vec<T>::N);
+    hipLaunchKernelGGL(mm_reduce_kernel<T>, dim3((unsigned)((vecs + 255) / 256)), dim3(256), 0, s, part, pl.ksplit,
+                       n, F, ldp, epi);
     return hipGetLastError();
   }
   DaParams p;
@@ -960,17 +961,9 @@ hipError_t densify_t(const CsrView& A, bool tiled, void* dense, int64_t ld, hipS
 }  // namespace
 
 size_t dense_agg_workspace_bytes(int prec, int64_t n, int64_t F, bool tiled, bool split) {
-  size_t b = xt_bytes(prec, n, F);
-  if (tiled && !use_dense_mm(n, F)) {
-    const StreamPlan pl = stream_plan(prec, n, F, split);
-    if (pl.ksplit > 1) b += (size_t)pl.ksplit * (size_t)n * (size_t)((F + 7) / 8 * 8) * sizeof(float);
-  }
-  if (tiled && use_dense_mm(n, F)) {
-    const MmPlan pl = mm_plan(prec, n, F);
-    const int64_t ve = prec == 0 ? 4 : 8;
-    if (pl.ksplit > 1) b += (size_t)pl.ksplit * (size_t)n * (size_t)((F + ve - 1) / ve * ve) * sizeof(float);
-  }
-  return b;
+  const DensePlan pl = dense_plan(prec, n, F, tiled, split);
+  return xt_bytes(prec, n, F) +
+         (pl.ksplit > 1 ? (size_t)pl.ksplit * (size_t)n * (size_t)((F + 7) / 8 * 8) * sizeof(float) : 0);
 }
 
 int64_t dense_tiled_elems(int prec, int64_t n) {

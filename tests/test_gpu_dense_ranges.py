@@ -1,8 +1,10 @@
-"""The streaming dense aggregation (F <= 64) where its row blocks, column
-tiles and k ranges end: 64-row blocks alone, 128-row blocks with one and with
-several k ranges (fewer row blocks than compute units, or a last round of them
-nearly empty), ragged n and F, in every storage type, against float64 on the
-stored values; and the workspace rule of the k ranges."""
+"""The tiled dense aggregation where its row blocks, column tiles and k
+ranges end, ragged n and F, in every storage type, against float64 on the
+stored values: F <= 64 with 64-row blocks alone and 128-row blocks with one and
+with several k ranges (fewer row blocks than compute units, or a last round of
+them nearly empty); wider F with each tile of the matrix-core kernel, whole
+and cut k ranges, odd and even chunk counts; and the workspace rule of the k
+ranges."""
 import numpy as np
 import pytest
 import torch
@@ -28,12 +30,16 @@ CASES = [
     # fp32: from ranges of a few chunks up
     (0, 140, 64), (0, 1100, 64), (0, 2049, 1), (0, 2048, 32), (0, 3001, 16), (0, 6001, 48), (0, 8191, 63),
     (0, 20000, 64),
+    # wide: 64-row blocks, then 128 x 128, 256 x 128, 256 x 192 and 256 x 256 tiles
+    (1, 257, 70), (1, 1100, 100), (2, 1100, 520), (1, 2500, 130), (2, 2529, 200), (1, 4096, 1000), (2, 6000, 250),
+    (1, 6001, 2040), (1, 8200, 380), (2, 12000, 129), (1, 12001, 1000), (1, 16384, 100), (2, 16384, 512),
+    (0, 257, 70), (0, 700, 300), (0, 2500, 192), (0, 4100, 200), (0, 5001, 1030),
 ]
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("prec,n,F", CASES, ids=lambda v: str(v))
-def test_stream_aggregation(prec, n, F):
+def test_tiled_aggregation(prec, n, F):
     dt = G.torch_dtype(prec)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n + F)
