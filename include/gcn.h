@@ -31,7 +31,7 @@
  *            ignored; columns [f, ld) of an output may be overwritten with 0.
  * Streams.   `stream` is a hipStream_t (NULL = default stream).  All calls are
  *            asynchronous on it, except gcn_normalize and gcn_schedule, which
- *            synchronise it (once and twice) to return sizes to the host.
+ *            synchronise it (once each) to return sizes to the host.
  * Errors.    Every call validates its arguments on the host before it
  *            launches anything and returns a gcn_status; a call that returns
  *            an argument error has had no effect.  GCN_ERR_DEVICE reports a
@@ -257,7 +257,7 @@ gcn_status gcn_densify(const gcn_adj* A, int32_t format, int32_t value_prec, voi
  * col_parts 1); col_parts must
  * otherwise be 1, 8, 16, 32 or 64 (GCN_ERR_INVALID_ARG).  sched: device
  * buffer of at least gcn_schedule_size() bytes (same arguments) that must
- * outlive every use of *A.  Synchronises `stream` twice.
+ * outlive every use of *A.  Synchronises `stream` once.
  * ------------------------------------------------------------------------- */
 gcn_status gcn_schedule_size(int64_t n, int64_t nnz, int64_t heavy_threshold, int64_t chunk_nnz,
                              int64_t col_parts, size_t* bytes);

@@ -20,7 +20,6 @@
 #include "radix.h"
 
 #include <algorithm>
-#include <vector>
 
 namespace gcn {
 
@@ -40,49 +39,63 @@ int64_t scan_scratch_elems(int64_t count) {
 }
 
 // ------------------------------------------------------------------ scan ----
-__global__ __launch_bounds__(256) void scan_block_kernel(int64_t* __restrict__ data, int64_t count,
-                                                         int64_t* __restrict__ block_sums) {
-  __shared__ int64_t s[256];
+// Four row counts scanned together: two int64 of two 32-bit halves each
+// (every total stays below 2^31, so no half carries into the other).
+struct Counts4 {
+  int64_t a, b;
+  __device__ __forceinline__ Counts4 operator+(const Counts4& o) const { return {a + o.a, b + o.b}; }
+  __device__ __forceinline__ Counts4 operator-(const Counts4& o) const { return {a - o.a, b - o.b}; }
+  __host__ __device__ static int64_t pack(int64_t hi, int64_t lo) { return hi << 32 | lo; }
+  __host__ __device__ static int64_t hi(int64_t x) { return x >> 32; }
+  __host__ __device__ static int64_t lo(int64_t x) { return x & 0xffffffffll; }
+};
+
+template <typename V>
+__global__ __launch_bounds__(256) void scan_block_kernel(V* __restrict__ data, int64_t count,
+                                                         V* __restrict__ block_sums) {
+  __shared__ V s[256];
   const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + threadIdx.x * 4;
-  int64_t v[4];
+  V v[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = base + i < count ? data[base + i] : 0;
-  const int64_t tsum = v[0] + v[1] + v[2] + v[3];
+  for (int i = 0; i < 4; ++i) v[i] = base + i < count ? data[base + i] : V{};
+  const V tsum = v[0] + v[1] + v[2] + v[3];
   s[threadIdx.x] = tsum;
   __syncthreads();
   for (int off = 1; off < 256; off <<= 1) {
-    const int64_t add = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
+    const V add = threadIdx.x >= off ? s[threadIdx.x - off] : V{};
     __syncthreads();
-    s[threadIdx.x] += add;
+    s[threadIdx.x] = s[threadIdx.x] + add;
     __syncthreads();
   }
-  int64_t run = s[threadIdx.x] - tsum;   // exclusive prefix of this thread
+  V run = s[threadIdx.x] - tsum;   // exclusive prefix of this thread
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     if (base + i < count) data[base + i] = run;
-    run += v[i];
+    run = run + v[i];
   }
   if (threadIdx.x == 255 && block_sums) block_sums[blockIdx.x] = s[255];
 }
 
-__global__ __launch_bounds__(256) void scan_add_kernel(int64_t* __restrict__ data, int64_t count,
-                                                       const int64_t* __restrict__ block_off) {
+template <typename V>
+__global__ __launch_bounds__(256) void scan_add_kernel(V* __restrict__ data, int64_t count,
+                                                       const V* __restrict__ block_off) {
   const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + threadIdx.x * 4;
-  const int64_t add = block_off[blockIdx.x];
+  const V add = block_off[blockIdx.x];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    if (base + i < count) data[base + i] += add;
+    if (base + i < count) data[base + i] = data[base + i] + add;
 }
 
 // In-place exclusive scan of data[0..count); scratch holds scan_scratch_elems(count).
-hipError_t scan_exclusive(int64_t* data, int64_t count, int64_t* scratch, hipStream_t s) {
+template <typename V>
+hipError_t scan_exclusive(V* data, int64_t count, V* scratch, hipStream_t s) {
   const int64_t nb = (count + SCAN_BLOCK - 1) / SCAN_BLOCK;
-  hipLaunchKernelGGL(scan_block_kernel, dim3((unsigned)nb), dim3(256), 0, s, data, count, nb > 1 ? scratch : nullptr);
+  hipLaunchKernelGGL(scan_block_kernel<V>, dim3((unsigned)nb), dim3(256), 0, s, data, count, nb > 1 ? scratch : nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || nb <= 1) return e;
   e = scan_exclusive(scratch, nb, scratch + nb, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)nb), dim3(256), 0, s, data, count, scratch);
+  hipLaunchKernelGGL(scan_add_kernel<V>, dim3((unsigned)nb), dim3(256), 0, s, data, count, scratch);
   return hipGetLastError();
 }
 
@@ -100,12 +113,6 @@ unsigned grid_for(int64_t items, int per_block = 256, int64_t cap = 65536) {
 }
 
 // ---------------------------------------------------------------- kernels ----
-// out[r] = in[r], out[n] = 0
-__global__ void widen_kernel(int64_t n, const int32_t* __restrict__ in, int64_t* __restrict__ out) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= n; r += (int64_t)gridDim.x * blockDim.x)
-    out[r] = r < n ? (int64_t)in[r] : 0;
-}
-
 // Item i of the sort: pair i forwards, pair i - E backwards, then the
 // self-loops.  A pair with a vertex id outside [0, n) raises *bad and stands
 // for the self-loop of vertex 0.
@@ -273,43 +280,38 @@ __device__ __forceinline__ int64_t range_end(const int32_t* __restrict__ colidx,
   return lo;
 }
 
-template <typename IdxT>
-__global__ void piece_count_kernel(int64_t n, const IdxT* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-                                   int64_t thr, int64_t seg, int64_t parts, int64_t* __restrict__ flag,
-                                   int64_t* __restrict__ npieces) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= n; r += (int64_t)gridDim.x * blockDim.x) {
-    if (r == n) { flag[n] = 0; npieces[n] = 0; continue; }
-    const int64_t beg = (int64_t)rowptr[r], end = (int64_t)rowptr[r + 1];
-    if (end - beg <= thr) { flag[r] = 0; npieces[r] = 0; continue; }
-    int64_t cnt = 0, a = beg;
-    for (int64_t q = 0; q < parts; ++q) {
-      const int64_t b = q + 1 == parts ? end : range_end(colidx, a, end, range_first(q + 1, n, parts));
-      cnt += (b - a + seg - 1) / seg;
-      a = b;
-    }
-    flag[r] = 1;
-    npieces[r] = cnt;
-  }
+// A heavy row's share of the scan: itself and its pieces; whether the fix-up
+// adds its partials with a whole workgroup or with a lane group.
+__device__ __forceinline__ Counts4 row_counts(int64_t pieces) {
+  const int64_t big = pieces > GCN_FIX_BIG_PIECES, small = pieces >= 2 && pieces <= GCN_FIX_BIG_PIECES;
+  return {Counts4::pack(1, pieces), Counts4::pack(big, small)};
 }
 
+// The scan of the rows' counts (heavy rows, their pieces; rows of many and of
+// a few pieces) says where everything of a row goes: its slot in heavy_rows,
+// its pieces, its place in fix_rows (rows of many pieces first).
 template <typename IdxT>
 __global__ void piece_fill_kernel(int64_t n, int64_t nnz, const IdxT* __restrict__ rowptr,
                                   const int32_t* __restrict__ colidx, int64_t thr, int64_t seg, int64_t parts,
-                                  const int64_t* __restrict__ hidx, const int64_t* __restrict__ poff,
-                                  int32_t* __restrict__ heavy_rows, int32_t* __restrict__ heavy_chunk_off,
-                                  int32_t* __restrict__ chunk_heavy, int64_t* __restrict__ chunk_beg) {
+                                  const Counts4* __restrict__ off, int32_t* __restrict__ heavy_rows,
+                                  int32_t* __restrict__ heavy_chunk_off, int32_t* __restrict__ chunk_heavy,
+                                  int64_t* __restrict__ chunk_beg, int32_t* __restrict__ fix_rows) {
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= n; r += (int64_t)gridDim.x * blockDim.x) {
     if (r == n) {
-      heavy_chunk_off[hidx[n]] = (int32_t)poff[n];
-      chunk_beg[poff[n]] = nnz;
+      const int64_t t = off[n].a;
+      heavy_chunk_off[Counts4::hi(t)] = (int32_t)Counts4::lo(t);
+      chunk_beg[Counts4::lo(t)] = nnz;
       continue;
     }
     const int64_t beg = (int64_t)rowptr[r], end = (int64_t)rowptr[r + 1];
     if (end - beg <= thr) continue;
-    const int64_t h = hidx[r];
+    const Counts4 o = off[r], o1 = off[r + 1];
+    const int64_t h = Counts4::hi(o.a);
     heavy_rows[h] = (int32_t)r;
-    heavy_chunk_off[h] = (int32_t)poff[r];
-    int64_t c = poff[r], a = beg;
+    heavy_chunk_off[h] = (int32_t)Counts4::lo(o.a);
+    if (Counts4::hi(o1.b) != Counts4::hi(o.b)) fix_rows[Counts4::hi(o.b)] = (int32_t)h;
+    else if (Counts4::lo(o1.b) != Counts4::lo(o.b)) fix_rows[Counts4::hi(off[n].b) + Counts4::lo(o.b)] = (int32_t)h;
+    int64_t c = Counts4::lo(o.a), a = beg;
     for (int64_t q = 0; q < parts; ++q) {
       const int64_t b = q + 1 == parts ? end : range_end(colidx, a, end, range_first(q + 1, n, parts));
       for (int64_t k = a; k < b; k += seg) {
@@ -366,9 +368,15 @@ __device__ __forceinline__ void row_range(int64_t n, int64_t* r0, int64_t* r1) {
   *r1 = *r0 + per < n ? *r0 + per : n;
 }
 
+// Per row: its counts for the scan (counts[n] = 0), and, for a light row, its
+// bucket's histogram.  A workgroup takes 1024 rows or more, so that the global
+// atomics, one per bucket and workgroup, stay few (a workgroup per 256 rows
+// spent 20 us on them at 262144 rows).
 template <typename IdxT>
-__global__ __launch_bounds__(256) void light_hist_kernel(int64_t n, const IdxT* __restrict__ rowptr, int64_t thr,
-                                                         int64_t blk, int64_t nb, int32_t* __restrict__ hist) {
+__global__ __launch_bounds__(256) void row_count_kernel(int64_t n, const IdxT* __restrict__ rowptr,
+                                                        const int32_t* __restrict__ colidx, int64_t thr, int64_t seg,
+                                                        int64_t parts, int64_t blk, int64_t nb,
+                                                        Counts4* __restrict__ counts, int32_t* __restrict__ hist) {
   __shared__ int32_t lh[LIGHT_LDS_BINS + 1];
   for (int b = threadIdx.x; b <= LIGHT_LDS_BINS; b += 256) lh[b] = 0;
   __syncthreads();
@@ -376,13 +384,24 @@ __global__ __launch_bounds__(256) void light_hist_kernel(int64_t n, const IdxT* 
   row_range(n, &r0, &r1);
   const int64_t base = (r0 / blk) * (thr + 1);
   for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
-    const int64_t d = (int64_t)rowptr[r + 1] - (int64_t)rowptr[r];
-    if (d > thr) continue;
+    const int64_t beg = (int64_t)rowptr[r], end = (int64_t)rowptr[r + 1], d = end - beg;
+    if (d > thr) {
+      int64_t cnt = 0, a = beg;
+      for (int64_t q = 0; q < parts; ++q) {
+        const int64_t b = q + 1 == parts ? end : range_end(colidx, a, end, range_first(q + 1, n, parts));
+        cnt += (b - a + seg - 1) / seg;
+        a = b;
+      }
+      counts[r] = row_counts(cnt);
+      continue;
+    }
+    counts[r] = Counts4{};
     const int64_t b = light_bucket(r, d, thr, blk, nb);
     const int k = light_slot(b, base, nb);
     if (k >= 0) atomicAdd(&lh[k], 1);
     else atomicAdd(&hist[b], 1);
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) counts[n] = Counts4{};
   __syncthreads();
   for (int k = threadIdx.x; k <= LIGHT_LDS_BINS; k += 256) {
     const int64_t b = slot_bucket(k, base, nb);
@@ -390,10 +409,13 @@ __global__ __launch_bounds__(256) void light_hist_kernel(int64_t n, const IdxT* 
   }
 }
 
+// Places the light rows: row_perm and, so that a lane group learns where a row
+// lies with one load, their 16-byte descriptors {first entry, row, length}.
 template <typename IdxT>
 __global__ __launch_bounds__(256) void light_scatter_kernel(int64_t n, const IdxT* __restrict__ rowptr, int64_t thr,
                                                             int64_t blk, int64_t nb, const int64_t* __restrict__ boff,
-                                                            int32_t* __restrict__ cur, int32_t* __restrict__ perm) {
+                                                            int32_t* __restrict__ cur, int32_t* __restrict__ perm,
+                                                            RowDesc* __restrict__ desc) {
   __shared__ int32_t lh[LIGHT_LDS_BINS + 1];     // count, then this workgroup's base within the bucket
   __shared__ int32_t lc[LIGHT_LDS_BINS + 1];     // local cursor
   for (int b = threadIdx.x; b <= LIGHT_LDS_BINS; b += 256) { lh[b] = 0; lc[b] = 0; }
@@ -414,12 +436,13 @@ __global__ __launch_bounds__(256) void light_scatter_kernel(int64_t n, const Idx
   }
   __syncthreads();
   for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
-    const int64_t d = (int64_t)rowptr[r + 1] - (int64_t)rowptr[r];
+    const int64_t beg = (int64_t)rowptr[r], d = (int64_t)rowptr[r + 1] - beg;
     if (d > thr) continue;
     const int64_t b = light_bucket(r, d, thr, blk, nb);
     const int k = light_slot(b, base, nb);
-    const int64_t pos = k >= 0 ? (int64_t)lh[k] + atomicAdd(&lc[k], 1) : (int64_t)atomicAdd(&cur[b], 1);
-    perm[boff[b] + pos] = (int32_t)r;
+    const int64_t pos = boff[b] + (k >= 0 ? (int64_t)lh[k] + atomicAdd(&lc[k], 1) : (int64_t)atomicAdd(&cur[b], 1));
+    perm[pos] = (int32_t)r;
+    desc[pos] = RowDesc{beg, (int32_t)r, (int32_t)d};
   }
 }
 
@@ -427,86 +450,122 @@ __global__ __launch_bounds__(256) void light_scatter_kernel(int64_t n, const Idx
 // their first entry (CHUNK_BUCKETS buckets over [0, n)).  The bucket of a
 // column, c * 4096 / n, nests in its column range c * P / n for every P
 // that divides 4096, so the sorted pieces of range p are one run, starting
-// at the offset of bucket p * 4096 / P.
+// at the offset of bucket p * 4096 / P.  The first pieces of the hubs crowd
+// into the lowest buckets, so a workgroup counts its pieces in LDS first (one
+// global atomic per piece took 33 us for 27,000 pieces, twice).
 constexpr int64_t CHUNK_BUCKETS = 4096;
 
-__global__ void part_off_kernel(int64_t parts, const int64_t* __restrict__ boff, int64_t* __restrict__ part_off) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q <= parts) part_off[q] = boff[q * (CHUNK_BUCKETS / parts)];
+// Pieces [c0, c1) of this workgroup; *total = all of them.
+__device__ __forceinline__ void piece_range(const Counts4* __restrict__ total, int64_t* c0, int64_t* c1) {
+  const int64_t m = Counts4::lo(total->a), per = (m + gridDim.x - 1) / gridDim.x;
+  *c0 = (int64_t)blockIdx.x * per;
+  *c1 = *c0 + per < m ? *c0 + per : m;
 }
 
-// 16-byte descriptors in launch order, so that a lane group learns where a
-// row or piece lies with one load: light rows {first entry, row, length};
-// pieces {first entry, row, length | 2^31 if the row has no other piece},
-// plus the launch position of every piece (its partial row's slot).
-template <typename IdxT>
-__global__ void light_desc_kernel(int64_t n_light, const IdxT* __restrict__ rowptr, const int32_t* __restrict__ perm,
-                                  RowDesc* __restrict__ desc) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_light; i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t r = perm[i];
-    const int64_t b = (int64_t)rowptr[r];
-    desc[i] = RowDesc{b, r, (int32_t)((int64_t)rowptr[r + 1] - b)};
+__device__ __forceinline__ int chunk_bucket(int64_t n, int32_t col) { return (int)((int64_t)col * CHUNK_BUCKETS / n); }
+
+__global__ __launch_bounds__(256) void chunk_hist_kernel(int64_t n, const Counts4* __restrict__ total,
+                                                         const int32_t* __restrict__ colidx,
+                                                         const int64_t* __restrict__ chunk_beg,
+                                                         int32_t* __restrict__ hist) {
+  __shared__ int32_t lh[CHUNK_BUCKETS];
+  int64_t c0, c1;
+  piece_range(total, &c0, &c1);
+  if (c0 >= c1) return;
+  for (int b = threadIdx.x; b < CHUNK_BUCKETS; b += 256) lh[b] = 0;
+  __syncthreads();
+  for (int64_t c = c0 + threadIdx.x; c < c1; c += 256) atomicAdd(&lh[chunk_bucket(n, colidx[chunk_beg[c]])], 1);
+  __syncthreads();
+  for (int b = threadIdx.x; b < CHUNK_BUCKETS; b += 256)
+    if (lh[b]) atomicAdd(&hist[b], lh[b]);
+}
+
+// Results of a schedule, read back by the host in one copy.
+struct SchedTotals {
+  int64_t rows_a, rows_b;      // Counts4 totals
+  int64_t n_light, n_multi;    // light rows; of them, rows of several entries
+  int64_t slots;               // most pieces on one XCD
+};
+
+// Bucket offsets from the histograms (workgroup 0: light rows, nb buckets;
+// workgroup 1: pieces), the column ranges' piece offsets and the totals.
+__global__ __launch_bounds__(1024) void bucket_scan_kernel(int64_t nb, const int32_t* __restrict__ lhist,
+                                                           int64_t* __restrict__ loff, const int32_t* __restrict__ chist,
+                                                           int64_t* __restrict__ coff, int64_t parts,
+                                                           int64_t* __restrict__ part_off,
+                                                           const Counts4* __restrict__ rows, SchedTotals* __restrict__ out) {
+  __shared__ int64_t red[16];
+  const int32_t* hist = blockIdx.x ? chist : lhist;
+  int64_t* off = blockIdx.x ? coff : loff;
+  const int64_t m = blockIdx.x ? CHUNK_BUCKETS : nb;
+  const int64_t per = (m + 1023) / 1024;
+  const int64_t b0 = threadIdx.x * per < m ? threadIdx.x * per : m, b1 = b0 + per < m ? b0 + per : m;
+  int64_t sum = 0;
+  for (int64_t b = b0; b < b1; ++b) sum += hist[b];
+  int64_t run = radix_block_scan<1024, int64_t>(sum, red);
+  for (int64_t b = b0; b < b1; ++b) {
+    off[b] = run;
+    if (!blockIdx.x && b == nb - 1) out->n_multi = run;
+    run += hist[b];
+  }
+  if (threadIdx.x == 1023) {                          // past the last bucket: the total
+    off[m] = run;
+    if (!blockIdx.x) {
+      out->n_light = run;
+      out->rows_a = rows->a;
+      out->rows_b = rows->b;
+    }
+  }
+  if (!blockIdx.x) return;
+  __syncthreads();                                    // the offsets written above are visible to the workgroup
+  for (int64_t q = threadIdx.x; q <= parts; q += 1024) part_off[q] = coff[q * (CHUNK_BUCKETS / parts)];
+  if (threadIdx.x == 0) {                             // ranges x, x + 8, ... run on XCD x
+    int64_t most = coff[CHUNK_BUCKETS];
+    if (parts > 1) {
+      most = 0;
+      for (int64_t x = 0; x < XCDS; ++x) {
+        int64_t t = 0;
+        for (int64_t q = x; q < parts; q += XCDS)
+          t += coff[(q + 1) * (CHUNK_BUCKETS / parts)] - coff[q * (CHUNK_BUCKETS / parts)];
+        if (t > most) most = t;
+      }
+    }
+    out->slots = most;
   }
 }
 
+// Places the pieces: chunk_order, their launch positions and their 16-byte
+// descriptors {first entry, row, length | 2^31 if the row has no other piece}.
 template <typename IdxT>
-__global__ void piece_desc_kernel(int64_t n_chunks, const IdxT* __restrict__ rowptr, const int32_t* __restrict__ order,
-                                  const int32_t* __restrict__ chunk_heavy, const int32_t* __restrict__ heavy_rows,
-                                  const int32_t* __restrict__ heavy_chunk_off, const int64_t* __restrict__ chunk_beg,
-                                  RowDesc* __restrict__ desc, int32_t* __restrict__ pos_of) {
-  for (int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; pos < n_chunks; pos += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t c = order[pos];
+__global__ __launch_bounds__(256) void chunk_scatter_kernel(
+    int64_t n, const Counts4* __restrict__ total, const IdxT* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+    const int64_t* __restrict__ boff, int32_t* __restrict__ cur, const int32_t* __restrict__ chunk_heavy,
+    const int32_t* __restrict__ heavy_rows, const int32_t* __restrict__ heavy_chunk_off,
+    const int64_t* __restrict__ chunk_beg, int32_t* __restrict__ order, RowDesc* __restrict__ desc,
+    int32_t* __restrict__ pos_of) {
+  __shared__ int32_t lh[CHUNK_BUCKETS];              // count, then the next position within the bucket
+  int64_t c0, c1;
+  piece_range(total, &c0, &c1);
+  if (c0 >= c1) return;
+  for (int b = threadIdx.x; b < CHUNK_BUCKETS; b += 256) lh[b] = 0;
+  __syncthreads();
+  for (int64_t c = c0 + threadIdx.x; c < c1; c += 256) atomicAdd(&lh[chunk_bucket(n, colidx[chunk_beg[c]])], 1);
+  __syncthreads();
+  for (int b = threadIdx.x; b < CHUNK_BUCKETS; b += 256)
+    if (lh[b]) lh[b] = atomicAdd(&cur[b], lh[b]);
+  __syncthreads();
+  for (int64_t c = c0 + threadIdx.x; c < c1; c += 256) {
+    const int64_t b = chunk_beg[c];
+    const int k = chunk_bucket(n, colidx[b]);
+    const int64_t pos = boff[k] + atomicAdd(&lh[k], 1);
     const int32_t h = chunk_heavy[c];
     const int32_t r = heavy_rows[h];
-    const int64_t b = chunk_beg[c];
     const int64_t rend = (int64_t)rowptr[r + 1];
     const int64_t e = chunk_beg[c + 1] < rend ? chunk_beg[c + 1] : rend;
     const bool single = heavy_chunk_off[h + 1] - heavy_chunk_off[h] == 1;
+    order[pos] = (int32_t)c;
     desc[pos] = RowDesc{b, r, (int32_t)((uint32_t)(e - b) | (single ? 0x80000000u : 0u))};
     pos_of[c] = (int32_t)pos;
-  }
-}
-
-// Heavy rows whose partials the fix-up adds (more than one piece), flagged
-// for two stable compactions: big[h] for more than GCN_FIX_BIG_PIECES
-// pieces, small[h] for 2 .. GCN_FIX_BIG_PIECES; entry n_heavy is 0.
-__global__ void fix_flag_kernel(int64_t n_heavy, const int32_t* __restrict__ heavy_chunk_off, int64_t* __restrict__ big,
-                                int64_t* __restrict__ small) {
-  for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h <= n_heavy; h += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = h < n_heavy ? heavy_chunk_off[h + 1] - heavy_chunk_off[h] : 0;
-    big[h] = m > GCN_FIX_BIG_PIECES ? 1 : 0;
-    small[h] = m >= 2 && m <= GCN_FIX_BIG_PIECES ? 1 : 0;
-  }
-}
-
-// fix_rows = [big rows ascending, small rows ascending] from the exclusive
-// scans of the flags.
-__global__ void fix_scatter_kernel(int64_t n_heavy, const int32_t* __restrict__ heavy_chunk_off,
-                                   const int64_t* __restrict__ big_off, const int64_t* __restrict__ small_off,
-                                   int32_t* __restrict__ fix_rows) {
-  const int64_t n_big = big_off[n_heavy];
-  for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h < n_heavy; h += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = heavy_chunk_off[h + 1] - heavy_chunk_off[h];
-    if (m > GCN_FIX_BIG_PIECES) fix_rows[big_off[h]] = (int32_t)h;
-    else if (m >= 2) fix_rows[n_big + small_off[h]] = (int32_t)h;
-  }
-}
-
-__global__ void chunk_key_kernel(int64_t n, int64_t n_chunks, const int32_t* __restrict__ colidx,
-                                 const int64_t* __restrict__ chunk_beg, int32_t* __restrict__ key,
-                                 int32_t* __restrict__ hist) {
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_chunks; c += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t b = (int32_t)((int64_t)colidx[chunk_beg[c]] * CHUNK_BUCKETS / n);
-    key[c] = b;
-    atomicAdd(&hist[b], 1);
-  }
-}
-
-__global__ void chunk_scatter_kernel(int64_t n_chunks, const int32_t* __restrict__ key, const int64_t* __restrict__ boff,
-                                     int32_t* __restrict__ cur, int32_t* __restrict__ order) {
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_chunks; c += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t b = key[c];
-    order[boff[b] + atomicAdd(&cur[b], 1)] = (int32_t)c;
   }
 }
 
@@ -664,166 +723,113 @@ int64_t max_pieces(int64_t n, int64_t nnz, int64_t thr, int64_t chunk_nnz, int64
   return nnz / chunk_nnz + rows * parts + 1;
 }
 
+namespace {
+// The schedule buffer: what the product reads, then what only the
+// construction needs.
+struct SchedLayout {
+  int32_t *order, *heavy_rows, *heavy_chunk_off, *chunk_heavy, *piece_pos, *fix_rows, *perm;
+  int64_t *chunk_beg, *part_off;
+  RowDesc *piece_desc, *row_desc;
+  Counts4 *counts, *scr;
+  int32_t *chist, *ccur, *hist, *cur;      // contiguous: cleared together
+  size_t zero_bytes;
+  int64_t *cboff, *boff;
+  SchedTotals* totals;
+  size_t bytes;
+};
+SchedLayout sched_layout(int64_t n, int64_t nnz, int64_t thr, int64_t chunk, int64_t parts, void* sched) {
+  const int64_t mc = max_pieces(n, nnz, thr, chunk, parts), nb = light_buckets(n, thr);
+  SchedLayout L;
+  char* base = static_cast<char*>(sched);
+  size_t o = 0;
+  auto take = [&](size_t bytes) { char* p = base ? base + o : nullptr; o += align256(bytes); return p; };
+  L.order = (int32_t*)take(sizeof(int32_t) * mc);
+  L.heavy_rows = (int32_t*)take(sizeof(int32_t) * n);
+  L.heavy_chunk_off = (int32_t*)take(sizeof(int32_t) * (n + 1));
+  L.chunk_heavy = (int32_t*)take(sizeof(int32_t) * mc);
+  L.chunk_beg = (int64_t*)take(sizeof(int64_t) * (mc + 1));
+  L.part_off = (int64_t*)take(sizeof(int64_t) * (parts + 1));
+  L.piece_desc = (RowDesc*)take(sizeof(RowDesc) * mc);
+  L.piece_pos = (int32_t*)take(sizeof(int32_t) * mc);
+  L.fix_rows = (int32_t*)take(sizeof(int32_t) * n);
+  L.row_desc = (RowDesc*)take(sizeof(RowDesc) * n);
+  L.perm = (int32_t*)take(sizeof(int32_t) * n);
+  L.counts = (Counts4*)take(sizeof(Counts4) * (n + 1));
+  L.scr = (Counts4*)take(sizeof(Counts4) * scan_scratch_elems(n + 1));
+  const size_t z0 = o;
+  L.chist = (int32_t*)take(sizeof(int32_t) * CHUNK_BUCKETS);
+  L.ccur = (int32_t*)take(sizeof(int32_t) * CHUNK_BUCKETS);
+  L.hist = (int32_t*)take(sizeof(int32_t) * nb);
+  L.cur = (int32_t*)take(sizeof(int32_t) * nb);
+  L.zero_bytes = o - z0;
+  L.cboff = (int64_t*)take(sizeof(int64_t) * (CHUNK_BUCKETS + 1));
+  L.boff = (int64_t*)take(sizeof(int64_t) * (nb + 1));
+  L.totals = (SchedTotals*)take(sizeof(SchedTotals));
+  L.bytes = o;
+  return L;
+}
+
+// Ten launches and one synchronisation: nothing on the way needs a count on
+// the host (the kernels over the pieces read their number on the device).
+template <typename IdxT>
+hipError_t schedule_t(int64_t n, int64_t nnz, const IdxT* rowptr, const int32_t* colidx, int64_t thr, int64_t chunk,
+                      int64_t parts, const SchedLayout& L, SchedTotals* host, hipStream_t s) {
+  const int64_t nb = light_buckets(n, thr), blk = light_block(n);
+  const dim3 rg(grid_for(n, 1024, 4096));
+  const dim3 cg(grid_for(max_pieces(n, nnz, thr, chunk, parts), 2048, 512));
+  hipError_t e;
+#define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
+  GCN_TRY(fill_zero(L.chist, L.zero_bytes, s));
+  hipLaunchKernelGGL(row_count_kernel<IdxT>, rg, dim3(256), 0, s, n, rowptr, colidx, thr, chunk, parts, blk, nb,
+                     L.counts, L.hist);
+  GCN_TRY(hipGetLastError());
+  GCN_TRY(scan_exclusive(L.counts, n + 1, L.scr, s));
+  const Counts4* total = L.counts + n;
+  hipLaunchKernelGGL(piece_fill_kernel<IdxT>, dim3(grid_for(n + 1)), dim3(256), 0, s, n, nnz, rowptr, colidx, thr, chunk,
+                     parts, L.counts, L.heavy_rows, L.heavy_chunk_off, L.chunk_heavy, L.chunk_beg, L.fix_rows);
+  GCN_TRY(hipGetLastError());
+  hipLaunchKernelGGL(chunk_hist_kernel, cg, dim3(256), 0, s, n, total, colidx, L.chunk_beg, L.chist);
+  GCN_TRY(hipGetLastError());
+  hipLaunchKernelGGL(bucket_scan_kernel, dim3(2), dim3(1024), 0, s, nb, L.hist, L.boff, L.chist, L.cboff, parts,
+                     L.part_off, total, L.totals);
+  GCN_TRY(hipGetLastError());
+  hipLaunchKernelGGL(light_scatter_kernel<IdxT>, rg, dim3(256), 0, s, n, rowptr, thr, blk, nb, L.boff, L.cur, L.perm,
+                     L.row_desc);
+  GCN_TRY(hipGetLastError());
+  hipLaunchKernelGGL(chunk_scatter_kernel<IdxT>, cg, dim3(256), 0, s, n, total, rowptr, colidx, L.cboff, L.ccur,
+                     L.chunk_heavy, L.heavy_rows, L.heavy_chunk_off, L.chunk_beg, L.order, L.piece_desc, L.piece_pos);
+  GCN_TRY(hipGetLastError());
+  GCN_TRY(hipMemcpyAsync(host, L.totals, sizeof(SchedTotals), hipMemcpyDeviceToHost, s));
+  GCN_TRY(hipStreamSynchronize(s));
+#undef GCN_TRY
+  return hipSuccess;
+}
+}  // namespace
+
 size_t schedule_bytes(int64_t n, int64_t nnz, int64_t thr, int64_t chunk_nnz, int64_t parts) {
-  const int64_t max_chunks = max_pieces(n, nnz, thr, chunk_nnz, parts);
-  const int64_t nb = light_buckets(n, thr);
-  int64_t scan_n = (n + 1 > nb + 1) ? n + 1 : nb + 1;
-  if (scan_n < CHUNK_BUCKETS + 1) scan_n = CHUNK_BUCKETS + 1;
-  size_t b = 0;
-  b += align256(sizeof(int32_t) * max_chunks);                  // chunk_order
-  b += align256(sizeof(int32_t) * max_chunks);                  // chunk keys
-  b += align256(sizeof(int32_t) * CHUNK_BUCKETS);               // chunk bucket histogram
-  b += align256(sizeof(int32_t) * CHUNK_BUCKETS);               // chunk bucket cursors
-  b += align256(sizeof(int64_t) * (CHUNK_BUCKETS + 1));         // chunk bucket offsets
-  b += align256(sizeof(int32_t) * n);                           // heavy_rows
-  b += align256(sizeof(int32_t) * (n + 1));                     // heavy_chunk_off
-  b += align256(sizeof(int32_t) * max_chunks);                  // chunk_heavy
-  b += align256(sizeof(int64_t) * (max_chunks + 1));            // chunk_beg
-  b += align256(sizeof(int64_t) * (parts + 1));                 // part_off
-  b += align256(sizeof(RowDesc) * max_chunks);                  // piece descriptors
-  b += align256(sizeof(int32_t) * max_chunks);                  // launch position of each piece
-  b += align256(sizeof(int32_t) * n);                           // fix_rows
-  b += align256(sizeof(RowDesc) * n);                           // light-row descriptors
-  b += align256(sizeof(int32_t) * n);                           // row_perm
-  b += align256(sizeof(int64_t) * (n + 1));                     // flags -> heavy index
-  b += align256(sizeof(int64_t) * (n + 1));                     // pieces per row -> piece offsets
-  b += align256(sizeof(int32_t) * nb);                          // (block, degree) histogram
-  b += align256(sizeof(int32_t) * nb);                          // bucket cursors
-  b += align256(sizeof(int64_t) * (nb + 1));                    // bucket offsets
-  b += align256(sizeof(int64_t) * scan_scratch_elems(scan_n));  // scan scratch
-  return b;
+  return sched_layout(n, nnz, thr, chunk_nnz, parts, nullptr).bytes;
 }
 
 hipError_t schedule_run(int64_t n, int64_t nnz, bool idx64, const void* rowptr, const int32_t* colidx, int64_t thr,
                         int64_t chunk, int64_t parts, void* sched, size_t sched_bytes, SchedOut* out, hipStream_t s) {
-  char* w = static_cast<char*>(sched);
-  auto take = [&](size_t bytes) { char* p = w; w += align256(bytes); return p; };
-  const int64_t max_chunks = max_pieces(n, nnz, thr, chunk, parts);
-  const int64_t nb = light_buckets(n, thr);
-  int64_t scan_n = (n + 1 > nb + 1) ? n + 1 : nb + 1;
-  if (scan_n < CHUNK_BUCKETS + 1) scan_n = CHUNK_BUCKETS + 1;
-  int32_t* corder = (int32_t*)take(sizeof(int32_t) * max_chunks);
-  int32_t* ckey = (int32_t*)take(sizeof(int32_t) * max_chunks);
-  int32_t* chist = (int32_t*)take(sizeof(int32_t) * CHUNK_BUCKETS);
-  int32_t* ccur = (int32_t*)take(sizeof(int32_t) * CHUNK_BUCKETS);
-  int64_t* cboff = (int64_t*)take(sizeof(int64_t) * (CHUNK_BUCKETS + 1));
-  int32_t* hr = (int32_t*)take(sizeof(int32_t) * n);
-  int32_t* hco = (int32_t*)take(sizeof(int32_t) * (n + 1));
-  int32_t* ch = (int32_t*)take(sizeof(int32_t) * max_chunks);
-  int64_t* cbeg = (int64_t*)take(sizeof(int64_t) * (max_chunks + 1));
-  int64_t* poff = (int64_t*)take(sizeof(int64_t) * (parts + 1));
-  RowDesc* pdesc = (RowDesc*)take(sizeof(RowDesc) * max_chunks);
-  int32_t* ppos = (int32_t*)take(sizeof(int32_t) * max_chunks);
-  int32_t* fixr = (int32_t*)take(sizeof(int32_t) * n);
-  RowDesc* ldesc = (RowDesc*)take(sizeof(RowDesc) * n);
-  int32_t* perm = (int32_t*)take(sizeof(int32_t) * n);
-  int64_t* hidx = (int64_t*)take(sizeof(int64_t) * (n + 1));
-  int64_t* choff = (int64_t*)take(sizeof(int64_t) * (n + 1));
-  int32_t* hist = (int32_t*)take(sizeof(int32_t) * nb);
-  int32_t* cur = (int32_t*)take(sizeof(int32_t) * nb);
-  int64_t* boff = (int64_t*)take(sizeof(int64_t) * (nb + 1));
-  int64_t* scr = (int64_t*)take(sizeof(int64_t) * scan_scratch_elems(scan_n));
-  if ((size_t)(w - static_cast<char*>(sched)) > sched_bytes) return hipErrorInvalidValue;
-  hipError_t e;
-#define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-  if (idx64)
-    hipLaunchKernelGGL(piece_count_kernel<int64_t>, dim3(grid_for(n + 1)), dim3(256), 0, s, n, (const int64_t*)rowptr, colidx, thr, chunk, parts, hidx, choff);
-  else
-    hipLaunchKernelGGL(piece_count_kernel<int32_t>, dim3(grid_for(n + 1)), dim3(256), 0, s, n, (const int32_t*)rowptr, colidx, thr, chunk, parts, hidx, choff);
-  GCN_TRY(hipGetLastError());
-  GCN_TRY(scan_exclusive(hidx, n + 1, scr, s));
-  GCN_TRY(scan_exclusive(choff, n + 1, scr, s));
-  if (idx64)
-    hipLaunchKernelGGL(piece_fill_kernel<int64_t>, dim3(grid_for(n + 1)), dim3(256), 0, s, n, nnz, (const int64_t*)rowptr, colidx, thr, chunk, parts, hidx, choff, hr, hco, ch, cbeg);
-  else
-    hipLaunchKernelGGL(piece_fill_kernel<int32_t>, dim3(grid_for(n + 1)), dim3(256), 0, s, n, nnz, (const int32_t*)rowptr, colidx, thr, chunk, parts, hidx, choff, hr, hco, ch, cbeg);
-  GCN_TRY(hipGetLastError());
-  // light rows, block by block, by decreasing degree inside a block
-  GCN_TRY(fill_zero(hist, sizeof(int32_t) * nb, s));
-  GCN_TRY(fill_zero(cur, sizeof(int32_t) * nb, s));
-  if (idx64)
-    hipLaunchKernelGGL(light_hist_kernel<int64_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int64_t*)rowptr, thr, light_block(n), nb, hist);
-  else
-    hipLaunchKernelGGL(light_hist_kernel<int32_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int32_t*)rowptr, thr, light_block(n), nb, hist);
-  GCN_TRY(hipGetLastError());
-  hipLaunchKernelGGL(widen_kernel, dim3(grid_for(nb + 1)), dim3(256), 0, s, nb, hist, boff);
-  GCN_TRY(hipGetLastError());
-  GCN_TRY(scan_exclusive(boff, nb + 1, scr, s));
-  if (idx64)
-    hipLaunchKernelGGL(light_scatter_kernel<int64_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int64_t*)rowptr, thr, light_block(n), nb, boff, cur, perm);
-  else
-    hipLaunchKernelGGL(light_scatter_kernel<int32_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int32_t*)rowptr, thr, light_block(n), nb, boff, cur, perm);
-  GCN_TRY(hipGetLastError());
-  int64_t host[4] = {0, 0, 0, 0};
-  GCN_TRY(hipMemcpyAsync(&host[0], hidx + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_TRY(hipMemcpyAsync(&host[1], choff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_TRY(hipMemcpyAsync(&host[2], boff + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_TRY(hipMemcpyAsync(&host[3], boff + nb - 1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_TRY(hipStreamSynchronize(s));
-  // light-row descriptors in row_perm order
-  if (host[2] > 0) {
-    if (idx64)
-      hipLaunchKernelGGL(light_desc_kernel<int64_t>, dim3(grid_for(host[2])), dim3(256), 0, s, host[2], (const int64_t*)rowptr, perm, ldesc);
-    else
-      hipLaunchKernelGGL(light_desc_kernel<int32_t>, dim3(grid_for(host[2])), dim3(256), 0, s, host[2], (const int32_t*)rowptr, perm, ldesc);
-    GCN_TRY(hipGetLastError());
-  }
-  // pieces in order of the column bucket of their first entry, which groups
-  // them by column range
-  const int64_t nch = host[1];
-  if (nch > max_chunks) return hipErrorInvalidValue;
-  int64_t slots = 0, n_fix = 0, n_fix_big = 0;
-  if (nch > 0) {
-    GCN_TRY(fill_zero(chist, sizeof(int32_t) * CHUNK_BUCKETS, s));
-    GCN_TRY(fill_zero(ccur, sizeof(int32_t) * CHUNK_BUCKETS, s));
-    hipLaunchKernelGGL(chunk_key_kernel, dim3(grid_for(nch)), dim3(256), 0, s, n, nch, colidx, cbeg, ckey, chist);
-    GCN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(widen_kernel, dim3(grid_for(CHUNK_BUCKETS + 1)), dim3(256), 0, s, CHUNK_BUCKETS, chist, cboff);
-    GCN_TRY(hipGetLastError());
-    GCN_TRY(scan_exclusive(cboff, CHUNK_BUCKETS + 1, scr, s));
-    hipLaunchKernelGGL(chunk_scatter_kernel, dim3(grid_for(nch)), dim3(256), 0, s, nch, ckey, cboff, ccur, corder);
-    GCN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(part_off_kernel, dim3(grid_for(parts + 1)), dim3(256), 0, s, parts, cboff, poff);
-    GCN_TRY(hipGetLastError());
-    if (idx64)
-      hipLaunchKernelGGL(piece_desc_kernel<int64_t>, dim3(grid_for(nch)), dim3(256), 0, s, nch, (const int64_t*)rowptr, corder, ch, hr, hco, cbeg, pdesc, ppos);
-    else
-      hipLaunchKernelGGL(piece_desc_kernel<int32_t>, dim3(grid_for(nch)), dim3(256), 0, s, nch, (const int32_t*)rowptr, corder, ch, hr, hco, cbeg, pdesc, ppos);
-    GCN_TRY(hipGetLastError());
-    // rows for the fix-up; hidx and choff (free again) hold the flag scans
-    const int64_t nh = host[0];
-    hipLaunchKernelGGL(fix_flag_kernel, dim3(grid_for(nh + 1)), dim3(256), 0, s, nh, hco, hidx, choff);
-    GCN_TRY(hipGetLastError());
-    GCN_TRY(scan_exclusive(hidx, nh + 1, scr, s));
-    GCN_TRY(scan_exclusive(choff, nh + 1, scr, s));
-    hipLaunchKernelGGL(fix_scatter_kernel, dim3(grid_for(nh)), dim3(256), 0, s, nh, hco, hidx, choff, fixr);
-    GCN_TRY(hipGetLastError());
-    int64_t nfix[2] = {0, 0};
-    GCN_TRY(hipMemcpyAsync(&nfix[0], hidx + nh, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    GCN_TRY(hipMemcpyAsync(&nfix[1], choff + nh, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    // the most pieces one XCD takes: ranges x, x + 8, ... run on XCD x
-    std::vector<int64_t> hp((size_t)parts + 1);
-    GCN_TRY(hipMemcpyAsync(hp.data(), poff, sizeof(int64_t) * (parts + 1), hipMemcpyDeviceToHost, s));
-    GCN_TRY(hipStreamSynchronize(s));
-    n_fix_big = nfix[0];
-    n_fix = nfix[0] + nfix[1];
-    if (parts > 1) {
-      for (int64_t x = 0; x < XCDS; ++x) {
-        int64_t t = 0;
-        for (int64_t q = x; q < parts; q += XCDS) t += hp[q + 1] - hp[q];
-        slots = std::max(slots, t);
-      }
-    } else {
-      slots = nch;
-    }
-  }
-#undef GCN_TRY
-  out->heavy_rows = hr; out->heavy_chunk_off = hco; out->chunk_heavy = ch; out->row_perm = perm;
-  out->chunk_order = nch > 0 ? corder : nullptr;
-  out->chunk_beg = cbeg; out->part_off = poff; out->part_slots = slots;
-  out->piece_desc = pdesc; out->piece_pos = ppos; out->row_desc = ldesc;
-  out->fix_rows = fixr; out->n_fix = n_fix; out->n_fix_big = n_fix_big;
-  out->n_heavy = host[0]; out->n_chunks = nch; out->n_light = host[2]; out->n_light_single = host[2] - host[3];
+  const SchedLayout L = sched_layout(n, nnz, thr, chunk, parts, sched);
+  if (L.bytes > sched_bytes) return hipErrorInvalidValue;
+  SchedTotals t{};
+  const hipError_t e = idx64 ? schedule_t(n, nnz, (const int64_t*)rowptr, colidx, thr, chunk, parts, L, &t, s)
+                             : schedule_t(n, nnz, (const int32_t*)rowptr, colidx, thr, chunk, parts, L, &t, s);
+  if (e != hipSuccess) return e;
+  const int64_t n_chunks = Counts4::lo(t.rows_a);
+  if (n_chunks > max_pieces(n, nnz, thr, chunk, parts)) return hipErrorInvalidValue;
+  out->heavy_rows = L.heavy_rows; out->heavy_chunk_off = L.heavy_chunk_off; out->chunk_heavy = L.chunk_heavy;
+  out->row_perm = L.perm;
+  out->chunk_order = n_chunks > 0 ? L.order : nullptr;
+  out->chunk_beg = L.chunk_beg; out->part_off = L.part_off; out->part_slots = n_chunks > 0 ? t.slots : 0;
+  out->piece_desc = L.piece_desc; out->piece_pos = L.piece_pos; out->row_desc = L.row_desc;
+  out->fix_rows = L.fix_rows;
+  out->n_fix_big = Counts4::hi(t.rows_b);
+  out->n_fix = Counts4::hi(t.rows_b) + Counts4::lo(t.rows_b);
+  out->n_heavy = Counts4::hi(t.rows_a); out->n_chunks = n_chunks;
+  out->n_light = t.n_light; out->n_light_single = t.n_light - t.n_multi;
   return hipSuccess;
 }
 
