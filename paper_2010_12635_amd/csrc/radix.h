@@ -5,7 +5,7 @@
 // of every digit's counts along the tiles, and a stable scatter.  What
 // bounds a pass is memory (two reads and one write of every item) and the
 // ranking arithmetic, so:
-//  * a tile is NT * IPT consecutive items, a wave owning 64 * IPT
+//  * a tile is 512 * IPT consecutive items, a wave owning 64 * IPT
 //    consecutive ones, all requested before the first is ranked;
 //  * equal digits of the 64 items of a round are found with one ballot per
 //    digit bit; the items of earlier rounds are counted in LDS counters
@@ -41,11 +41,17 @@ struct ItemArray {
 };
 
 constexpr int RADIX_NT = 512;                        // threads per tile
-constexpr int RADIX_IPT = 8;                         // items per thread
-constexpr int RADIX_TILE = RADIX_NT * RADIX_IPT;
 constexpr int RADIX_MAX_BITS = 9;                    // widest digit
 
-inline int64_t radix_tiles(int64_t total) { return (total + RADIX_TILE - 1) / RADIX_TILE; }
+// Items per thread: 8, or 16 from 2^25 items on.  Longer digit runs write
+// fuller lines, which count once the items leave the caches (138 M 8-byte keys
+// sorted and compacted in 10.4 ms with 8, 8.8 ms with 16), but a short list
+// then fills fewer compute units (20,000 keys 95 -> 114 us, 8.7 M 387 -> 400).
+inline int radix_ipt(int64_t total) { return total < ((int64_t)1 << 25) ? 8 : 16; }
+inline int64_t radix_tiles(int64_t total) {
+  const int64_t t = RADIX_NT * radix_ipt(total);
+  return (total + t - 1) / t;
+}
 
 // Passes and digit width for keys of `bits` bits: as few passes as 9-bit
 // digits allow, of equal width.
@@ -67,10 +73,10 @@ inline size_t radix_scratch_bytes(int64_t total) {
 namespace {
 
 // cnt[tile][d] = items of the tile with digit d.
-template <int LOGD, typename Src, typename OffT>
+template <int LOGD, int RADIX_IPT, typename Src, typename OffT>
 __global__ __launch_bounds__(RADIX_NT) void radix_hist_kernel(Src src, int64_t total, int shift, uint32_t mask,
                                                               OffT* __restrict__ cnt) {
-  constexpr int D = 1 << LOGD, NW = RADIX_NT / 64;
+  constexpr int D = 1 << LOGD, NW = RADIX_NT / 64, RADIX_TILE = RADIX_NT * RADIX_IPT;
   __shared__ uint32_t h[NW][D];
   for (int i = threadIdx.x; i < NW * D; i += RADIX_NT) (&h[0][0])[i] = 0;
   __syncthreads();
@@ -95,15 +101,17 @@ __global__ __launch_bounds__(RADIX_NT) void radix_hist_kernel(Src src, int64_t t
 }
 
 // In place: cnt[t][d] -> items with digit d in the tiles before t; tot[d] =
-// all of them.  A workgroup takes 16 digits, its 64 groups of 16 threads a
-// contiguous range of tiles each.
+// all of them.  A workgroup takes DW digits, its 1024 / DW groups of DW threads
+// a contiguous range of tiles each.  16 digits are a whole 64-byte piece of a
+// count row; with 4 (four times as many workgroups, which then share lines they
+// write) sorting 8.7 M keys took 425 instead of 390 us.
 template <int LOGD, typename OffT>
 __global__ __launch_bounds__(1024) void radix_scan_kernel(OffT* __restrict__ cnt, int64_t ntiles, OffT* __restrict__ tot) {
-  constexpr int D = 1 << LOGD, U = 8;
-  __shared__ OffT part[16][65];
-  const int dl = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  const int d = blockIdx.x * 16 + dl;
-  const int64_t per = (ntiles + 63) / 64;
+  constexpr int D = 1 << LOGD, U = 8, DW = 16, GR = 1024 / DW;
+  __shared__ OffT part[DW][GR + 1];
+  const int dl = threadIdx.x % DW, grp = threadIdx.x / DW;
+  const int d = blockIdx.x * DW + dl;
+  const int64_t per = (ntiles + GR - 1) / GR;
   const int64_t t0 = grp * per < ntiles ? grp * per : ntiles, t1 = t0 + per < ntiles ? t0 + per : ntiles;
   OffT a = 0;
   for (int64_t t = t0; t < t1; t += U) {
@@ -116,7 +124,7 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(OffT* __restrict__ cnt
   part[dl][grp] = a;
   __syncthreads();
   {
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;   // wave w: digit w of the 16
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;   // wave w: digit w's 64 group sums
     const OffT v = part[w][lane];
     OffT x = v;
 #pragma unroll
@@ -125,7 +133,7 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(OffT* __restrict__ cnt
       if (lane >= o) x += y;
     }
     part[w][lane] = x - v;
-    if (lane == 63) tot[blockIdx.x * 16 + w] = x;
+    if (lane == 63) tot[blockIdx.x * DW + w] = x;
   }
   __syncthreads();
   OffT run = part[dl][grp];
@@ -161,12 +169,13 @@ __device__ __forceinline__ V radix_block_scan(V v, V* red) {
   return before + x - v;
 }
 
-template <int LOGD, typename Src, typename Dst, typename OffT>
+template <int LOGD, int RADIX_IPT, typename Src, typename Dst, typename OffT>
 __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst dst, int64_t total, int shift,
                                                                  uint32_t mask, const OffT* __restrict__ cnt,
                                                                  const OffT* __restrict__ tot) {
   typedef typename Src::Item Item;
   constexpr int D = 1 << LOGD, NW = RADIX_NT / 64, W = sizeof(Item) / 4;
+  constexpr int RADIX_TILE = RADIX_NT * RADIX_IPT;
   static_assert(D <= RADIX_NT, "at most one digit per thread");
   __shared__ uint32_t stage[W][RADIX_TILE];
   __shared__ uint16_t wc[NW][D];                     // items of the digit in the wave's earlier rounds; then its slot base
@@ -256,33 +265,37 @@ __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst ds
   }
 }
 
-template <int LOGD, typename Src, typename Dst, typename OffT>
+template <int LOGD, int IPT, typename Src, typename Dst, typename OffT>
 hipError_t radix_pass_t(const Src& src, const Dst& dst, int64_t total, int shift, int width, void* scratch, hipStream_t s) {
   const int64_t nt = radix_tiles(total);
   OffT* cnt = static_cast<OffT*>(scratch);
   OffT* tot = cnt + nt * ((int64_t)1 << LOGD);
   const uint32_t mask = (1u << width) - 1u;
-  hipLaunchKernelGGL((radix_hist_kernel<LOGD, Src, OffT>), dim3((unsigned)nt), dim3(RADIX_NT), 0, s, src, total, shift,
-                     mask, cnt);
+  hipLaunchKernelGGL((radix_hist_kernel<LOGD, IPT, Src, OffT>), dim3((unsigned)nt), dim3(RADIX_NT), 0, s, src, total,
+                     shift, mask, cnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((radix_scan_kernel<LOGD, OffT>), dim3((1 << LOGD) / 16), dim3(1024), 0, s, cnt, nt, tot);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((radix_scatter_kernel<LOGD, Src, Dst, OffT>), dim3((unsigned)nt), dim3(RADIX_NT), 0, s, src, dst,
-                     total, shift, mask, cnt, tot);
+  hipLaunchKernelGGL((radix_scatter_kernel<LOGD, IPT, Src, Dst, OffT>), dim3((unsigned)nt), dim3(RADIX_NT), 0, s, src,
+                     dst, total, shift, mask, cnt, tot);
   return hipGetLastError();
 }
 
 // One stable pass over digit (key >> shift) of `width` <= 9 bits; total > 0.
 template <typename Src, typename Dst>
 hipError_t radix_pass(const Src& src, const Dst& dst, int64_t total, int shift, int width, void* scratch, hipStream_t s) {
-  if (total < ((int64_t)1 << 32)) {
-    if (width <= 8) return radix_pass_t<8, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
-    return radix_pass_t<9, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
+  if (radix_ipt(total) == 8) {
+    if (width <= 8) return radix_pass_t<8, 8, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
+    return radix_pass_t<9, 8, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
   }
-  if (width <= 8) return radix_pass_t<8, Src, Dst, uint64_t>(src, dst, total, shift, width, scratch, s);
-  return radix_pass_t<9, Src, Dst, uint64_t>(src, dst, total, shift, width, scratch, s);
+  if (total < ((int64_t)1 << 32)) {
+    if (width <= 8) return radix_pass_t<8, 16, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
+    return radix_pass_t<9, 16, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
+  }
+  if (width <= 8) return radix_pass_t<8, 16, Src, Dst, uint64_t>(src, dst, total, shift, width, scratch, s);
+  return radix_pass_t<9, 16, Src, Dst, uint64_t>(src, dst, total, shift, width, scratch, s);
 }
 
 }  // namespace
