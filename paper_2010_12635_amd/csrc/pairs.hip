@@ -21,7 +21,9 @@
 //    every positive finds the ends of its run of equal scores by binary
 //    search: negatives below / equal and all scores >= it follow from the
 //    counts at those ends, O((P + N) log(P + N)) in all.  Fixed-order sums.
-#include "internal.h"
+#include "radix.h"
+
+#include <algorithm>
 
 namespace gcn {
 
@@ -179,203 +181,53 @@ hipError_t pair_loss_t(PairLossParams p, int lpr, hipStream_t s, int64_t* nb_out
 //
 // Entry i of the 2K entries is endpoint (i even ? u : v) of pair k = i / 2;
 // its key is that endpoint (n for a pair with an id outside [0, n)).  A
-// stable LSD radix sort by key (8-bit digits: per-tile digit histograms,
-// one exclusive scan, a stable scatter that ranks equal digits by ballots)
-// puts each row's entries together in increasing k without atomics.  The
+// stable radix sort by key (radix.h) puts each row's entries together in
+// increasing k without atomics.  2^21 pairs, n = 2^17: two passes of 9 bits
+// instead of three of 8, no workgroup barrier between the rounds of a tile:
+// 215 -> 113 us.  The
 // sorted entries are cut into segments of SEG entries; a lane group per
 // segment sums the rows that lie inside it and leaves partial sums for the
 // rows that cross its ends, which a fix-up pass adds in segment order.
-constexpr int RS_MAX_BITS = 8;                      // digit width
-constexpr int RS_IPT = 8;                           // items per thread per tile
-constexpr int RS_TILE = 256 * RS_IPT;
 constexpr int SEG = 64;                             // sorted entries per gather segment
 
-__device__ __forceinline__ int32_t entry_key(int64_t n, const int32_t* __restrict__ pu, const int32_t* __restrict__ pv,
-                                             int64_t i) {
-  const int32_t u = pu[i >> 1], v = pv[i >> 1];
-  const bool ok = u >= 0 && v >= 0 && u < n && v < n;
-  return ok ? ((i & 1) ? v : u) : (int32_t)n;
-}
+// A pair endpoint: its vertex (the key), the gradient g_k of its pair (as
+// bits) and the other endpoint, so that the segment sums read g_k with the
+// entry instead of gathering it by pair index.
+struct PairEnd {
+  int32_t k, g, other;
+  __device__ __forceinline__ uint64_t key() const { return (uint32_t)k; }
+};
 
-// Digit histogram of one tile: hist[d * nblk + blockIdx.x] (digit-major).
-template <int BITS>
-__global__ __launch_bounds__(256) void rs_hist_kernel(int64_t n, const int32_t* __restrict__ pu,
-                                                      const int32_t* __restrict__ pv, const int32_t* __restrict__ keys,
-                                                      int64_t total, int shift, int64_t nblk,
-                                                      int64_t* __restrict__ hist) {
-  constexpr int DIGITS = 1 << BITS;
-  __shared__ int cnt[DIGITS];
-  for (int d = threadIdx.x; d < DIGITS; d += 256) cnt[d] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-  int32_t ks[RS_IPT];                               // all loads first (clamped indices)
-#pragma unroll
-  for (int r = 0; r < RS_IPT; ++r) {
-    int64_t i = base + r * 256 + threadIdx.x;
-    i = i < total ? i : total - 1;
-    ks[r] = keys ? keys[i] : entry_key(n, pu, pv, i);
+// The unsorted endpoints, in pair order.
+struct PairEnds {
+  typedef PairEnd Item;
+  int64_t n;
+  const int32_t* pu;
+  const int32_t* pv;
+  const float* g;
+  __device__ __forceinline__ PairEnd load(int64_t i) const {
+    const int32_t u = pu[i >> 1], v = pv[i >> 1];
+    const bool ok = u >= 0 && v >= 0 && u < n && v < n;
+    return PairEnd{ok ? ((i & 1) ? v : u) : (int32_t)n, __float_as_int(g[i >> 1]), (i & 1) ? u : v};
   }
-#pragma unroll
-  for (int r = 0; r < RS_IPT; ++r)
-    if (base + r * 256 + threadIdx.x < total) atomicAdd(&cnt[(ks[r] >> shift) & (DIGITS - 1)], 1);
-  __syncthreads();
-  for (int d = threadIdx.x; d < DIGITS; d += 256) hist[(int64_t)d * nblk + blockIdx.x] = cnt[d];
-}
-
-// Stable scatter of one tile: items are ranked round by round (256
-// consecutive items per round, thread order = item order); inside a wave
-// the lanes with the same digit are found with 8 ballots, across the four
-// waves through per-wave counts in LDS stamped with the round.  The ranked
-// items are first placed in LDS in the tile's own digit order, then written
-// out digit run by digit run, so that neighbouring lanes store to
-// neighbouring addresses (placed straight at their global positions, every
-// lane of a store would hit another cache line).
-// Each item carries the gradient g_k of its pair (as bits) and the other
-// endpoint: the segment sums then read g_k with the entry instead of
-// gathering it by pair index.
-template <int BITS>
-__global__ __launch_bounds__(256) void rs_scatter_kernel(int64_t n, const int32_t* __restrict__ pu,
-                                                         const int32_t* __restrict__ pv,
-                                                         const int32_t* __restrict__ kin, const int32_t* __restrict__ vin,
-                                                         const int32_t* __restrict__ oin, const float* __restrict__ g,
-                                                         int64_t total, int shift, int64_t nblk,
-                                                         const int64_t* __restrict__ off, int32_t* __restrict__ kout,
-                                                         int32_t* __restrict__ vout, int32_t* __restrict__ oout) {
-  constexpr int DIGITS = 1 << BITS;
-  static_assert(DIGITS == 256, "one digit per thread");
-  __shared__ int cnt[4][DIGITS];                    // (round << 16) | count
-  __shared__ int run[DIGITS];
-  __shared__ int toff[DIGITS];                      // first slot of each digit in the tile
-  __shared__ int wsum[4];
-  __shared__ int64_t dbase[DIGITS];
-  __shared__ int32_t lk[RS_TILE], lv[RS_TILE], lo[RS_TILE];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-  // every item of the tile is requested before the first round: the rounds
-  // are separated by barriers, and loads issued round by round would cost a
-  // memory latency each (indices past the end read the last item, unused)
-  int32_t ks[RS_IPT], vs[RS_IPT], os[RS_IPT];
-#pragma unroll
-  for (int r = 0; r < RS_IPT; ++r) {
-    int64_t i = base + r * 256 + threadIdx.x;
-    i = i < total ? i : total - 1;
-    if (kin) {
-      ks[r] = kin[i];
-      vs[r] = vin[i];
-      os[r] = oin[i];
-    } else {                                        // first pass: items in pair order
-      ks[r] = entry_key(n, pu, pv, i);
-      vs[r] = __float_as_int(g[i >> 1]);
-      os[r] = (i & 1) ? pu[i >> 1] : pv[i >> 1];
-    }
-  }
-  {
-    // thread d: the global start of digit d for this tile, and the tile's
-    // count of digit d (difference of consecutive entries of the scanned
-    // digit-major histogram); an exclusive scan of the counts gives toff
-    const int d = threadIdx.x;
-    const int64_t L = (int64_t)d * nblk + blockIdx.x;
-    const int64_t b0 = off[L];
-    const int64_t b1 = L + 1 < (int64_t)DIGITS * nblk ? off[L + 1] : total;
-    const int c = (int)(b1 - b0);
-    run[d] = 0;
-    dbase[d] = b0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) cnt[w][d] = -1;     // stamp -1: no round yet
-    int x = c;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[wave] = x;
-    __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += wsum[w];
-    toff[d] = before + x - c;
-  }
-  __syncthreads();
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-#pragma unroll
-  for (int r = 0; r < RS_IPT; ++r) {
-    const int64_t i = base + r * 256 + threadIdx.x;
-    const bool valid = i < total;
-    const int32_t k = valid ? ks[r] : 0, val = vs[r], oth = os[r];
-    const int d = (k >> shift) & (DIGITS - 1);
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < BITS; ++bit) {
-      const uint64_t bb = __ballot((d >> bit) & 1);
-      m &= ((d >> bit) & 1) ? bb : ~bb;
-    }
-    const int rank = __popcll(m & lt);
-    if (valid && rank == 0) cnt[wave][d] = (r << 16) | __popcll(m);
-    __syncthreads();
-    if (valid) {
-      int before = 0;
-      for (int w = 0; w < wave; ++w) {
-        const int c = cnt[w][d];
-        if ((c >> 16) == r) before += c & 0xFFFF;
-      }
-      const int slot = toff[d] + run[d] + before + rank;
-      lk[slot] = k;
-      lv[slot] = val;
-      lo[slot] = oth;
-    }
-    __syncthreads();
-    {
-      const int dd = threadIdx.x;
-      int add = 0;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int c = cnt[w][dd];
-        if ((c >> 16) == r) add += c & 0xFFFF;
-      }
-      run[dd] += add;
-    }
-    __syncthreads();
-  }
-  // slot j of the tile holds the (j - toff[d])-th item of digit d
-  const int64_t rest = total - base;
-  const int tile_n = rest < RS_TILE ? (int)rest : RS_TILE;
-  for (int j = threadIdx.x; j < tile_n; j += 256) {
-    const int32_t k = lk[j];
-    const int d = (k >> shift) & (DIGITS - 1);
-    const int64_t pos = dbase[d] + (j - toff[d]);
-    kout[pos] = k;
-    vout[pos] = lv[j];
-    oout[pos] = lo[j];
-  }
-}
+};
 
 // Row offsets from sorted keys: off[r] = first position with key >= r,
 // r = 0 .. n (keys equal to n, the skipped pairs, lie past off[n]).
-__global__ void rs_bounds_kernel(int64_t n, const int32_t* __restrict__ keys, int64_t total,
+__global__ void rs_bounds_kernel(int64_t n, const PairEnd* __restrict__ ends, int64_t total,
                                  int64_t* __restrict__ off) {
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j <= total; j += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t lo = j == 0 ? -1 : keys[j - 1];
-    const int64_t hi = j == total ? n : min<int64_t>(keys[j], n);
+    const int64_t lo = j == 0 ? -1 : ends[j - 1].k;
+    const int64_t hi = j == total ? n : min<int64_t>(ends[j].k, n);
     for (int64_t r = lo + 1; r <= hi; ++r) off[r] = j;
   }
-}
-
-__device__ __forceinline__ int64_t lower_row(const int64_t* __restrict__ off, int64_t n, int64_t x) {
-  int64_t lo = 0, hi = n;                           // first r in [0, n] with off[r] >= x
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (off[mid] < x) lo = mid + 1; else hi = mid;
-  }
-  return lo;
 }
 
 struct SegParams {
   int64_t n, F, ld;
   const void* Z;
-  const int32_t* pu;
-  const int32_t* pv;
   const int64_t* off;                               // [n + 1]
-  const int32_t* pg;                                // sorted entries: the pair's gradient g_k (bits)
-  const int32_t* po;                                // sorted entries: other endpoint
+  const PairEnd* ends;                              // sorted
   int64_t nseg;
   float* head;                                      // [nseg][ldp]
   float* tail;                                      // [nseg][ldp]
@@ -395,8 +247,9 @@ __device__ __forceinline__ void seg_sum(const SegParams& p, int64_t e0, int64_t 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t ee = e + u < e1 ? e + u : e1 - 1;
-      w[u] = __int_as_float(p.pg[ee]);
-      other[u] = p.po[ee];
+      const PairEnd x = p.ends[ee];
+      w[u] = __int_as_float(x.g);
+      other[u] = x.other;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) w[u] = e + u < e1 ? w[u] : 0.f;
@@ -430,10 +283,12 @@ __global__ __launch_bounds__(256) void pair_segment_kernel(SegParams p) {
       continue;
     }
     // rows starting in [a, b) belong to this segment; the last one also
-    // takes the empty rows that start at the end
+    // takes the empty rows that start at the end.  The first row with
+    // off[r] >= x is the one after the row of entry x - 1 (a binary search
+    // in off took 17 dependent loads per end).
     const int64_t a = sgi * SEG, b = min(a + SEG, total);
-    const int64_t r0 = lower_row(p.off, p.n, a);
-    const int64_t r1 = sgi == nuse - 1 ? p.n : lower_row(p.off, p.n, b);
+    const int64_t r0 = a > 0 ? (int64_t)p.ends[a - 1].k + 1 : 0;
+    const int64_t r1 = sgi == nuse - 1 ? p.n : (int64_t)p.ends[b - 1].k + 1;
     float acc[VE];
     // head: the row that started before this segment
     if (r0 > 0 && p.off[r0] > a && a < b) {
@@ -466,32 +321,92 @@ __global__ __launch_bounds__(256) void pair_segment_kernel(SegParams p) {
   }
 }
 
+// VE floats of a partial row.
+template <int VE>
+__device__ __forceinline__ void add_row(float* acc, const float4 (&v)[VE / 4], bool live) {
+#pragma unroll
+  for (int i = 0; i < VE / 4; ++i) {
+    acc[4 * i] = live ? acc[4 * i] + v[i].x : acc[4 * i];
+    acc[4 * i + 1] = live ? acc[4 * i + 1] + v[i].y : acc[4 * i + 1];
+    acc[4 * i + 2] = live ? acc[4 * i + 2] + v[i].z : acc[4 * i + 2];
+    acc[4 * i + 3] = live ? acc[4 * i + 3] + v[i].w : acc[4 * i + 3];
+  }
+}
+
+// Head partials of segments [t0, t1) added in order, eight in flight.
+template <int VE>
+__device__ __forceinline__ void add_heads(const SegParams& p, int64_t t0, int64_t t1, int64_t col0, float* acc) {
+  constexpr int U = 8;
+#pragma unroll 1
+  for (int64_t t = t0; t < t1; t += U) {
+    float4 v[U][VE / 4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < VE / 4; ++i)
+        v[u][i] = reinterpret_cast<const float4*>(p.head + (t + u < t1 ? t + u : t1 - 1) * p.ldp + col0)[i];
+#pragma unroll
+    for (int u = 0; u < U; ++u) add_row<VE>(acc, v[u], t + u < t1);
+  }
+}
+
 // Rows that cross segment ends: the tail partial of the segment where the
-// row starts plus the head partials of the following segments, in order.
+// row starts plus the head partials of the following segments, in order.  A
+// row of more than FIX_BIG segments is left to the whole workgroup: its lane
+// groups add contiguous runs of segments, then the runs are added in order
+// (one lane group alone walked the 650 segments of a hub for 174 us while the
+// rest of the chip idled; 19 us now, 2^21 pairs, n = 2^17, F = 64).
+constexpr int FIX_BIG = 32;
+
 template <typename T, int LPR>
 __global__ __launch_bounds__(256) void pair_fixup_kernel(SegParams p) {
   constexpr int VE = Vec<T>::N;
-  constexpr int G = 64 / LPR;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gi = lane / LPR, li = lane % LPR;
+  constexpr int G = 64 / LPR, NG = 4 * G;
+  __shared__ int big[NG];
+  __shared__ float red[NG][LPR * VE];
+  const int gi = threadIdx.x / LPR, li = threadIdx.x % LPR;
   const int64_t col0 = (int64_t)li * VE;
-  if (col0 >= p.ep.ldo) return;
-  for (int64_t sgi = ((int64_t)blockIdx.x * 4 + wave) * G + gi; sgi < p.nseg; sgi += (int64_t)gridDim.x * 4 * G) {
-    const int32_t r = p.tail_row[sgi];
-    if (r < 0) continue;
-    float acc[VE];
+  const bool live = col0 < p.F, out = col0 < p.ep.ldo;
+  for (int64_t s0 = (int64_t)blockIdx.x * NG; s0 < p.nseg; s0 += (int64_t)gridDim.x * NG) {
+    const int64_t sgi = s0 + gi;
+    const int32_t r = sgi < p.nseg ? p.tail_row[sgi] : -1;
+    const int64_t last = r >= 0 ? (p.off[r + 1] - 1) / SEG : 0;
+    const bool is_big = r >= 0 && last - sgi > FIX_BIG;
+    if (li == 0) big[gi] = is_big;
+    if (r >= 0 && !is_big && out) {
+      float acc[VE];
 #pragma unroll
-    for (int q = 0; q < VE; ++q) acc[q] = 0.f;
-    if (col0 < p.F) {
-      const int64_t last = (p.off[r + 1] - 1) / SEG;
-#pragma unroll
-      for (int q = 0; q < VE; ++q) acc[q] = p.tail[sgi * p.ldp + col0 + q];
-      for (int64_t t = sgi + 1; t <= last; ++t) {
-#pragma unroll
-        for (int q = 0; q < VE; ++q) acc[q] += p.head[t * p.ldp + col0 + q];
-      }
+      for (int q = 0; q < VE; ++q) acc[q] = live ? p.tail[sgi * p.ldp + col0 + q] : 0.f;
+      if (live) add_heads<VE>(p, sgi + 1, last + 1, col0, acc);
+      epi_store_vec<T>(p.ep, r, col0, acc);
     }
-    epi_store_vec<T>(p.ep, r, col0, acc);
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < NG; ++k) {
+      if (!big[k]) continue;
+      const int64_t sk = s0 + k;
+      const int32_t rk = p.tail_row[sk];
+      const int64_t t0 = sk + 1, t1 = (p.off[rk + 1] - 1) / SEG + 1, per = (t1 - t0 + NG - 1) / NG;
+      const int64_t a0 = t0 + gi * per < t1 ? t0 + gi * per : t1, a1 = a0 + per < t1 ? a0 + per : t1;
+      float acc[VE];
+#pragma unroll
+      for (int q = 0; q < VE; ++q) acc[q] = 0.f;
+      if (live) add_heads<VE>(p, a0, a1, col0, acc);
+#pragma unroll
+      for (int q = 0; q < VE; ++q) red[gi][li * VE + q] = acc[q];
+      __syncthreads();
+      if (gi == 0 && out) {
+#pragma unroll
+        for (int q = 0; q < VE; ++q) acc[q] = live ? p.tail[sk * p.ldp + col0 + q] : 0.f;
+#pragma unroll 4
+        for (int j = 0; j < NG; ++j)
+#pragma unroll
+          for (int q = 0; q < VE; ++q) acc[q] += red[j][li * VE + q];
+        epi_store_vec<T>(p.ep, rk, col0, acc);
+      }
+      __syncthreads();
+    }
+    __syncthreads();                                 // big is free for the next round
   }
 }
 
@@ -527,31 +442,32 @@ __device__ __forceinline__ uint32_t score_key(float x) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// Sort input: key, positive flag and index of each of the P + N scores.
-__global__ __launch_bounds__(256) void metrics_prep_kernel(const float* __restrict__ scores, int64_t P, int64_t total,
-                                                           int32_t* __restrict__ key, int32_t* __restrict__ pos,
-                                                           int32_t* __restrict__ idx) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    key[i] = (int32_t)score_key(scores[i]);
-    pos[i] = i < P ? 1 : 0;
-    idx[i] = (int32_t)i;
-  }
-}
+// A score to sort: its key and whether it is a positive's.
+struct ScoreItem {
+  uint32_t k;
+  int32_t pos;
+  __device__ __forceinline__ uint64_t key() const { return k; }
+};
+struct ScoreItems {
+  typedef ScoreItem Item;
+  const float* scores;
+  int64_t P;
+  __device__ __forceinline__ ScoreItem load(int64_t i) const { return ScoreItem{score_key(scores[i]), i < P ? 1 : 0}; }
+};
 
 // cnt[j] = 1 for a negative at sorted position j, cnt[total] = 0; an
 // exclusive scan then gives the negatives before every position.
-__global__ __launch_bounds__(256) void metrics_negflag_kernel(const int32_t* __restrict__ pos, int64_t total,
+__global__ __launch_bounds__(256) void metrics_negflag_kernel(const ScoreItem* __restrict__ items, int64_t total,
                                                               int64_t* __restrict__ cnt) {
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j <= total; j += (int64_t)gridDim.x * blockDim.x)
-    cnt[j] = j < total ? 1 - pos[j] : 0;
+    cnt[j] = j < total ? 1 - items[j].pos : 0;
 }
 
 // For the positive at sorted position j with key k: lo = first position
 // with key k, hi = first position past them (binary searches).  Negatives
 // below: neg[lo]; equal: neg[hi] - neg[lo]; scores >= s: total - lo, of
 // which positives: P - (lo - neg[lo]).  Sums per workgroup in position order.
-__global__ __launch_bounds__(256) void metrics_count_kernel(const int32_t* __restrict__ key,
-                                                            const int32_t* __restrict__ pos,
+__global__ __launch_bounds__(256) void metrics_count_kernel(const ScoreItem* __restrict__ items,
                                                             const int64_t* __restrict__ neg, int64_t P, int64_t total,
                                                             unsigned long long* __restrict__ auc_part,
                                                             double* __restrict__ ap_part) {
@@ -560,18 +476,18 @@ __global__ __launch_bounds__(256) void metrics_count_kernel(const int32_t* __res
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   double ap = 0.0;
   unsigned long long auc2 = 0;
-  if (j < total && pos[j]) {
-    const uint32_t k = (uint32_t)key[j];
+  if (j < total && items[j].pos) {
+    const uint32_t k = items[j].k;
     int64_t a = 0, b = j;                           // first position in [0, j] with key >= k
     while (a < b) {
       const int64_t m = a + (b - a) / 2;
-      if ((uint32_t)key[m] < k) a = m + 1; else b = m;
+      if (items[m].k < k) a = m + 1; else b = m;
     }
     const int64_t lo = a;
     a = j + 1; b = total;                           // first position in [j + 1, total) with key > k
     while (a < b) {
       const int64_t m = a + (b - a) / 2;
-      if ((uint32_t)key[m] <= k) a = m + 1; else b = m;
+      if (items[m].k <= k) a = m + 1; else b = m;
     }
     const int64_t hi = a;
     const int64_t nlo = neg[lo], nhi = neg[hi];
@@ -660,13 +576,11 @@ hipError_t pair_loss_launch(int prec, int64_t n, int64_t F, int64_t ld, const vo
   return hipGetLastError();
 }
 
-// Passes for keys in [0, n] with 8-bit digits (wider digits measured no
-// faster: the 9-bit scatter took as long as the pass it saved).
-void rs_plan(int64_t n, int* passes, int* width) {
+// Bits of the keys 0 .. n.
+int pair_key_bits(int64_t n) {
   int bits = 1;
   while (((int64_t)1 << bits) <= n) ++bits;
-  *width = 8;
-  *passes = (bits + 7) / 8;
+  return bits;
 }
 
 int64_t pair_seg_count(int64_t n_pairs) {
@@ -679,87 +593,66 @@ int64_t pair_partial_ld(int prec, int64_t F) {
   return (F + ve - 1) / ve * ve;
 }
 
+namespace {
+struct PairLayout {
+  PairEnd *eA, *eB;
+  void* radix;
+  int64_t* off;
+  float *head, *tail;
+  int32_t* tail_row;
+  size_t bytes;
+};
+// Carves the workspace (ws may be NULL to size it, for every precision).
+PairLayout pair_layout(int64_t n, int64_t n_pairs, int64_t F, void* ws) {
+  const int64_t total = 2 * n_pairs, nseg = pair_seg_count(n_pairs);
+  const int64_t ldp = std::max(pair_partial_ld(1, F), pair_partial_ld(0, F));
+  PairLayout L;
+  char* base = static_cast<char*>(ws);
+  size_t o = 0;
+  auto take = [&](size_t bytes) { char* q = base ? base + o : nullptr; o += align256(bytes); return q; };
+  L.eA = (PairEnd*)take(sizeof(PairEnd) * (total > 0 ? total : 1));
+  L.eB = (PairEnd*)take(sizeof(PairEnd) * (total > 0 ? total : 1));
+  L.radix = take(radix_scratch_bytes(total));
+  L.off = (int64_t*)take(sizeof(int64_t) * (n + 1));
+  L.head = (float*)take(sizeof(float) * nseg * ldp);
+  L.tail = (float*)take(sizeof(float) * nseg * ldp);
+  L.tail_row = (int32_t*)take(sizeof(int32_t) * nseg);
+  L.bytes = o;
+  return L;
+}
+}  // namespace
+
 size_t pair_backward_workspace_bytes(int64_t n, int64_t n_pairs, int64_t F) {
-  const int64_t total = 2 * n_pairs;
-  const int64_t nblk = (total + RS_TILE - 1) / RS_TILE;
-  const int64_t nh = ((int64_t)1 << RS_MAX_BITS) * (nblk < 1 ? 1 : nblk);
-  const int64_t nseg = pair_seg_count(n_pairs);
-  const int64_t ldp = pair_partial_ld(1, F) > pair_partial_ld(0, F) ? pair_partial_ld(1, F) : pair_partial_ld(0, F);
-  size_t b = 0;
-  b += 6 * align256(sizeof(int32_t) * (total > 0 ? total : 1));          // key, pair, other: two buffers each
-  b += align256(sizeof(int64_t) * nh);                                    // digit histograms / offsets
-  b += align256(sizeof(int64_t) * segment_scan_scratch_elems(nh));        // scan scratch
-  b += align256(sizeof(int64_t) * (n + 1));                               // row offsets
-  b += 2 * align256(sizeof(float) * nseg * ldp);                          // head and tail partials
-  b += align256(sizeof(int32_t) * nseg);                                  // tail rows
-  return b;
+  return pair_layout(n, n_pairs, F, nullptr).bytes;
 }
 
 hipError_t pair_backward_launch(int prec, int64_t n, int64_t F, int64_t ld, const void* Z, const int32_t* pair_u,
                                 const int32_t* pair_v, int64_t n_pairs, const float* g, void* dZ, int64_t ldz,
                                 int32_t* flag, void* ws, hipStream_t s) {
   const int64_t total = 2 * n_pairs;
-  const int64_t nblk = (total + RS_TILE - 1) / RS_TILE;
-  const int64_t nh = ((int64_t)1 << RS_MAX_BITS) * (nblk < 1 ? 1 : nblk);
-  const int64_t nseg = pair_seg_count(n_pairs);
-  const int64_t ldp = pair_partial_ld(prec, F);
-  char* w = static_cast<char*>(ws);
-  auto take = [&](size_t bytes) { char* q = w; w += align256(bytes); return q; };
-  const size_t tb = sizeof(int32_t) * (total > 0 ? total : 1);
-  int32_t* kA = (int32_t*)take(tb);
-  int32_t* vA = (int32_t*)take(tb);
-  int32_t* oA = (int32_t*)take(tb);
-  int32_t* kB = (int32_t*)take(tb);
-  int32_t* vB = (int32_t*)take(tb);
-  int32_t* oB = (int32_t*)take(tb);
-  int64_t* hist = (int64_t*)take(sizeof(int64_t) * nh);
-  int64_t* scr = (int64_t*)take(sizeof(int64_t) * segment_scan_scratch_elems(nh));
-  int64_t* off = (int64_t*)take(sizeof(int64_t) * (n + 1));
-  const size_t pbytes = sizeof(float) * nseg * (pair_partial_ld(1, F) > pair_partial_ld(0, F) ? pair_partial_ld(1, F)
-                                                                                               : pair_partial_ld(0, F));
-  float* head = (float*)take(pbytes);
-  float* tail = (float*)take(pbytes);
-  int32_t* trow = (int32_t*)take(sizeof(int32_t) * nseg);
+  const PairLayout L = pair_layout(n, n_pairs, F, ws);
   hipError_t e;
 #define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-  const int32_t* kin = nullptr;
-  const int32_t* vin = nullptr;
-  const int32_t* oin = nullptr;
-  int32_t* kout = kA;
-  int32_t* vout = vA;
-  int32_t* oout = oA;
+  ItemArray<PairEnd> in{L.eB}, out{L.eA};
   if (total > 0) {
-    int passes = 0, width = 8;
-    rs_plan(n, &passes, &width);
-    const int64_t nhw = ((int64_t)1 << width) * nblk;
+    const int bits = pair_key_bits(n);
+    int passes = 0, width = 0;
+    radix_plan(bits, &passes, &width);
     for (int ps = 0; ps < passes; ++ps) {
-      const int shift = ps * width;
-#define RS_PASS(B)                                                                                          \
-  hipLaunchKernelGGL(rs_hist_kernel<B>, dim3((unsigned)nblk), dim3(256), 0, s, n, pair_u, pair_v, kin, total, \
-                     shift, nblk, hist);                                                                    \
-  GCN_TRY(hipGetLastError());                                                                               \
-  GCN_TRY(segment_scan_exclusive(hist, nhw, scr, s));                                                       \
-  hipLaunchKernelGGL(rs_scatter_kernel<B>, dim3((unsigned)nblk), dim3(256), 0, s, n, pair_u, pair_v, kin, vin, \
-                     oin, g, total, shift, nblk, hist, kout, vout, oout);                                      \
-  GCN_TRY(hipGetLastError());
-      RS_PASS(8)
-#undef RS_PASS
-      kin = kout;
-      vin = vout;
-      oin = oout;
-      kout = kout == kA ? kB : kA;
-      vout = vout == vA ? vB : vA;
-      oout = oout == oA ? oB : oA;
+      const int shift = ps * width, w = std::min(width, bits - shift);
+      if (ps == 0) GCN_TRY(radix_pass(PairEnds{n, pair_u, pair_v, g}, out, total, shift, w, L.radix, s));
+      else GCN_TRY(radix_pass(in, out, total, shift, w, L.radix, s));
+      std::swap(in, out);
     }
   }
   const unsigned bb = (unsigned)capped_blocks(total + 1, 256);
-  hipLaunchKernelGGL(rs_bounds_kernel, dim3(bb), dim3(256), 0, s, n, kin ? kin : kA, total, off);
+  hipLaunchKernelGGL(rs_bounds_kernel, dim3(bb), dim3(256), 0, s, n, in.p, total, L.off);
   GCN_TRY(hipGetLastError());
   SegParams p;
-  p.n = n; p.F = F; p.ld = ld; p.Z = Z; p.pu = pair_u; p.pv = pair_v; p.off = off;
-  p.pg = vin ? vin : vA;
-  p.po = oin ? oin : oA;
-  p.nseg = nseg; p.head = head; p.tail = tail; p.tail_row = trow; p.ldp = ldp;
+  p.n = n; p.F = F; p.ld = ld; p.Z = Z; p.off = L.off;
+  p.ends = in.p;
+  p.nseg = pair_seg_count(n_pairs); p.head = L.head; p.tail = L.tail; p.tail_row = L.tail_row;
+  p.ldp = pair_partial_ld(prec, F);
   Epilogue ep{};
   ep.out = dZ; ep.ldo = ldz; ep.rows = n; ep.cols = F; ep.mode = EPI_STORE; ep.flag = flag; ep.keep_scale = 1.f;
   p.ep = ep;
@@ -776,27 +669,24 @@ hipError_t pair_backward_launch(int prec, int64_t n, int64_t F, int64_t ld, cons
 
 namespace {
 struct MetricsLayout {
-  int32_t *kA, *pA, *iA, *kB, *pB, *iB;
-  int64_t *hist, *scr, *neg;
+  ScoreItem *iA, *iB;
+  void* radix;
+  int64_t *scr, *neg;
   double* ap_part;
   unsigned long long* auc_part;
   size_t bytes;
 };
 // Carves the workspace (ws may be NULL to size it).
 MetricsLayout metrics_layout(int64_t total, void* ws) {
-  const int64_t nblk = (total + RS_TILE - 1) / RS_TILE;
-  const int64_t nh = ((int64_t)1 << RS_MAX_BITS) * (nblk < 1 ? 1 : nblk);
   const int64_t nb = (total + 255) / 256;
-  const int64_t scan_n = nh > total + 1 ? nh : total + 1;
   MetricsLayout L;
   char* base = static_cast<char*>(ws);
   size_t o = 0;
   auto take = [&](size_t bytes) { char* q = base ? base + o : nullptr; o += align256(bytes); return q; };
-  const size_t tb = sizeof(int32_t) * total;
-  L.kA = (int32_t*)take(tb); L.pA = (int32_t*)take(tb); L.iA = (int32_t*)take(tb);
-  L.kB = (int32_t*)take(tb); L.pB = (int32_t*)take(tb); L.iB = (int32_t*)take(tb);
-  L.hist = (int64_t*)take(sizeof(int64_t) * nh);
-  L.scr = (int64_t*)take(sizeof(int64_t) * segment_scan_scratch_elems(scan_n));
+  L.iA = (ScoreItem*)take(sizeof(ScoreItem) * total);
+  L.iB = (ScoreItem*)take(sizeof(ScoreItem) * total);
+  L.radix = take(radix_scratch_bytes(total));
+  L.scr = (int64_t*)take(sizeof(int64_t) * segment_scan_scratch_elems(total + 1));
   L.neg = (int64_t*)take(sizeof(int64_t) * (total + 1));
   L.ap_part = (double*)take(sizeof(double) * nb);
   L.auc_part = (unsigned long long*)take(sizeof(unsigned long long) * nb);
@@ -813,32 +703,21 @@ hipError_t pair_metrics_launch(const float* scores, int64_t n_pos, int64_t n_neg
                                hipStream_t s) {
   const int64_t total = n_pos + n_neg;
   const MetricsLayout L = metrics_layout(total, ws);
-  const int64_t nblk = (total + RS_TILE - 1) / RS_TILE;
   const int64_t nb = (total + 255) / 256;
   const unsigned gb = (unsigned)capped_blocks(total + 1, 256);
   hipError_t e;
 #define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-  hipLaunchKernelGGL(metrics_prep_kernel, dim3(gb), dim3(256), 0, s, scores, n_pos, total, L.kA, L.pA, L.iA);
-  GCN_TRY(hipGetLastError());
-  // four stable 8-bit passes over the 32-bit keys: A -> B -> A -> B -> A
-  int32_t *kin = L.kA, *pin = L.pA, *iin = L.iA, *kout = L.kB, *pout = L.pB, *iout = L.iB;
-  for (int shift = 0; shift < 32; shift += RS_MAX_BITS) {
-    hipLaunchKernelGGL(rs_hist_kernel<RS_MAX_BITS>, dim3((unsigned)nblk), dim3(256), 0, s, (int64_t)0, nullptr, nullptr,
-                       kin, total, shift, nblk, L.hist);
-    GCN_TRY(hipGetLastError());
-    GCN_TRY(segment_scan_exclusive(L.hist, ((int64_t)1 << RS_MAX_BITS) * nblk, L.scr, s));
-    hipLaunchKernelGGL(rs_scatter_kernel<RS_MAX_BITS>, dim3((unsigned)nblk), dim3(256), 0, s, (int64_t)0, nullptr,
-                       nullptr, kin, pin, iin, nullptr, total, shift, nblk, L.hist, kout, pout, iout);
-    GCN_TRY(hipGetLastError());
-    int32_t* t;
-    t = kin; kin = kout; kout = t;
-    t = pin; pin = pout; pout = t;
-    t = iin; iin = iout; iout = t;
+  // four stable 8-bit passes over the 32-bit keys
+  ItemArray<ScoreItem> in{L.iB}, out{L.iA};
+  for (int shift = 0; shift < 32; shift += 8) {
+    if (shift == 0) GCN_TRY(radix_pass(ScoreItems{scores, n_pos}, out, total, shift, 8, L.radix, s));
+    else GCN_TRY(radix_pass(in, out, total, shift, 8, L.radix, s));
+    std::swap(in, out);
   }
-  hipLaunchKernelGGL(metrics_negflag_kernel, dim3(gb), dim3(256), 0, s, pin, total, L.neg);
+  hipLaunchKernelGGL(metrics_negflag_kernel, dim3(gb), dim3(256), 0, s, in.p, total, L.neg);
   GCN_TRY(hipGetLastError());
   GCN_TRY(segment_scan_exclusive(L.neg, total + 1, L.scr, s));
-  hipLaunchKernelGGL(metrics_count_kernel, dim3((unsigned)nb), dim3(256), 0, s, kin, pin, L.neg, n_pos, total,
+  hipLaunchKernelGGL(metrics_count_kernel, dim3((unsigned)nb), dim3(256), 0, s, in.p, L.neg, n_pos, total,
                      L.auc_part, L.ap_part);
   GCN_TRY(hipGetLastError());
   hipLaunchKernelGGL(pair_metrics_final_kernel, dim3(1), dim3(256), 0, s, L.auc_part, L.ap_part, nb, n_pos, n_neg,
