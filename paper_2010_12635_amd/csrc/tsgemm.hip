@@ -11,9 +11,11 @@
 //    MFMA operand fragments straight from global memory (rows are adjacent,
 //    so a wave's loads stay inside one compact region), with a 3-deep
 //    register ring of chunks in flight; B fragments come from LDS;
-//  * the output of each 16-row tile is staged through a per-wave LDS buffer
-//    and written as 16-byte row-contiguous vectors after the epilogue
-//    (plain store, or the ReLU/dropout derivative read from H).
+//  * the output of each 16-row tile is staged, 128 bytes of a row at a time,
+//    through a per-wave LDS buffer and written as 16-byte row-contiguous
+//    vectors after the epilogue (plain store, or the ReLU/dropout derivative
+//    read from H).  The buffer is kept that small, and the column blocks that
+//    narrow, so that two workgroups (two waves per SIMD) share a compute unit.
 #include "internal.h"
 #include "xpose.h"
 
@@ -56,19 +58,31 @@ struct TsParams {
   float* colsum;           // CS: [gridDim.x][N] column sums of the stored C, one row per workgroup
 };
 
-// Dynamic LDS: B block [nblk][kpad + VE] (T), then 4 per-wave staging
-// buffers [16][nblk + 4] (fp32).
+// Staging of a wave: 16 rows of VPC output vectors, in fp32 where the epilogue
+// still has to scale the sums, else already rounded to T.
+template <typename T, bool DM, int TNW>
+struct TsStage {
+  static constexpr int OV = Vec<T>::N;
+  static constexpr int VPC = TNW * 16 / OV < 8 ? TNW * 16 / OV : 8;     // vectors per row and step (at most 128 bytes)
+  static constexpr int NCH = (TNW * 16 / OV + VPC - 1) / VPC;            // steps per 16-row tile
+  static constexpr int NT = VPC * OV / 16;                               // 16-column tiles per step
+  static constexpr int IT = VPC < 4 ? 1 : VPC / 4;                       // vectors per lane and step
+  static constexpr int ROW = DM ? (VPC * OV + 4) * 4 : (VPC * OV + 16 / (int)sizeof(T)) * (int)sizeof(T);   // bytes
+  static constexpr int BYTES = 16 * ROW;
+};
+
+// Dynamic LDS: B block [nblk][kpad + VE] (T), then 4 per-wave staging buffers.
 // DM: epilogue multiplies by the ReLU/dropout derivative read from H
 // (EPI_DMASK with relu); otherwise a plain store.
 // CS: the workgroup also sums the stored values (as stored, i.e. rounded to
-// T) of each of its columns: the store pass writes them back to its staging
-// buffer, a lane adds the tile's 16 rows of its columns (tiles in order),
-// and at the end the four waves' sums are added in wave order into the
+// T) of each of its columns: a lane stores the same column vectors of every
+// tile and sums them in registers (tiles in order); at the end the lanes of
+// equal columns, then the four waves in wave order, are added into the
 // workgroup's row of p.colsum (bias gradient of the layer below, without a
 // pass of its own over C).
-template <typename T, bool BKC, bool DM, int CSM, int TM, int TNW>
+template <typename T, bool BKC, bool DM, bool CS, int TM, int TNW>
 __global__ __launch_bounds__(256) void tsgemm_kernel(TsParams p) {
-  constexpr bool CS = CSM != 0;
+  using St = TsStage<T, DM, TNW>;
   constexpr int VE = Vec<T>::N;
   constexpr int KC = 4 * VE;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -77,9 +91,8 @@ __global__ __launch_bounds__(256) void tsgemm_kernel(TsParams p) {
   const int nblk = p.nblk;
   const int64_t ldsb = p.kpad + VE;                 // LDS row stride of B (elements)
   T* sB = reinterpret_cast<T*>(smem);
-  float* sC = reinterpret_cast<float*>(smem + ((size_t)nblk * ldsb * sizeof(T) + 15) / 16 * 16);
-  const int ldc = nblk + 4;
-  float* myC = sC + wave * 16 * ldc;
+  unsigned char* sC = smem + ((size_t)nblk * ldsb * sizeof(T) + 15) / 16 * 16;
+  unsigned char* myC = sC + wave * St::BYTES;
   const int64_t n0 = (int64_t)blockIdx.y * nblk;
   const T* __restrict__ Bg = reinterpret_cast<const T*>(p.B);
 
@@ -141,15 +154,12 @@ __global__ __launch_bounds__(256) void tsgemm_kernel(TsParams p) {
   const int64_t full = p.K / KC;                    // chunks with no k >= K
   const int tnw = min(TNW, nblk / 16);              // live column tiles of this block
   constexpr int OV = Vec<T>::N;
-  const int vpr = nblk / OV;
-  // CSM == 1 (vpr divides 64): a lane always stores the same column vector
-  // and sums it in registers (creg); CSM == 2: the tile's stored values go
-  // back to LDS and a lane sums columns lane and lane + 64 (csum)
-  constexpr bool cs_reg = CSM == 1;
-  float csum[2] = {0.f, 0.f};
-  float creg[OV];
+  const int sr = lane / St::VPC, sv = lane % St::VPC;   // this lane's row and vector of a staging step
+  float creg[St::NCH][OV];                              // CS: sums of its column vectors
 #pragma unroll
-  for (int j = 0; j < OV; ++j) creg[j] = 0.f;
+  for (int c = 0; c < St::NCH; ++c)
+#pragma unroll
+    for (int j = 0; j < OV; ++j) creg[c][j] = 0.f;
 
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t r0 = tile * tile_rows + (int64_t)wave * (TM * 16);
@@ -185,7 +195,7 @@ __global__ __launch_bounds__(256) void tsgemm_kernel(TsParams p) {
     // the tile costs one memory latency.
     constexpr bool dmask = DM;
     constexpr bool HPRE = DM && sizeof(T) == 2;          // H prefetched into registers
-    constexpr int EIT = HPRE ? 4 : 1;                    // vectors per lane per 16 rows (nblk <= 128)
+    constexpr int EIT = HPRE ? St::NCH * St::IT : 1;     // vectors per lane per 16 rows
     uint4 hv[TM][EIT];
     auto prefetch_h = [&]() {
       if constexpr (HPRE) {
@@ -194,10 +204,9 @@ __global__ __launch_bounds__(256) void tsgemm_kernel(TsParams p) {
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
           for (int it = 0; it < EIT; ++it) {
-            const int idx = lane + 64 * it;
-            const int rr = idx / vpr, cv = idx % vpr;
+            const int rr = sr + (64 / St::VPC) * (it % St::IT), cv = sv + St::VPC * (it / St::IT);
             const int64_t row = r0 + tm * 16 + rr, col = n0 + cv * OV;
-            const bool ok = idx < 16 * vpr && row < p.M && col < p.N;
+            const bool ok = rr < 16 && cv * OV < nblk && row < p.M && col < p.N;
             hv[tm][it] = ldg16(hm + (ok ? row * p.epi.ldh + col : 0));
           }
       }
@@ -262,69 +271,60 @@ __global__ __launch_bounds__(256) void tsgemm_kernel(TsParams p) {
     }
 #undef TS_FENCE
 
-    // ---- epilogue: per 16-row tile, MFMA layout -> LDS -> row vectors
+    // ---- epilogue: per 16-row tile and step, MFMA layout -> LDS -> row vectors
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
-      for (int tn = 0; tn < TNW; ++tn)
-        if (tn < tnw) {
+      for (int c = 0; c < St::NCH; ++c) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) myC[((lane >> 4) * 4 + v) * ldc + tn * 16 + (lane & 15)] = acc[tm][tn][v];
-        }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      constexpr int NIT = 16 * 128 / Vec<T>::N / 64;   // iterations covering nblk <= 128
+        for (int q = 0; q < St::NT; ++q) {
+          const int tn = c * St::NT + q;
+          if (tn < TNW && tn < tnw) {
 #pragma unroll
-      for (int it = 0; it < NIT; ++it) {
-        const int idx = lane + 64 * it;
-        if (idx >= 16 * vpr) break;
-        const int rr = idx / vpr, cv = idx % vpr;
-        const int64_t row = r0 + tm * 16 + rr, col = n0 + cv * OV;
-        if (row >= p.M || col >= p.N) {
-          if constexpr (CS && !cs_reg) {
-#pragma unroll
-            for (int j = 0; j < OV; ++j) myC[rr * ldc + cv * OV + j] = 0.f;
+            for (int v = 0; v < 4; ++v) {
+              unsigned char* at = myC + ((lane >> 4) * 4 + v) * St::ROW;
+              const int cc = q * 16 + (lane & 15);
+              const float x = acc[tm][tn < TNW ? tn : 0][v];
+              if constexpr (dmask) reinterpret_cast<float*>(at)[cc] = x;
+              else reinterpret_cast<T*>(at)[cc] = from_f32<T>(x);
+            }
           }
-          continue;
         }
-        float v[OV];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int j = 0; j < OV; ++j) v[j] = myC[rr * ldc + cv * OV + j];
-        if constexpr (dmask) {
-          float h[OV];
-          if constexpr (HPRE) unpack<T>(hv[tm][it], h);
-          else unpack<T>(ldg16(reinterpret_cast<const T*>(p.epi.hmask) + row * p.epi.ldh + col), h);
+        for (int it = 0; it < St::IT; ++it) {
+          const int rr = sr + (64 / St::VPC) * it, cv = sv + St::VPC * c;
+          const int64_t row = r0 + tm * 16 + rr, col = n0 + cv * OV;
+          if (rr >= 16 || cv * OV >= nblk || row >= p.M || col >= p.N) continue;
+          const unsigned char* at = myC + rr * St::ROW;
+          const int64_t nl = p.N - col;
+          const int live = nl >= OV ? OV : (int)nl;        // columns >= N are stored as 0
+          uint4 o;
+          if constexpr (dmask) {
+            float v[OV], h[OV];
 #pragma unroll
-          for (int j = 0; j < OV; ++j) v[j] = h[j] > 0.f ? v[j] * p.epi.keep_scale : 0.f;
-        }
-        if constexpr (CS) {
-          if constexpr (cs_reg) {
+            for (int j = 0; j < OV; ++j) v[j] = reinterpret_cast<const float*>(at)[sv * OV + j];
+            if constexpr (HPRE) unpack<T>(hv[tm][c * St::IT + it], h);
+            else unpack<T>(ldg16(reinterpret_cast<const T*>(p.epi.hmask) + row * p.epi.ldh + col), h);
 #pragma unroll
-            for (int j = 0; j < OV; ++j) creg[j] += col + j < p.N ? to_f32<T>(from_f32<T>(v[j])) : 0.f;
+            for (int j = 0; j < OV; ++j) v[j] = h[j] > 0.f ? v[j] * p.epi.keep_scale : 0.f;
+            o = pack<T>(v);
           } else {
-#pragma unroll
-            for (int j = 0; j < OV; ++j)
-              myC[rr * ldc + cv * OV + j] = col + j < p.N ? to_f32<T>(from_f32<T>(v[j])) : 0.f;
+            o = *reinterpret_cast<const uint4*>(at + sv * 16);
           }
-        }
-        Epilogue plain = p.epi;
-        plain.mode = EPI_STORE;
-        epi_store_vec<T>(plain, row, col, v);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if constexpr (CS && !cs_reg) {
-        // the tile's stored values are in myC: rows in order per column
+          o = keep_first<T>(o, live);
+          stg16(reinterpret_cast<T*>(p.epi.out) + row * p.epi.ldo + col, o);
+          float st[OV];
+          unpack<T>(o, st);
+          bool bad = false;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int c = lane + 64 * h;
-          if (c < nblk) {
-            float a = myC[c];
+          for (int j = 0; j < OV; ++j) bad |= !finite_f32(st[j]);
+          if (bad) raise_flag(p.epi.flag);
+          if constexpr (CS) {
 #pragma unroll
-            for (int r = 1; r < 16; ++r) a += myC[r * ldc + c];
-            csum[h] += a;
+            for (int j = 0; j < OV; ++j) creg[c][j] += st[j];
           }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -334,80 +334,90 @@ __global__ __launch_bounds__(256) void tsgemm_kernel(TsParams p) {
     }
   }
   if constexpr (CS) {
-    if constexpr (cs_reg) {
-      // lanes l, l + vpr, l + 2 vpr, ... hold the same columns: butterfly
+    // lanes sv, sv + VPC, sv + 2 VPC, ... hold the same columns: butterfly
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1)
-        if (off >= vpr)
+    for (int off = 32; off >= St::VPC; off >>= 1)
 #pragma unroll
-          for (int j = 0; j < OV; ++j) creg[j] += __shfl_xor(creg[j], off);
-    }
+      for (int c = 0; c < St::NCH; ++c)
+#pragma unroll
+        for (int j = 0; j < OV; ++j) creg[c][j] += __shfl_xor(creg[c][j], off);
     __syncthreads();
-    if constexpr (cs_reg) {
-      if (lane < vpr)
+    float* sum = reinterpret_cast<float*>(sC);              // [4][nblk]
+    if (lane < St::VPC) {
 #pragma unroll
-        for (int j = 0; j < OV; ++j) myC[lane * OV + j] = creg[j];
-    } else {
+      for (int c = 0; c < St::NCH; ++c)
+        if ((sv + St::VPC * c) * OV < nblk)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (lane + 64 * h < nblk) myC[lane + 64 * h] = csum[h];
+          for (int j = 0; j < OV; ++j) sum[wave * nblk + (sv + St::VPC * c) * OV + j] = creg[c][j];
     }
     __syncthreads();
     for (int c = threadIdx.x; c < nblk; c += 256) {
       if (n0 + c < p.N) {
-        float a = sC[c];
-        a += sC[1 * 16 * ldc + c];
-        a += sC[2 * 16 * ldc + c];
-        a += sC[3 * 16 * ldc + c];
+        float a = sum[c];
+        a += sum[nblk + c];
+        a += sum[2 * nblk + c];
+        a += sum[3 * nblk + c];
         p.colsum[(int64_t)blockIdx.x * p.N + n0 + c] = a;
       }
     }
   }
 }
 
-// Dynamic LDS of one workgroup: the B block, then the four staging buffers.
+// Dynamic LDS of one workgroup: the B block, then the four staging buffers
+// (at most 128 bytes of output, or 256 of fp32 sums, and 16 more per row).
 template <typename T>
-size_t ts_lds_bytes(int64_t nblk, int64_t kpad) {
-  return ((size_t)nblk * (kpad + Vec<T>::N) * sizeof(T) + 15) / 16 * 16 + (size_t)4 * 16 * (nblk + 4) * sizeof(float);
+size_t ts_lds_bytes(int64_t nblk, int64_t kpad, bool dm) {
+  const int64_t w = std::min<int64_t>(8, (nblk <= 16 ? 16 : nblk <= 32 ? 32 : 64) / Vec<T>::N) * Vec<T>::N;
+  const size_t row = dm ? (w + 4) * 4 : w * sizeof(T) + 16;
+  return ((size_t)nblk * (kpad + Vec<T>::N) * sizeof(T) + 15) / 16 * 16 + 4 * 16 * row;
 }
 
 // Half of a gfx950 compute unit's 160 KB of LDS.
 constexpr size_t TS_LDS_TWO_WG = 80 * 1024;
 
+// Workgroups per column block: enough to fill every CU twice, and a multiple of
+// the dies, so that the column blocks of a row tile run on the same die and
+// share A's lines in its L2.
+int64_t ts_wgs_per_col(int64_t nb) { return std::max<int64_t>(XCDS, 512 / nb / XCDS * XCDS); }
+
+// Columns of a block: equal blocks (every block gets as many workgroups), and
+// narrow enough (us, with one workgroup per compute unit -> now: fp16 n =
+// 131072, 256 -> 256 72.8 -> 40.0, 500 -> 64 43.6 -> 33.1; n = 1 M, 256 -> 256
+// 481 -> 262, 128 -> 128 118 -> 99; n = 2048, 400 -> 150 11.2 -> 7.6; fp32 n = 1
+// M, 256 -> 256 1379 -> 1149)
+//  * for the B block's cap and for two workgroups per compute unit: with one
+//    wave per SIMD the matrix instructions wait on each B read from LDS, and
+//    the loads of A on the epilogue, with no other wave to issue;
+//  * where the rows are few, for a workgroup per compute unit (not below 32
+//    columns: each block reads all of A).
 template <typename T>
-int ts_nblk(int64_t N, int64_t kpad) {
-  int64_t nb = std::min<int64_t>(128, (N + 15) / 16 * 16);
-  const int64_t cap = (TS_LDS_B_BYTES / ((kpad + Vec<T>::N) * (int64_t)sizeof(T))) / 16 * 16;
-  nb = std::min<int64_t>(nb, std::max<int64_t>(cap, 16));
-  // fp32: equal narrower column blocks rather than one workgroup (one wave
-  // per SIMD) per compute unit: a 128 x 128 fp32 block of W with its
-  // staging needs 101 KB, and the 16x16x4 fp32 matrix instructions then
-  // wait on each B read from LDS with no other wave to issue
-  if (sizeof(T) == 4) {
-    for (int64_t parts = 2; nb > 16 && ts_lds_bytes<T>(nb, kpad) > TS_LDS_TWO_WG; ++parts)
-      nb = std::min<int64_t>(nb, ((N + parts - 1) / parts + 15) / 16 * 16);
-  }
-  return (int)nb;
+int ts_nblk(int64_t M, int64_t N, int64_t kpad, bool dm) {
+  auto block = [&](int64_t parts) { return ((N + parts - 1) / parts + 15) / 16 * 16; };
+  const int64_t cap = std::max<int64_t>(TS_LDS_B_BYTES / ((kpad + Vec<T>::N) * (int64_t)sizeof(T)) / 16 * 16, 16);
+  int64_t parts = (N + 127) / 128;
+  while (block(parts) > 16 && (block(parts) > cap || ts_lds_bytes<T>(block(parts), kpad, dm) > TS_LDS_TWO_WG)) ++parts;
+  while (block(parts + 1) >= 32 && (M + 63) / 64 * parts < 256) ++parts;
+  return (int)block(parts);
 }
 
-template <typename T, bool BKC, bool DM, int CSM, int TM>
+template <typename T, bool BKC, bool DM, bool CS, int TM>
 hipError_t launch_tm(const TsParams& p, int* grid_rows, hipStream_t s) {
   const int tnw = p.nblk / 16;
-  const size_t lds = ts_lds_bytes<T>(p.nblk, p.kpad);
+  const size_t lds = ts_lds_bytes<T>(p.nblk, p.kpad, DM);
   // persistent workgroups: enough to fill every CU twice, each looping over row tiles
   const int64_t nb = (p.N + p.nblk - 1) / p.nblk;
   const int64_t ntiles = (p.M + 64 * TM - 1) / (64 * TM);
-  const int64_t per_col = std::max<int64_t>(1, 512 / nb);
+  const int64_t per_col = ts_wgs_per_col(nb);
   dim3 grid((unsigned)std::min<int64_t>(ntiles, per_col), (unsigned)nb);
   if (grid_rows) *grid_rows = (int)grid.x;
 #define TS_L(TNW_)                                                                                          \
   do {                                                                                                      \
     if (lds > 65536) {                                                                                      \
-      hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&tsgemm_kernel<T, BKC, DM, CSM, TM, TNW_>),\
+      hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&tsgemm_kernel<T, BKC, DM, CS, TM, TNW_>),\
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);           \
       if (ea != hipSuccess) return ea;                                                                      \
     }                                                                                                       \
-    hipLaunchKernelGGL((tsgemm_kernel<T, BKC, DM, CSM, TM, TNW_>), grid, dim3(256), lds, s, p);                \
+    hipLaunchKernelGGL((tsgemm_kernel<T, BKC, DM, CS, TM, TNW_>), grid, dim3(256), lds, s, p);                \
   } while (0)
   if (tnw <= 1) TS_L(1);
   else if (tnw <= 2) TS_L(2);
@@ -419,23 +429,20 @@ hipError_t launch_tm(const TsParams& p, int* grid_rows, hipStream_t s) {
 
 template <typename T, bool BKC, bool DM, bool CS>
 hipError_t launch_b(TsParams p, int* grid_rows, hipStream_t s) {
-  constexpr int OV = Vec<T>::N;
   constexpr int KC = 4 * Vec<T>::N;
   p.kpad = (p.K + KC - 1) / KC * KC;
-  p.nblk = ts_nblk<T>(p.N, p.kpad);
-  // rows per wave: 32 when there are enough rows to fill the GPU, else 16
-  const int64_t tiles64 = (p.M + 255) / 256 * ((p.N + p.nblk - 1) / p.nblk);
+  p.nblk = ts_nblk<T>(p.M, p.N, p.kpad, DM);
+  // rows per wave: 32 (each B fragment read from LDS then serves two MFMAs)
+  // unless 16 leave the fullest workgroup less to do, as where the rows are
+  // few or the last round of tiles is nearly empty
   // (TM = 4 would need more than 256 registers per lane with the whole-K
   // fragment sets, i.e. one wave per SIMD; TM = 2 keeps two)
   // (the H-mask epilogue with 128-column blocks holds another 32 registers:
   // one row tile per wave keeps two waves per SIMD there)
-  const bool two = tiles64 >= 256 && !(DM && p.nblk > 64);
-  if constexpr (CS) {
-    if (64 % (p.nblk / OV) == 0)
-      return two ? launch_tm<T, BKC, DM, 1, 2>(p, grid_rows, s) : launch_tm<T, BKC, DM, 1, 1>(p, grid_rows, s);
-    return two ? launch_tm<T, BKC, DM, 2, 2>(p, grid_rows, s) : launch_tm<T, BKC, DM, 2, 1>(p, grid_rows, s);
-  }
-  return two ? launch_tm<T, BKC, DM, 0, 2>(p, grid_rows, s) : launch_tm<T, BKC, DM, 0, 1>(p, grid_rows, s);
+  const int64_t wgs = ts_wgs_per_col((p.N + p.nblk - 1) / p.nblk);
+  auto most = [&](int64_t tm) { return ((p.M + 64 * tm - 1) / (64 * tm) + wgs - 1) / wgs * tm; };
+  const bool two = 10 * most(2) <= 12 * most(1) && !(DM && p.nblk > 64);
+  return two ? launch_tm<T, BKC, DM, CS, 2>(p, grid_rows, s) : launch_tm<T, BKC, DM, CS, 1>(p, grid_rows, s);
 }
 
 // Column sums (CS) are only asked of dZ_below = (G_S W^T) * mask, whose B
