@@ -52,25 +52,41 @@ struct WgParams {
 
 // One k tile of H and G_S (KT vertices x 128 columns each) cut into VE x VE
 // blocks; thread t holds block(s) of VE rows x 16 bytes in registers.
-//   16-bit: 8 x 16 blocks per operand, threads 0..127 take H, 128..255 G_S.
-//   fp32:   8 x 32 blocks per operand, every thread takes one of each.
-template <typename T>
+// G_S has NB columns here: 128, or 16, 32, 48, 64 where N is no more.
+//   16-bit: 8 x 16 blocks of H, threads 0..127; 8 x NB / 8 of G_S, threads
+//           128 .. 127 + NB.
+//   fp32:   8 x 32 blocks of H, one per thread; 8 x NB / 4 of G_S, threads
+//           0 .. 2 NB - 1.
+// Four neighbouring lanes take four column blocks of a row block (64
+// contiguous bytes of each row), the next ones the other row blocks: with a
+// whole row of column blocks side by side the LDS stores of a wave fell on 16
+// (fp32) or 8 (16-bit) of the 64 banks.
+template <typename T, int NB>
 struct Tile {
   static constexpr int VE = Vec<T>::N;
   static constexpr int KT = 8 * VE;                // 64 (16-bit) / 32 (fp32)
-  static constexpr int CB = WG_B / VE;             // column blocks per operand
   static constexpr int NBLK = VE == 8 ? 1 : 2;     // blocks per thread
   uint4 r[NBLK][VE];
   int vrows[NBLK];                                 // rows of the block inside the span
   int vcols[NBLK];                                 // columns of the block inside the operand
 
+  // Row and column block of the blk-th block of an operand of COLS columns.
+  template <int COLS>
+  static __device__ __forceinline__ void place(int blk, int& rb, int& cb) {
+    constexpr int CB = COLS / VE, Q = CB % 4 == 0 ? 4 : 2;
+    cb = blk % Q + blk / (8 * Q) * Q;
+    rb = blk / Q % 8;
+  }
+
   // Issue the block's VE row loads without waiting for any of them: rows
   // beyond the span and blocks beyond the operand read row kfirst / column 0
   // instead (always in bounds) and are zeroed in store(), so the loads are
   // unconditional and stay in flight while the previous tile is multiplied.
+  template <int COLS>
   __device__ __forceinline__ void load_block(int b, const T* __restrict__ base, int64_t ld, int64_t c0, int64_t cols,
                                              int64_t k0, int64_t kend, int64_t kfirst, int blk) {
-    const int rb = blk / CB, cb = blk % CB;
+    int rb, cb;
+    place<COLS>(blk, rb, cb);
     const int64_t gc = c0 + (int64_t)cb * VE;
     const int64_t r0 = k0 + rb * VE;
     const int64_t nr = kend - r0, ncol = cols - gc;
@@ -86,11 +102,11 @@ struct Tile {
   __device__ __forceinline__ void load(const WgParams& p, const T* H, const T* G, int64_t m0, int64_t n0,
                                        int64_t k0, int64_t kend, int64_t kfirst, int tid) {
     if (VE == 8) {
-      if (tid < 128) load_block(0, H, p.ldh, m0, p.M, k0, kend, kfirst, tid);
-      else load_block(0, G, p.ldg, n0, p.N, k0, kend, kfirst, tid - 128);
+      if (tid < 128) load_block<WG_B>(0, H, p.ldh, m0, p.M, k0, kend, kfirst, tid);
+      else if (tid < 128 + NB) load_block<NB>(0, G, p.ldg, n0, p.N, k0, kend, kfirst, tid - 128);
     } else {
-      load_block(0, H, p.ldh, m0, p.M, k0, kend, kfirst, tid);
-      load_block(NBLK - 1, G, p.ldg, n0, p.N, k0, kend, kfirst, tid);
+      load_block<WG_B>(0, H, p.ldh, m0, p.M, k0, kend, kfirst, tid);
+      if (tid < 2 * NB) load_block<NB>(NBLK - 1, G, p.ldg, n0, p.N, k0, kend, kfirst, tid);
     }
   }
   // Zero the rows and columns outside the operand (first use of the data),
@@ -115,34 +131,44 @@ struct Tile {
     }
   }
   // LDS tiles [column][KT + VE], k-contiguous: one 16-byte store per column
+  template <int COLS>
+  __device__ __forceinline__ void store_block(int b, T* __restrict__ tile, int blk) {
+    mask(b);
+    int rb, cb;
+    place<COLS>(blk, rb, cb);
+    uint4 t[VE];
+    transpose_block(r[b], t, T());
+    T* dst = tile + (cb * VE) * (KT + VE) + rb * VE;
+#pragma unroll
+    for (int j = 0; j < VE; ++j) *reinterpret_cast<uint4*>(dst + j * (KT + VE)) = t[j];
+  }
   __device__ __forceinline__ void store(T* __restrict__ sA, T* __restrict__ sB, int tid) {
-#pragma unroll
-    for (int b = 0; b < NBLK; ++b) {
-      mask(b);
-      const bool isB = VE == 8 ? tid >= 128 : b == 1;
-      const int blk = VE == 8 ? (tid & 127) : tid;
-      const int rb = blk / CB, cb = blk % CB;
-      uint4 t[VE];
-      transpose_block(r[b], t, T());
-      T* dst = (isB ? sB : sA) + (cb * VE) * (KT + VE) + rb * VE;
-#pragma unroll
-      for (int j = 0; j < VE; ++j) *reinterpret_cast<uint4*>(dst + j * (KT + VE)) = t[j];
+    if (VE == 8) {
+      if (tid < 128) store_block<WG_B>(0, sA, tid);
+      else if (tid < 128 + NB) store_block<NB>(0, sB, tid - 128);
+    } else {
+      store_block<WG_B>(0, sA, tid);
+      if (tid < 2 * NB) store_block<NB>(NBLK - 1, sB, tid);
     }
   }
 };
 
-// NARROW (N <= 64, one column block): the four waves take 32 rows x 64
-// columns each instead of 2 x 2 tiles of 64 x 64, so that no wave
-// multiplies the zero columns 64 .. 127 (fp32 dW of a 64-column layer had
-// half of its matrix instructions on zeros).
-template <typename T, bool NARROW>
+// NB <= 64 (N <= NB, one column block): the four waves take 32 rows x NB
+// columns each instead of 2 x 2 tiles of 64 x 64, so that no more than 15 of
+// the columns multiplied, staged and loaded are padding (with 64 columns for
+// every N <= 64 the matrix instructions and the LDS stores bound fp32: n =
+// 200000, 128 x 40, 50.0 us, now 40.8; 134 MB, 27 us at a copy's rate; fp16 n =
+// 2048, 512 x 16 10.1 us, now 6.6).
+template <typename T, int NB>
 __global__ __launch_bounds__(256) void wgrad_kernel(WgParams p) {
+  typedef Tile<T, NB> TileT;
+  constexpr bool NARROW = NB <= 64;
   constexpr int VE = Vec<T>::N;
-  constexpr int KT = Tile<T>::KT;
+  constexpr int KT = TileT::KT;
   constexpr int LDK = KT + VE;
-  constexpr int TM = NARROW ? 2 : 4, TN = 4;       // wave tile 32 x 64 (4 x 1 waves) or 64 x 64 (2 x 2)
+  constexpr int TM = NARROW ? 2 : 4, TN = NARROW ? NB / 16 : 4;   // wave tile 32 x NB (4 x 1 waves) or 64 x 64 (2 x 2)
   __shared__ __align__(16) T sA[2][WG_B * LDK];
-  __shared__ __align__(16) T sB[2][WG_B * LDK];
+  __shared__ __align__(16) T sB[2][NB * LDK];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -161,8 +187,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgParams p) {
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int64_t nt = ke > kb ? (ke - kb + KT - 1) / KT : 0;
-  Tile<T> t0, t1;
-  auto load = [&](Tile<T>& x, int64_t t) { x.load(p, Hg, Gg, m0, n0, kb + t * KT, ke, kb, tid); };
+  TileT t0, t1;
+  auto load = [&](TileT& x, int64_t t) { x.load(p, Hg, Gg, m0, n0, kb + t * KT, ke, kb, tid); };
   auto compute = [&](int st) {
     const T* as = sA[st] + (wr + (lane & 15)) * LDK + (lane >> 4) * VE;
     const T* bs = sB[st] + (wc + (lane & 15)) * LDK + (lane >> 4) * VE;
@@ -181,7 +207,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgParams p) {
   };
   // one step: park tile t (registers x) in LDS buffer t % 2, refill x with
   // tile t + 2, multiply tile t
-  auto step = [&](Tile<T>& x, int64_t t) {
+  auto step = [&](TileT& x, int64_t t) {
     const int st = (int)(t & 1);
     x.store(sA[st], sB[st], tid);
     __syncthreads();
@@ -214,8 +240,11 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgParams p) {
 template <typename T>
 hipError_t launch_t(const WgParams& p, int splits, hipStream_t s) {
   dim3 grid((unsigned)splits, (unsigned)((p.M + WG_B - 1) / WG_B), (unsigned)((p.N + WG_B - 1) / WG_B));
-  if (p.N <= 64) hipLaunchKernelGGL((wgrad_kernel<T, true>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((wgrad_kernel<T, false>), grid, dim3(256), 0, s, p);
+  if (p.N <= 16) hipLaunchKernelGGL((wgrad_kernel<T, 16>), grid, dim3(256), 0, s, p);
+  else if (p.N <= 32) hipLaunchKernelGGL((wgrad_kernel<T, 32>), grid, dim3(256), 0, s, p);
+  else if (p.N <= 48) hipLaunchKernelGGL((wgrad_kernel<T, 48>), grid, dim3(256), 0, s, p);
+  else if (p.N <= 64) hipLaunchKernelGGL((wgrad_kernel<T, 64>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((wgrad_kernel<T, 128>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
