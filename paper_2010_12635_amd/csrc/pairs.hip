@@ -178,6 +178,9 @@ int64_t capped_blocks(int64_t items, int64_t per_block) {
 
 // Workgroups that several pairs per lane group and iteration must leave: with
 // fewer the chip is not full and one pair at a time is the shorter chain.
+// Whole call at the line and above: 2^17 pairs, F = 64, fp16 13.9 -> 10.3 us,
+// 2^16, F = 130 19.8 -> 12.5, 2^14, F = 500 14.2 -> 10.5, 2^15, F = 128, fp32 13.6
+// -> 10.4; below it the launches bound both (9.6 to 10.9 us).
 constexpr int64_t PAIR_LOSS_MIN_WG = 512;
 
 template <typename T, int LPR>
@@ -266,9 +269,25 @@ struct SegParams {
   Epilogue ep;
 };
 
+// The (g, other endpoint) of a segment's entries from the sorted list itself, or
+// from the segment's copy in LDS, whose entry 0 is entry `first` of the list.
+struct EndsGlobal {
+  const PairEnd* ends;
+  __device__ __forceinline__ int2 operator()(int64_t e) const {
+    const PairEnd x = ends[e];
+    return make_int2(x.g, x.other);
+  }
+};
+struct EndsLds {
+  const int2* ends;
+  int64_t first;
+  __device__ __forceinline__ int2 operator()(int64_t e) const { return ends[(int)(e - first)]; }
+};
+
 // Sum of g_k Z[other endpoint] over sorted entries [e0, e1) into acc.
-template <typename T>
-__device__ __forceinline__ void seg_sum(const SegParams& p, int64_t e0, int64_t e1, int64_t col0, float* acc) {
+template <typename T, typename Ends>
+__device__ __forceinline__ void seg_sum(const SegParams& p, const Ends& ends, int64_t e0, int64_t e1, int64_t col0,
+                                        float* acc) {
   constexpr int VE = Vec<T>::N, U = 8;
   const T* __restrict__ Z = reinterpret_cast<const T*>(p.Z);
   for (int64_t e = e0; e < e1; e += U) {
@@ -277,9 +296,9 @@ __device__ __forceinline__ void seg_sum(const SegParams& p, int64_t e0, int64_t 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t ee = e + u < e1 ? e + u : e1 - 1;
-      const PairEnd x = p.ends[ee];
-      w[u] = __int_as_float(x.g);
-      other[u] = x.other;
+      const int2 x = ends(ee);
+      w[u] = __int_as_float(x.x);
+      other[u] = x.y;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) w[u] = e + u < e1 ? w[u] : 0.f;
@@ -296,15 +315,25 @@ __device__ __forceinline__ void seg_sum(const SegParams& p, int64_t e0, int64_t 
   }
 }
 
+// What bounds it is the chain of dependent loads of a lane group (row ends,
+// entries, gathered rows) per eight entries, so from 4 lanes per group on the
+// group first copies its segment's entries to LDS, all loads at once, and a
+// row's end is loaded while the row before it is summed.  2^21 pairs, n = 2^17,
+// F = 64, fp16: 117.6 us with the entries read as they are used, 89.3 us so.
+// (Groups of 1 or 2 lanes would need 64 KB of LDS per workgroup or more.)
 template <typename T, int LPR>
-__global__ __launch_bounds__(256) void pair_segment_kernel(SegParams p) {
+__global__ __launch_bounds__(256, 4) void pair_segment_kernel(SegParams p) {
   constexpr int VE = Vec<T>::N;
   constexpr int G = 64 / LPR;
+  constexpr bool STAGED = LPR >= 4;
+  __shared__ int2 s_ends[STAGED ? 4 * G * SEG : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int gi = lane / LPR, li = lane % LPR;
   const int64_t col0 = (int64_t)li * VE;
   if (col0 >= p.ep.ldo) return;
   const bool live = col0 < p.F;                     // padding slices only write zeros
+  const int lanes = (int)min((int64_t)LPR, (p.ep.ldo + VE - 1) / VE);   // of the group, still running
+  int2* mine = s_ends + (STAGED ? (wave * G + gi) * SEG : 0);
   const int64_t total = p.off[p.n];                 // entries of valid pairs
   const int64_t nuse = total > 0 ? (total + SEG - 1) / SEG : 1;
   for (int64_t sgi = ((int64_t)blockIdx.x * 4 + wave) * G + gi; sgi < p.nseg; sgi += (int64_t)gridDim.x * 4 * G) {
@@ -319,33 +348,54 @@ __global__ __launch_bounds__(256) void pair_segment_kernel(SegParams p) {
     const int64_t a = sgi * SEG, b = min(a + SEG, total);
     const int64_t r0 = a > 0 ? (int64_t)p.ends[a - 1].k + 1 : 0;
     const int64_t r1 = sgi == nuse - 1 ? p.n : (int64_t)p.ends[b - 1].k + 1;
+    if constexpr (STAGED) {
+      // a group's lanes share a wave, whose LDS operations complete in order:
+      // the fences only keep the compiler from moving them
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll 8
+      for (int j = li; j < (int)(b - a); j += lanes) mine[j] = EndsGlobal{p.ends}(a + j);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    const auto ends = [&] {
+      if constexpr (STAGED) return EndsLds{mine, a};
+      else return EndsGlobal{p.ends};
+    }();
     float acc[VE];
     // head: the row that started before this segment
     if (r0 > 0 && p.off[r0] > a && a < b) {
 #pragma unroll
       for (int q = 0; q < VE; ++q) acc[q] = 0.f;
-      if (live) seg_sum<T>(p, a, min(p.off[r0], b), col0, acc);
+      if (live) seg_sum<T>(p, ends, a, min(p.off[r0], b), col0, acc);
       if (col0 < p.ldp) {
 #pragma unroll
         for (int q = 0; q < VE; ++q) p.head[sgi * p.ldp + col0 + q] = acc[q];
       }
     }
     int32_t trow = -1;
+    int64_t rs = 0, re = 0;
+    if (r0 < r1) {
+      rs = p.off[r0];
+      re = p.off[r0 + 1];
+    }
     for (int64_t r = r0; r < r1; ++r) {
-      const int64_t rs = p.off[r], re = p.off[r + 1];
+      const int64_t re_next = p.off[r + 2 <= r1 ? r + 2 : r1];
 #pragma unroll
       for (int q = 0; q < VE; ++q) acc[q] = 0.f;
       if (re <= b) {
-        if (live) seg_sum<T>(p, rs, re, col0, acc);
+        if (live) seg_sum<T>(p, ends, rs, re, col0, acc);
         epi_store_vec<T>(p.ep, r, col0, acc);
       } else {                                      // crosses the end: partial, fixed up later
-        if (live) seg_sum<T>(p, rs, b, col0, acc);
+        if (live) seg_sum<T>(p, ends, rs, b, col0, acc);
         if (col0 < p.ldp) {
 #pragma unroll
           for (int q = 0; q < VE; ++q) p.tail[sgi * p.ldp + col0 + q] = acc[q];
         }
         trow = (int32_t)r;
       }
+      rs = re;
+      re = re_next;
     }
     if (li == 0) p.tail_row[sgi] = trow;
   }
