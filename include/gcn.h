@@ -348,8 +348,10 @@ gcn_status gcn_layer_bwd(const gcn_adj* A, const gcn_layer* L, int32_t prec,
  * per GPU, held until the process ends; the call itself allocates nothing.
  * Arguments, results and errors are those of gcn_layer_bwd (same kernels,
  * bit-identical outputs), plus GCN_ERR_CAPACITY when the call would need
- * more scratch than the array holds (gcn_layer_workspace_size() tells how
- * much it needs).  Every call on one GPU shares that GPU's array and leaves
+ * more scratch than the array holds: never where gcn_layer_workspace_size()
+ * is no more than that, and in a dense product whose partial sums alone
+ * exceed it not either (the product then takes its rows in several
+ * launches).  Every call on one GPU shares that GPU's array and leaves
  * its contents behind: calls that overlap on one GPU (several streams or
  * host threads) race, and the caller must serialise them.  The current HIP
  * device must be the device of `stream`.

@@ -129,10 +129,15 @@ struct LayerPlan {
 };
 
 size_t plan_bytes(const LayerPlan& p) { return (size_t)p.floats * sizeof(float) + 256; }
+size_t plan_step_bytes(const LayerPlan& p) { return (size_t)(p.floats - p.cs_floats - p.cb_floats) * sizeof(float); }
 
-LayerPlan plan_layer_ranges(const gcn_adj* A, const gcn_layer* L, int32_t prec, bool ranges) {
+// Scratch of the dense aggregation: the partials of every row's k ranges, those
+// of the fewest rows it can take at a time, or none (the k range uncut).
+enum class Ranges { AllRows, FewestRows, None };
+
+LayerPlan plan_layer(const gcn_adj* A, const gcn_layer* L, int32_t prec, Ranges ranges = Ranges::AllRows) {
   LayerPlan p;
-  p.ranges = ranges;
+  p.ranges = ranges != Ranges::None;
   const int64_t n = A->n;
   const bool ident = L->identity_input != 0;    // no product with H = I
   p.s_split = ident ? 1 : gemm_choose_splits(prec, n, L->f_out, L->f_in);
@@ -146,7 +151,10 @@ LayerPlan plan_layer_ranges(const gcn_adj* A, const gcn_layer* L, int32_t prec, 
   upd((int64_t)p.dw_split * L->f_in * L->f_out);
   int64_t cs = 0;
   if (A->format != GCN_CSR) {
-    upd((int64_t)(dense_agg_workspace_bytes(prec, n, L->f_out, A->format == GCN_DENSE_TILED, ranges) / sizeof(float)) + 1);
+    const bool tiled = A->format == GCN_DENSE_TILED;
+    const size_t b = ranges == Ranges::FewestRows ? dense_agg_min_bytes(prec, n, L->f_out, tiled)
+                                                  : dense_agg_workspace_bytes(prec, n, L->f_out, tiled, p.ranges);
+    upd((int64_t)(b / sizeof(float)) + 1);
     cs = dense_agg_colsum_rows(prec, n) * L->f_out;
   } else {
     upd(spmm_partials_floats(view_of(A), prec, L->f_out));
@@ -161,14 +169,25 @@ LayerPlan plan_layer_ranges(const gcn_adj* A, const gcn_layer* L, int32_t prec, 
   return p;
 }
 
-// The k ranges of the streaming dense aggregation are an option: a layer that
-// fits the fixed scratch of gcn_layer_bwd_noalloc only without their partials
-// goes without them, in every call alike.
-LayerPlan plan_layer(const gcn_adj* A, const gcn_layer* L, int32_t prec) {
-  const LayerPlan p = plan_layer_ranges(A, L, prec, true);
-  if (plan_bytes(p) <= (size_t)GCN_NOALLOC_SCRATCH_BYTES) return p;
-  const LayerPlan q = plan_layer_ranges(A, L, prec, false);
-  return plan_bytes(q) <= (size_t)GCN_NOALLOC_SCRATCH_BYTES ? q : p;
+// gcn_layer_bwd_noalloc has GCN_NOALLOC_SCRATCH_BYTES whatever the layer.  Where
+// the partials of the k ranges do not fit it for all rows, the aggregation takes
+// the rows in several launches, which changes no bit; where not even one row of
+// tiles fits but the layer without partials does, the k range is not cut, there
+// and in gcn_layer_bwd, whose bits the call shares.
+constexpr size_t NOALLOC_BYTES = GCN_NOALLOC_SCRATCH_BYTES;
+
+LayerPlan plan_layer_fixed(const gcn_adj* A, const gcn_layer* L, int32_t prec) {
+  LayerPlan p = plan_layer(A, L, prec, Ranges::FewestRows);
+  if (plan_bytes(p) > NOALLOC_BYTES) p = plan_layer(A, L, prec, Ranges::None);
+  if (plan_bytes(p) <= NOALLOC_BYTES) p.floats = (int64_t)((NOALLOC_BYTES - 256) / sizeof(float));   // all of it
+  return p;
+}
+
+LayerPlan plan_layer_bwd(const gcn_adj* A, const gcn_layer* L, int32_t prec) {
+  LayerPlan p = plan_layer(A, L, prec);
+  const LayerPlan q = plan_layer_fixed(A, L, prec);
+  if (plan_bytes(q) <= NOALLOC_BYTES) p.ranges = q.ranges;
+  return p;
 }
 
 Epilogue base_epi(void* out, int64_t ldo, int64_t rows, int64_t cols, int mode, int32_t* flag) {
@@ -205,10 +224,10 @@ hipError_t row_product(int32_t prec, const void* A, int64_t lda, const void* B, 
 // Y = epilogue(A_hat X).  For dense A_hat, colsum (may be NULL) receives the
 // column-sum partials of X computed during its transposition.
 hipError_t aggregate(const gcn_adj* A, int32_t prec, const void* X, int64_t ldx, int64_t F, const Epilogue& epi,
-                     float* ws, float* colsum, hipStream_t s, bool ranges = true) {
+                     float* ws, size_t ws_bytes, float* colsum, hipStream_t s, bool ranges = true) {
   if (A->format != GCN_CSR)
     return dense_agg_launch(prec, A->dense, A->ld_dense, A->format == GCN_DENSE_TILED, A->n, X, ldx, F, epi, ws,
-                            colsum, s, ranges);
+                            ws_bytes, colsum, s, ranges);
   return spmm_launch(view_of(A), prec, X, ldx, F, epi, ws, s);
 }
 
@@ -414,7 +433,7 @@ gcn_status gcn_layer_fwd(const gcn_adj* A, const gcn_layer* L, int32_t prec, int
 
   Epilogue ea = agg_epi(H_out, L->ld_out, n, L->f_out, bias, L->act, L->dropout_p, training, seed, L->layer_id,
                         epoch, overflow, L->epoch_from);
-  GCN_HIP(aggregate(A, prec, Sx, L->ld_out, L->f_out, ea, ws, nullptr, s, plan.ranges));
+  GCN_HIP(aggregate(A, prec, Sx, L->ld_out, L->f_out, ea, ws, plan_step_bytes(plan), nullptr, s));
   return finish(hipSuccess, s);
 }
 
@@ -471,7 +490,7 @@ gcn_status gcn_aggregate(const gcn_adj* A, int64_t F, int32_t prec, const void* 
     return GCN_ERR_WORKSPACE;
   if (workspace && !aligned16(workspace)) return GCN_ERR_ALIGNMENT;
   Epilogue ea = agg_epi(Y, ldy, A->n, F, bias, act, dropout_p, training, seed, layer_id, epoch, overflow);
-  GCN_HIP(aggregate(A, prec, X, ldx, F, ea, static_cast<float*>(workspace), nullptr, s));
+  GCN_HIP(aggregate(A, prec, X, ldx, F, ea, static_cast<float*>(workspace), workspace_bytes, nullptr, s));
   return finish(hipSuccess, s);
 }
 
@@ -518,7 +537,8 @@ gcn_status layer_bwd_run(const gcn_adj* A, const gcn_layer* L, int32_t prec, con
   // G_S = A_hat^T dZ = A_hat dZ (A_hat symmetric); for dense A_hat the
   // transposition of dZ also yields the column-sum partials for dbias
   Epilogue eg = base_epi(GS, L->ld_out, n, L->f_out, EPI_STORE, overflow);
-  GCN_HIP(aggregate(A, prec, dZ, L->ld_out, L->f_out, eg, ws, dbias && dense ? cs : nullptr, s, plan.ranges));
+  GCN_HIP(aggregate(A, prec, dZ, L->ld_out, L->f_out, eg, ws, plan_step_bytes(plan), dbias && dense ? cs : nullptr, s,
+                    plan.ranges));
   RedJob jb{};
   if (dbias) {
     Epilogue eb = base_epi(dbias, L->ld_out, 1, L->f_out, EPI_F32, overflow);
@@ -586,7 +606,7 @@ gcn_status gcn_layer_bwd(const gcn_adj* A, const gcn_layer* L, int32_t prec, con
   hipStream_t s = static_cast<hipStream_t>(stream);
   gcn_status st = layer_bwd_check(A, L, prec, H, W, dZ, act_below, p_below, dW, dbias, dZ_below, dbias_below, GS);
   if (st != GCN_OK) return st;
-  const LayerPlan plan = plan_layer(A, L, prec);
+  const LayerPlan plan = plan_layer_bwd(A, L, prec);
   if (!workspace || workspace_bytes < plan_bytes(plan)) return GCN_ERR_WORKSPACE;
   if (!aligned16(workspace)) return GCN_ERR_ALIGNMENT;
   return layer_bwd_run(A, L, prec, plan, H, W, dZ, act_below, p_below, dW, dbias, dZ_below, dbias_below, GS, overflow,
@@ -630,8 +650,8 @@ gcn_status gcn_layer_bwd_noalloc(const gcn_adj* A, const gcn_layer* L, int32_t p
   hipStream_t s = static_cast<hipStream_t>(stream);
   gcn_status st = layer_bwd_check(A, L, prec, H, W, dZ, act_below, p_below, dW, dbias, dZ_below, dbias_below, GS);
   if (st != GCN_OK) return st;
-  const LayerPlan plan = plan_layer(A, L, prec);
-  if (plan_bytes(plan) > (size_t)GCN_NOALLOC_SCRATCH_BYTES) return GCN_ERR_CAPACITY;
+  const LayerPlan plan = plan_layer_fixed(A, L, prec);
+  if (plan_bytes(plan) > NOALLOC_BYTES) return GCN_ERR_CAPACITY;
   void* scr = nullptr;
   st = scratch_of_current_device(&scr);
   if (st != GCN_OK) return st;
@@ -795,5 +815,9 @@ gcn_status gcn_pair_metrics(const float* scores, int64_t n_pos, int64_t n_neg, d
   GCN_HIP(pair_metrics_launch(scores, n_pos, n_neg, auc_ap, workspace, s));
   return finish(hipSuccess, s);
 }
+
+// Not part of the interface (gcn.h): for tests that have to know which kernel
+// a size takes.
+void gcn_internal_dense_plan(int32_t prec, int64_t n, int64_t F, int64_t* out) { dense_plan_query(prec, n, F, out); }
 
 }  // extern "C"

@@ -354,10 +354,10 @@ struct StreamParams {
   const void* Xt;     // tiled X^T
   int64_t n, F, nc;   // vertices, features, k chunks
   int64_t rblocks;    // 64-row blocks of A_hat
-  int64_t rowb;       // 128-row blocks
+  int64_t rb0, rowb;  // 128-row blocks of this launch: the first, how many
   int64_t ksplit;
-  float* part;        // ksplit > 1: fp32 partial products [ksplit][n][ldp]
-  int64_t ldp;
+  float* part;        // ksplit > 1: fp32 partial products [ksplit][prows][ldp] of the launch's rows
+  int64_t prows, ldp;
   Epilogue epi;
 };
 
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   __shared__ float red[2][16 * TM * LDR];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t rbk = blockIdx.x % p.rowb, split = blockIdx.x / p.rowb;   // k ranges outermost
+  const int64_t rbk = p.rb0 + blockIdx.x % p.rowb, split = blockIdx.x / p.rowb;   // k ranges outermost
   const int64_t blk = p.nc * 4 * PIECE;            // elements of one 64-row block
   const T* __restrict__ A = reinterpret_cast<const T*>(p.A);
   const T* __restrict__ Xt = reinterpret_cast<const T*>(p.Xt);
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int e = 0; e < OV; ++e) v[e] = red[0][r * LDR + cv * OV + e] + red[1][r * LDR + cv * OV + e];
     if (p.ksplit > 1) {
-      float4* o = reinterpret_cast<float4*>(p.part + (split * p.n + row) * p.ldp + col);
+      float4* o = reinterpret_cast<float4*>(p.part + (split * p.prows + row - p.rb0 * 128) * p.ldp + col);
 #pragma unroll
       for (int e = 0; e < OV / 4; ++e) o[e] = make_float4(v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]);
     } else {
@@ -512,9 +512,11 @@ struct MmParams {
   int64_t n, F, nc;   // vertices, features, k chunks
   int64_t rblocks;    // 64-row blocks of A_hat
   int64_t fblocks;    // 64-row blocks of X^T
+  int64_t tr0;        // first row of tiles of this launch
   int64_t tiles, cb, per_xcd;
   int64_t ksplit, kc; // k ranges of kc chunks (the last one shorter), one per workgroup of a tile
-  float* part;        // ksplit > 1: fp32 partial products [ksplit][n][ldp]
+  float* part;        // ksplit > 1: fp32 partial products [ksplit][prows][ldp] of the launch's rows
+  int64_t row0, prows;
   int64_t ldp;        // F rounded up to a whole output vector
   Epilogue epi;
 };
@@ -549,7 +551,7 @@ template <int W, int OV>
 __device__ __forceinline__ void mm_store_strip_part(const MmParams& p, const float* st, int lane, int64_t row0,
                                                     int64_t col0, int64_t split) {
   constexpr int VPR = W / OV;
-  float* part = p.part + split * p.n * p.ldp;
+  float* part = p.part + (split * p.prows - p.row0) * p.ldp;
 #pragma unroll 1
   for (int k = 0; k < 16 * VPR / 64; ++k) {
     const int idx = k * 64 + lane;
@@ -565,10 +567,11 @@ __device__ __forceinline__ void mm_store_strip_part(const MmParams& p, const flo
 }
 
 // Sum of the k ranges' partials in range order, one output vector per
-// thread, through the vector epilogue (one Philox block per 8 outputs).
+// thread, through the vector epilogue (one Philox block per 8 outputs); the
+// partials are those of rows row0 .. row0 + n - 1.
 template <typename T>
-__global__ __launch_bounds__(256) void mm_reduce_kernel(const float* __restrict__ part, int64_t ksplit, int64_t n,
-                                                        int64_t F, int64_t ldp, Epilogue epi) {
+__global__ __launch_bounds__(256) void mm_reduce_kernel(const float* __restrict__ part, int64_t ksplit, int64_t row0,
+                                                        int64_t n, int64_t ldp, Epilogue epi) {
   constexpr int VE = Vec<T>::N;
   const int64_t vpr = ldp / VE;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -585,7 +588,7 @@ __global__ __launch_bounds__(256) void mm_reduce_kernel(const float* __restrict_
       acc[4 * e] += v.x; acc[4 * e + 1] += v.y; acc[4 * e + 2] += v.z; acc[4 * e + 3] += v.w;
     }
   }
-  epi_store_vec<T>(epi, row, col0, acc);
+  epi_store_vec<T>(epi, row0 + row, col0, acc);
 }
 
 // 1 KiB from global memory straight into LDS (64 lanes x 16 bytes, lane order
@@ -616,7 +619,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if (u >= p.tiles * p.ksplit) return;
   const int64_t split = u / p.tiles;
   const int64_t t = u - split * p.tiles;
-  const int64_t tr = t / p.cb, tc = t - (t / p.cb) * p.cb;
+  const int64_t tr = p.tr0 + t / p.cb, tc = t - (t / p.cb) * p.cb;
   const int64_t c_lo = split * p.kc;                  // this workgroup's k chunks: [c_lo, c_lo + nc)
   const int nc = (int)(min(p.nc, c_lo + p.kc) - c_lo);
   const int64_t blk = p.nc * 4 * PIECE;               // elements of one 64-row block
@@ -791,20 +794,29 @@ constexpr MmTile MM_TILES[] = {
 };
 constexpr double NEAR_BYTES = 2e8;
 
+double price_rounds(int64_t units) { return (double)((units + 255) / 256); }
+
+// `rows` rows of the product through tile t, S ranges of kc chunks (us).
+double mm_price(int prec, int64_t n, int64_t rows, int64_t F, const MmTile& t, int64_t S, int64_t kc) {
+  const int64_t ct = (F + t.cols - 1) / t.cols, tiles = (rows + t.rows - 1) / t.rows * ct;
+  const bool near = (double)n * (double)n * (prec == 0 ? 4 : 2) <= NEAR_BYTES;
+  const double chunk = prec == 0 ? std::max(t.w32, t.h / ct) : near ? t.near : std::max(t.far + t.s / ct, t.h / ct);
+  return price_rounds(tiles * S) * (kc * chunk + t.fixed) + (S > 1 ? 6.0 + 8.0 * S * (double)rows * F / 9e6 : 0.0);
+}
+
 DensePlan dense_plan(int prec, int64_t n, int64_t F, bool tiled, bool split) {
   const int64_t nc = (n + (prec == 0 ? 15 : 31)) / (prec == 0 ? 16 : 32);
   DensePlan pl{DK_ROWS64, 0, 1, nc};
   if (!tiled) return pl;
   const double es = prec == 0 ? 4 : 2, dn = (double)n;
   const double cu_bytes = 4.8e4, chip = dn * dn * es / 6.8e6;                      // per us
-  auto rounds = [](int64_t units) { return (double)((units + 255) / 256); };
   auto unit = [&](double rows, double cols, double cu_flops) {
     return std::max((rows + cols) * dn * es / cu_bytes, 2 * rows * dn * cols / cu_flops);
   };
   const int64_t cb64 = (F + 63) / 64, ldp = (F + 7) / 8 * 8;
   const double cols = F > 64 ? 64.0 : 16.0 * ((F + 15) / 16);
   const double ends = F <= 64 ? 0.0 : prec == 0 ? 7.0 : 4.0;
-  double best = 0.93 * std::max(rounds((n + 63) / 64 * cb64) * (unit(64, cols, prec == 0 ? 4.8e5 : 4.8e6) + ends), chip * cb64);
+  double best = 0.93 * std::max(price_rounds((n + 63) / 64 * cb64) * (unit(64, cols, prec == 0 ? 4.8e5 : 4.8e6) + ends), chip * cb64);
   if (best < 8.0) return pl;                            // less than any other candidate's start and end
   auto offer = [&](double t, DenseKind kind, int tile, int64_t S, int64_t kc) {
     if (t < best) { best = t; pl = DensePlan{kind, tile, S, kc}; }
@@ -813,25 +825,60 @@ DensePlan dense_plan(int prec, int64_t n, int64_t F, bool tiled, bool split) {
     const int64_t blocks = (n + 127) / 128;
     for (int64_t S = 1; S <= DP_MAX_SPLIT; ++S) {
       if (S > 1 && (!split || nc < 8 * S || S * n * ldp * 4 > ST_PART_BYTES)) break;
-      offer(std::max(rounds(blocks * S) * (unit(128, cols, prec == 0 ? 5.1e5 : 5.1e6) / S + 4.0), chip) +
+      offer(std::max(price_rounds(blocks * S) * (unit(128, cols, prec == 0 ? 5.1e5 : 5.1e6) / S + 4.0), chip) +
                 (S > 1 ? 7.0 + 8.0 * S * dn * F / 3e6 : 0.0),
             DK_STREAM, 0, S, 0);
     }
     return pl;
   }
   for (int i = 0; nc >= 8 && i < 4; ++i) {
-    const MmTile& t = MM_TILES[i];
-    const int64_t ct = (F + t.cols - 1) / t.cols, tiles = (n + t.rows - 1) / t.rows * ct;
-    const double chunk = prec == 0 ? std::max(t.w32, t.h / ct)
-                         : dn * dn * es <= NEAR_BYTES ? t.near : std::max(t.far + t.s / ct, t.h / ct);
     for (int64_t S = 1; S <= DP_MAX_SPLIT; ++S) {
       const int64_t kc = (nc + S - 1) / S;
       if (S > 1 && (!split || kc < 8 || S * n * ldp * 4 > DP_PART_BYTES)) break;
       if (nc - (S - 1) * kc < 8) continue;
-      offer(rounds(tiles * S) * (kc * chunk + t.fixed) + (S > 1 ? 6.0 + 8.0 * S * dn * F / 9e6 : 0.0), DK_MM, i, S, kc);
+      offer(mm_price(prec, n, n, F, MM_TILES[i], S, kc), DK_MM, i, S, kc);
     }
   }
   return pl;
+}
+
+// With less scratch than the partials of all rows need, the product takes its
+// rows in several launches, each followed by its reduction.  The k ranges stay
+// and with them every bit: the order in which an output is summed depends on the
+// ranges, not on the tile that holds it, so each launch takes the tile that is
+// cheapest for its rows.  (All rows with one tile left compute units idle: n =
+// 16384, F = 512, 16-bit, two ranges through the 64 MiB of
+// gcn_layer_bwd_noalloc 400 us, 313 with the rows and tiles priced.)
+size_t dense_part_bytes(const DensePlan& pl, int64_t rows, int64_t F) {
+  return pl.ksplit > 1 ? (size_t)pl.ksplit * (size_t)rows * (size_t)((F + 7) / 8 * 8) * sizeof(float) : 0;
+}
+int64_t dense_row_step(const DensePlan& pl) { return pl.kind == DK_MM ? 256 : 128; }   // whole tiles, whichever
+
+int cheapest_tile(int prec, const DensePlan& pl, int64_t n, int64_t rows, int64_t F, double* price) {
+  int best = pl.tile;
+  *price = mm_price(prec, n, rows, F, MM_TILES[best], pl.ksplit, pl.kc);
+  for (int i = 0; i < 4; ++i) {
+    const double t = mm_price(prec, n, rows, F, MM_TILES[i], pl.ksplit, pl.kc);
+    if (t < *price) { *price = t; best = i; }
+  }
+  return best;
+}
+
+// Rows of a launch (the last one takes the rest): all where their partials fit.
+int64_t dense_rows_per_launch(int prec, const DensePlan& pl, int64_t n, int64_t F, size_t part_bytes) {
+  if (part_bytes >= dense_part_bytes(pl, n, F)) return n;
+  const int64_t step = dense_row_step(pl), most = (int64_t)(part_bytes / dense_part_bytes(pl, 1, F)) / step * step;
+  if (pl.kind != DK_MM) return most;
+  int64_t best = most;
+  double best_t = 0.0;
+  for (int64_t per = most; per > most / 2; per -= step) {
+    double whole, last = 0.0;
+    cheapest_tile(prec, pl, n, per, F, &whole);
+    if (n % per) cheapest_tile(prec, pl, n, n % per, F, &last);
+    const double t = (double)(n / per) * whole + last;
+    if (per == most || t < best_t) { best_t = t; best = per; }
+  }
+  return best;
 }
 
 template <typename T, int TN, int DEPTH>
@@ -839,33 +886,26 @@ void stream_launch(const StreamParams& q, hipStream_t s) {
   hipLaunchKernelGGL((dense_stream_kernel<T, TN, DEPTH>), dim3((unsigned)(q.rowb * q.ksplit)), dim3(256), 0, s, q);
 }
 
+// Rows row0 .. row0 + rows - 1: row0 a multiple of dense_row_step, rows too
+// except for the last ones of the product.
 template <typename T>
-hipError_t launch_t(const void* A, int64_t lda, bool tiled, int64_t n, const void* X, int64_t ldx, int64_t F,
-                    const Epilogue& epi, void* ws, float* colsum, bool split, hipStream_t s) {
-  constexpr int KC = tile_kc<T>();
-  const int64_t nc = (n + KC - 1) / KC;
-  const int64_t fblocks = (F + 63) / 64;
-  T* Xt = reinterpret_cast<T*>(ws);
-  dim3 tg((unsigned)((nc * KC + XpGeom<T>::WG_K - 1) / XpGeom<T>::WG_K), (unsigned)fblocks);
-  hipLaunchKernelGGL(transpose_tiled_kernel<T>, tg, dim3(256), 0, s, reinterpret_cast<const T*>(X), ldx, n, F, Xt, nc,
-                     colsum);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const DensePlan pl = dense_plan(sizeof(T) == 4 ? 0 : 1, n, F, tiled, split);
+hipError_t launch_rows(const DensePlan& pl, const void* A, int64_t n, const T* Xt, int64_t F, int64_t nc, int64_t row0,
+                       int64_t rows, const Epilogue& epi, float* part, hipStream_t s) {
   const int64_t ldp = (F + Vec<T>::N - 1) / Vec<T>::N * Vec<T>::N;
-  float* part = pl.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + xt_bytes(sizeof(T) == 4 ? 0 : 1, n, F))
-                              : nullptr;
+  const int64_t step = pl.kind == DK_MM ? MM_TILES[pl.tile].rows : 128, steps = (rows + step - 1) / step;
   if (pl.kind == DK_MM) {
-    const MmTile& t = MM_TILES[pl.tile];
     MmParams q;
     q.A = A; q.Xt = Xt; q.n = n; q.F = F; q.nc = nc;
     q.rblocks = (n + 63) / 64;
-    q.fblocks = fblocks;
-    q.cb = (F + t.cols - 1) / t.cols;
-    q.tiles = (n + t.rows - 1) / t.rows * q.cb;
+    q.fblocks = (F + 63) / 64;
+    q.tr0 = row0 / step;
+    q.cb = (F + MM_TILES[pl.tile].cols - 1) / MM_TILES[pl.tile].cols;
+    q.tiles = steps * q.cb;
     q.ksplit = pl.ksplit;
     q.kc = pl.kc;
     q.part = part;
+    q.row0 = row0;
+    q.prows = rows;
     q.ldp = ldp;
     q.per_xcd = (q.tiles * q.ksplit + 7) / 8;
     q.epi = epi;
@@ -876,14 +916,16 @@ hipError_t launch_t(const void* A, int64_t lda, bool tiled, int64_t n, const voi
       case 2: hipLaunchKernelGGL((dense_mm_kernel<T, 8, 4, 6>), g, dim3(256), 0, s, q); break;
       default: hipLaunchKernelGGL((dense_mm_kernel<T, 4, 4, 8>), g, dim3(256), 0, s, q); break;
     }
-  } else if (pl.kind == DK_STREAM) {
+  } else {
     StreamParams q;
     q.A = A; q.Xt = Xt; q.n = n; q.F = F; q.nc = nc;
     q.rblocks = (n + 63) / 64;
-    q.rowb = (n + 127) / 128;
+    q.rb0 = row0 / step;
+    q.rowb = steps;
     q.ksplit = pl.ksplit;
-    q.ldp = ldp;
     q.part = part;
+    q.prows = rows;
+    q.ldp = ldp;
     q.epi = epi;
     switch ((F + 15) / 16) {
       case 1: stream_launch<T, 1, 8>(q, s); break;
@@ -892,14 +934,42 @@ hipError_t launch_t(const void* A, int64_t lda, bool tiled, int64_t n, const voi
       default: stream_launch<T, 4, 6>(q, s); break;
     }
   }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || pl.ksplit == 1) return e;
+  // the k ranges' partials, added in range order, through the epilogue
+  const int64_t vecs = rows * (ldp / Vec<T>::N);
+  hipLaunchKernelGGL(mm_reduce_kernel<T>, dim3((unsigned)((vecs + 255) / 256)), dim3(256), 0, s, part, pl.ksplit, row0,
+                     rows, ldp, epi);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_t(const void* A, int64_t lda, bool tiled, int64_t n, const void* X, int64_t ldx, int64_t F,
+                    const Epilogue& epi, void* ws, size_t ws_bytes, float* colsum, bool split, hipStream_t s) {
+  constexpr int KC = tile_kc<T>();
+  constexpr int PREC = sizeof(T) == 4 ? 0 : 1;
+  const int64_t nc = (n + KC - 1) / KC;
+  const int64_t fblocks = (F + 63) / 64;
+  DensePlan pl = dense_plan(PREC, n, F, tiled, split);
+  const size_t xb = xt_bytes(PREC, n, F);
+  const int64_t per = ws_bytes < xb ? 0 : dense_rows_per_launch(PREC, pl, n, F, ws_bytes - xb);
+  if (per <= 0) return hipErrorInvalidValue;
+  T* Xt = reinterpret_cast<T*>(ws);
+  dim3 tg((unsigned)((nc * KC + XpGeom<T>::WG_K - 1) / XpGeom<T>::WG_K), (unsigned)fblocks);
+  hipLaunchKernelGGL(transpose_tiled_kernel<T>, tg, dim3(256), 0, s, reinterpret_cast<const T*>(X), ldx, n, F, Xt, nc,
+                     colsum);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   if (pl.kind != DK_ROWS64) {
-    e = hipGetLastError();
-    if (e != hipSuccess || pl.ksplit == 1) return e;
-    // the k ranges' partials, added in range order, through the epilogue
-    const int64_t vecs = n * (ldp / Vec<T>::N);
-    hipLaunchKernelGGL(mm_reduce_kernel<T>, dim3((unsigned)((vecs + 255) / 256)), dim3(256), 0, s, part, pl.ksplit,
-                       n, F, ldp, epi);
-    return hipGetLastError();
+    float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + xb);
+    for (int64_t r = 0; r < n; r += per) {
+      const int64_t rows = std::min(per, n - r);
+      double price;
+      if (per < n && pl.kind == DK_MM) pl.tile = cheapest_tile(PREC, pl, n, rows, F, &price);
+      e = launch_rows<T>(pl, A, n, Xt, F, nc, r, rows, epi, part, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
   DaParams p;
   p.A = A; p.lda = lda; p.Xt = Xt; p.ldt = 0; p.n = n; p.F = F; p.epi = epi;
@@ -961,9 +1031,22 @@ hipError_t densify_t(const CsrView& A, bool tiled, void* dense, int64_t ld, hipS
 }  // namespace
 
 size_t dense_agg_workspace_bytes(int prec, int64_t n, int64_t F, bool tiled, bool split) {
-  const DensePlan pl = dense_plan(prec, n, F, tiled, split);
-  return xt_bytes(prec, n, F) +
-         (pl.ksplit > 1 ? (size_t)pl.ksplit * (size_t)n * (size_t)((F + 7) / 8 * 8) * sizeof(float) : 0);
+  return xt_bytes(prec, n, F) + dense_part_bytes(dense_plan(prec, n, F, tiled, split), n, F);
+}
+
+size_t dense_agg_min_bytes(int prec, int64_t n, int64_t F, bool tiled) {
+  const DensePlan pl = dense_plan(prec, n, F, tiled, true);
+  return xt_bytes(prec, n, F) + dense_part_bytes(pl, std::min(n, dense_row_step(pl)), F);
+}
+
+void dense_plan_query(int prec, int64_t n, int64_t F, int64_t out[5]) {
+  const DensePlan pl = dense_plan(prec, n, F, true, true);
+  const bool mm = pl.kind == DK_MM;
+  out[0] = pl.kind;
+  out[1] = mm ? MM_TILES[pl.tile].rows : pl.kind == DK_STREAM ? 128 : 64;
+  out[2] = mm ? MM_TILES[pl.tile].cols : 64;
+  out[3] = pl.ksplit;
+  out[4] = mm ? pl.kc : (n + (prec == 0 ? 15 : 31)) / (prec == 0 ? 16 : 32);
 }
 
 int64_t dense_tiled_elems(int prec, int64_t n) {
@@ -972,11 +1055,12 @@ int64_t dense_tiled_elems(int prec, int64_t n) {
 }
 
 hipError_t dense_agg_launch(int prec, const void* A, int64_t lda, bool tiled, int64_t n, const void* X, int64_t ldx,
-                            int64_t F, const Epilogue& epi, void* ws, float* colsum, hipStream_t s, bool split) {
+                            int64_t F, const Epilogue& epi, void* ws, size_t ws_bytes, float* colsum, hipStream_t s,
+                            bool split) {
   switch (prec) {
-    case 0: return launch_t<float>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, split, s);
-    case 1: return launch_t<f16>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, split, s);
-    case 2: return launch_t<bf16>(A, lda, tiled, n, X, ldx, F, epi, ws, colsum, split, s);
+    case 0: return launch_t<float>(A, lda, tiled, n, X, ldx, F, epi, ws, ws_bytes, colsum, split, s);
+    case 1: return launch_t<f16>(A, lda, tiled, n, X, ldx, F, epi, ws, ws_bytes, colsum, split, s);
+    case 2: return launch_t<bf16>(A, lda, tiled, n, X, ldx, F, epi, ws, ws_bytes, colsum, split, s);
   }
   return hipErrorInvalidValue;
 }

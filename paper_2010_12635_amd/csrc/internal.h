@@ -124,14 +124,21 @@ hipError_t wgrad_launch(int prec, const void* H, int64_t ldh, const void* G, int
 
 // ------------------------------------------------ dense-A_hat aggregation ----
 // Y = epilogue(A_hat X) for dense A_hat (n x lda); ws holds the padded
-// transpose of X and, for the wide kernel with k ranges, their fp32
-// partials (dense_agg_workspace_bytes).  With colsum != NULL the
+// transpose of X and, where the k range is cut, the ranges' fp32 partials:
+// dense_agg_workspace_bytes() for all rows at once; with less, down to
+// dense_agg_min_bytes(), the rows are taken in several launches, with the same
+// bits.  split = false forbids cutting the k range.  With colsum != NULL the
 // transposition also writes column-sum partials of X, [rows][F] floats with
 // rows = dense_agg_colsum_rows(); reduce with make_job(colsum, rows, 1, F, ..).
 size_t dense_agg_workspace_bytes(int prec, int64_t n, int64_t F, bool tiled, bool split = true);
+size_t dense_agg_min_bytes(int prec, int64_t n, int64_t F, bool tiled);
 int64_t dense_agg_colsum_rows(int prec, int64_t n);
 hipError_t dense_agg_launch(int prec, const void* A, int64_t lda, bool tiled, int64_t n, const void* X, int64_t ldx,
-                            int64_t F, const Epilogue& epi, void* ws, float* colsum, hipStream_t s, bool split = true);
+                            int64_t F, const Epilogue& epi, void* ws, size_t ws_bytes, float* colsum, hipStream_t s,
+                            bool split = true);
+// How the tiled product is cut: kernel (0: 64-row blocks, 1: streaming, 2: MFMA
+// tiles), rows and columns of a workgroup, k ranges, chunks of the longest one.
+void dense_plan_query(int prec, int64_t n, int64_t F, int64_t out[5]);
 // Elements of the tiled dense A_hat (rows padded to 64, columns to the chunk).
 int64_t dense_tiled_elems(int prec, int64_t n);
 // Dense A_hat from CSR: row-major (ld) or tiled operand order.

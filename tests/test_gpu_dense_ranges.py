@@ -3,9 +3,10 @@ ranges end, ragged n and F, in every storage type, against float64 on the
 stored values: F <= 64 with 64-row blocks alone and 128-row blocks with one and
 with several k ranges (fewer row blocks than compute units, or a last round of
 them nearly empty); wider F with each tile of the matrix-core kernel, whole
-and cut k ranges, odd and even chunk counts; and the workspace rule of the k
-ranges."""
-import numpy as np
+and cut k ranges, odd and even chunk counts; and the k ranges of whole layers,
+with a workspace and in the fixed scratch."""
+import ctypes
+
 import pytest
 import torch
 
@@ -74,20 +75,117 @@ def test_tiled_aggregation(prec, n, F):
     assert bool(fin[:, :F - 1].all()) and not bool(fin[A[:, n - 1] > 0, F - 1].any()) and flag.item() == 1
 
 
-def test_ranges_keep_a_layer_inside_the_fixed_scratch():
-    """A dense layer that fits the scratch of gcn_layer_bwd_noalloc without
-    the partials of the k ranges still fits: it goes without them."""
+def plan(prec, n, F):
+    """(kernel, rows, columns, k ranges, chunks of the longest range) of a tiled product."""
+    out = (ctypes.c_int64 * 5)()
+    G.lib().gcn_internal_dense_plan(ctypes.c_int32(prec), ctypes.c_int64(n), ctypes.c_int64(F), out)
+    return tuple(out)
+
+
+def _adj(n, prec, dense):
     a = G.GcnAdj()
-    n = 35000
-    a.n, a.nnz, a.format, a.value_prec = n, 0, G.GCN_DENSE_TILED, G.GCN_F16
-    a.dense = 4096                                   # never read
+    a.n, a.nnz, a.format, a.value_prec, a.dense = n, 0, G.GCN_DENSE_TILED, prec, dense
+    return a
 
-    def size(f_in):
-        return G.gcn_layer_workspace_size(a, G.GcnLayer(f_in, 64, f_in, 64, G.GCN_ACT_NONE, 0.0, 0, 0), G.GCN_F16)
 
+def _layer(f_in, f_out):
+    return G.GcnLayer(f_in, f_out, (f_in + 7) // 8 * 8, (f_out + 7) // 8 * 8, G.GCN_ACT_NONE, 0.0, 0, 0)
+
+
+# partials of 23 to 88 MB: with the transposed columns more than
+# GCN_NOALLOC_SCRATCH_BYTES in all but the first two
+LAYERS = [(1, 6001, 16, 64), (2, 12000, 40, 256), (1, 12000, 24, 384), (2, 16384, 16, 512), (1, 20000, 16, 256),
+          (0, 20000, 16, 128)]
+
+
+@pytest.mark.parametrize("prec,n,f_in,f_out", LAYERS)
+def test_layer_workspace_holds_every_range(prec, n, f_in, f_out):
+    """A layer call cuts the k range as gcn_aggregate does: its workspace has
+    room for the transposed columns and the partials of all ranges."""
+    ranges = plan(prec, n, f_out)[3]
+    assert ranges > 1
+    size = G.gcn_layer_workspace_size(_adj(n, prec, 4096), _layer(f_in, f_out), prec)   # never read
+    assert size >= n * f_out * (4 if prec == 0 else 2) + ranges * n * f_out * 4
+
+
+def _operands(prec, n, f_in, f_out):
+    dt = G.torch_dtype(prec)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + f_out)
+    At = tile(torch.rand((n, n), generator=gen, device="cuda").to(dt), prec)
+    H = torch.relu(torch.randn((n, f_in), generator=gen, device="cuda")).to(dt)
+    W = torch.randn((f_in, f_out), generator=gen, device="cuda").to(dt)
+    dZ = torch.randn((n, f_out), generator=gen, device="cuda").to(dt)
+    return _adj(n, prec, At.data_ptr()), At, H, W, dZ
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,n,f_in,f_out", LAYERS)
+def test_layer_forward_is_transform_and_aggregate(prec, n, f_in, f_out):
+    a, At, H, W, X = _operands(prec, n, f_in, f_out)
+    L = _layer(f_in, f_out)
+    ov = torch.zeros(1, dtype=torch.int32, device="cuda")
+    S, Y, S2, Y2 = (torch.empty_like(X) for _ in range(4))
+    ws = torch.empty(G.gcn_layer_workspace_size(a, L, prec), dtype=torch.uint8, device="cuda")
+    G.gcn_layer_fwd(a, L, prec, False, H, W, None, 0, 0, S, Y, ov, ws)
+    wt = torch.empty(G.gcn_transform_workspace_size(n, f_in, f_out, prec), dtype=torch.uint8, device="cuda")
+    G.gcn_transform(n, f_in, f_out, prec, H, f_in, W, f_out, S2, f_out, ov, wt)
+    wa = torch.empty(G.gcn_aggregate_workspace_size(a, f_out, prec), dtype=torch.uint8, device="cuda")
+    G.gcn_aggregate(a, f_out, prec, S2, f_out, None, G.GCN_ACT_NONE, 0.0, False, 0, 0, 0, Y2, f_out, ov, wa)
+    assert torch.equal(S, S2) and torch.equal(Y, Y2)
+
+
+def _noalloc_against_workspace(prec, n, f_in, f_out):
+    a, At, H, W, dZ = _operands(prec, n, f_in, f_out)
+    L = _layer(f_in, f_out)
+    ws = torch.empty(G.gcn_layer_workspace_size(a, L, prec), dtype=torch.uint8, device="cuda")
+    res = []
+    for call in ("workspace", "noalloc"):
+        dW, db = (torch.full(s, 7.0, device="cuda") for s in ((f_in, f_out), (f_out,)))
+        dZb, GS = torch.empty_like(H), torch.empty_like(dZ)
+        ov = torch.zeros(1, dtype=torch.int32, device="cuda")
+        if call == "workspace":
+            G.gcn_layer_bwd(a, L, prec, H, W, dZ, G.GCN_ACT_RELU, 0.5, dW, db, dZb, GS, ov, ws)
+        else:
+            G.gcn_layer_bwd_noalloc(a, L, prec, H, W, dZ, G.GCN_ACT_RELU, 0.5, dW, db, dZb, GS, ov)
+        res.append((dW, db, dZb, GS, ov))
+    torch.cuda.synchronize()
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,n,f_in,f_out", LAYERS)
+def test_noalloc_takes_the_rows_in_several_launches(prec, n, f_in, f_out):
+    """Less scratch than the partials of all rows: the same bits."""
+    _noalloc_against_workspace(prec, n, f_in, f_out)
+
+
+@pytest.mark.gpu
+def test_noalloc_where_the_scratch_ends():
+    """The column sums of dZ_below (512 floats per feature) leave less and less
+    of the fixed scratch: room for the partials of some rows, of one row of
+    tiles, of none (then neither call cuts the k range), and no room at all."""
+    prec, n, f_out = 0, 30000, 160
+    ranges = plan(prec, n, f_out)[3]
+    assert ranges > 1
+    everything, least = ranges * n * f_out * 4, ranges * 256 * f_out * 4
     limit = G.NOALLOC_SCRATCH_BYTES
-    assert size(16) >= n * 64 * 2 + 2 * n * 64 * 4   # X^T and the partials of two ranges
-    # the column sums of dZ_below grow by 512 floats per feature; past the
-    # limit the partials go, and the layer needs less than a narrower one
-    assert size(20800) < size(20000) <= limit
-    assert size(40000) > limit                       # does not fit either way
+
+    def without(f_in):
+        return G.gcn_layer_workspace_size(_adj(n, prec, 4096), _layer(f_in, f_out), prec) - everything
+
+    def last(bytes_left):
+        lo, hi = 8, 1 << 17                          # widest f_in that leaves so much
+        while hi - lo > 8:
+            mid = (lo + hi) // 16 * 8
+            lo, hi = (mid, hi) if without(mid) + bytes_left <= limit else (lo, mid)
+        return lo
+
+    some, one, none = last(everything // 2), last(least), last(0)
+    assert some < one < none
+    for f_in in (some, one, none):
+        _noalloc_against_workspace(prec, n, f_in, f_out)
+    with pytest.raises(G.GcnError) as e:
+        _noalloc_against_workspace(prec, n, none + 8, f_out)
+    assert e.value.status == 5                       # GCN_ERR_CAPACITY
