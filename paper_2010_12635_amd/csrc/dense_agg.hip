@@ -515,6 +515,7 @@ struct MmParams {
   int64_t tr0;        // first row of tiles of this launch
   int64_t tiles, cb, per_xcd;
   int64_t ksplit, kc; // k ranges of kc chunks (the last one shorter), one per workgroup of a tile
+  int chain;          // CHAINS: chunks (even) added to an accumulator before it is added to the sums
   float* part;        // ksplit > 1: fp32 partial products [ksplit][prows][ldp] of the launch's rows
   int64_t row0, prows;
   int64_t ldp;        // F rounded up to a whole output vector
@@ -600,8 +601,11 @@ __device__ __forceinline__ void dma_1k(const void* base, uint32_t voff, uint32_t
 }
 
 // A wave owns TM x TN 16 x 16 tiles, the workgroup's 2 x 2 waves (32 TM) x
-// (32 TN) of the output; S stages of one k chunk each in the LDS ring.
-template <typename T, int TM, int TN, int S>
+// (32 TN) of the output; S stages of one k chunk each in the LDS ring.  CHAINS:
+// after every p.chain chunks the accumulators are added to a second set of sums,
+// so that no addition meets more roundings than that (rule at dense_plan; at
+// most 128 accumulators per lane leave registers for it).
+template <typename T, int TM, int TN, int S, bool CHAINS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void dense_mm_kernel(MmParams p) {
   constexpr int VE = Vec<T>::N, KC = 4 * VE, PIECE = 16 * KC;
   constexpr int RB = TM / 2, CB = TN / 2;          // 64-row blocks of A_hat and of X^T per workgroup
@@ -683,6 +687,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
   };
   auto next = [&](int s) { return s + 1 < S ? s + 1 : 0; };
+  f32x4 sum[CHAINS ? TM : 1][CHAINS ? TN : 1];
+  int left = p.chain;
+  if constexpr (CHAINS) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 #pragma unroll
   for (int d = 0; d < S; ++d)
 #pragma unroll
@@ -714,7 +726,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     step(f1, f0, c + 1, s1, s2);
     s0 = s2;
     c += 2;
+    if constexpr (CHAINS) {
+      left -= 2;
+      if (left <= 0) {
+        left = p.chain;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            sum[i][j] += acc[i][j];
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+      }
+    }
   } while (c < nc);
+  if constexpr (CHAINS) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += sum[i][j];
+  }
   MM_LANDED(0);                                    // the ring becomes the epilogue's staging area
 #undef MM_FENCE
 #undef MM_LANDED
@@ -769,7 +800,19 @@ size_t xt_bytes(int prec, int64_t n, int64_t F) {
 //    flight come from HBM; fp32: `w32`, the matrix instructions;
 //  * a round costs its start and end (`fixed`; 4 to 7 us for 64-row blocks of several column blocks),
 //    k ranges the reduction launch and the partials' traffic; they are bounded
-//    by DP_MAX_SPLIT, eight chunks each and the bytes of the partials.
+//    by DP_MAX_SPLIT, eight chunks each and the bytes of the partials;
+//  * fp32 results show the rounding of the additions, and the more chains an
+//    output is summed in the smaller it is (16-bit results do not show it:
+//    2.078e-4 with one chain or eight).  The prices know nothing of it, so fp32
+//    keeps to eight chains below F = 192, as the eight waves of the 64-row
+//    blocks sum them, and above to as many, up to eight, as tiles of 128 x 128
+//    need to fill the compute units; the streaming kernel's four waves take two
+//    ranges at least.
+//    They are ranges, or, up to 256 x 128, chains within a range, which cost
+//    2 % of the time; a wider tile takes the ranges whatever their bytes.
+//    Relative error on a full A_hat, one chain per range -> now: n = 8192 F =
+//    128 8.1e-7 -> 5.8e-7 in 0.16 ms, n = 24000 F = 160 1.24e-6 -> 9.8e-7, 1.66
+//    -> 1.58 ms, n = 12000 F = 190 8.8e-7 -> 6.2e-7, 0.44 -> 0.46 ms.
 // One call with the transposition (us, before -> with the LDS ring of
 // dense_mm_kernel, dense_stream_kernel and this rule), 16-bit: n = 16384 F =
 // 128 191 -> 124, F = 384 357 -> 190; n = 8192 F = 512 90 -> 64; n = 24000 F =
@@ -784,7 +827,9 @@ struct DensePlan {
   DenseKind kind;
   int tile;             // DK_MM: index of MM_TILES
   int64_t ksplit, kc;   // k ranges, chunks per range
+  int chain;            // DK_MM: chunks of a chain (0: one chain per range)
 };
+constexpr int MM_CHAIN_TILE = 2;   // the first of MM_TILES whose waves have registers for chains
 struct MmTile { int rows, cols; double near, far, s, h, w32, fixed; };
 constexpr MmTile MM_TILES[] = {
     {256, 256, 0.56, 0.55, 0.12, 0.80, 3.55, 9.0},
@@ -806,7 +851,7 @@ double mm_price(int prec, int64_t n, int64_t rows, int64_t F, const MmTile& t, i
 
 DensePlan dense_plan(int prec, int64_t n, int64_t F, bool tiled, bool split) {
   const int64_t nc = (n + (prec == 0 ? 15 : 31)) / (prec == 0 ? 16 : 32);
-  DensePlan pl{DK_ROWS64, 0, 1, nc};
+  DensePlan pl{DK_ROWS64, 0, 1, nc, 0};
   if (!tiled) return pl;
   const double es = prec == 0 ? 4 : 2, dn = (double)n;
   const double cu_bytes = 4.8e4, chip = dn * dn * es / 6.8e6;                      // per us
@@ -818,25 +863,33 @@ DensePlan dense_plan(int prec, int64_t n, int64_t F, bool tiled, bool split) {
   const double ends = F <= 64 ? 0.0 : prec == 0 ? 7.0 : 4.0;
   double best = 0.93 * std::max(price_rounds((n + 63) / 64 * cb64) * (unit(64, cols, prec == 0 ? 4.8e5 : 4.8e6) + ends), chip * cb64);
   if (best < 8.0) return pl;                            // less than any other candidate's start and end
-  auto offer = [&](double t, DenseKind kind, int tile, int64_t S, int64_t kc) {
-    if (t < best) { best = t; pl = DensePlan{kind, tile, S, kc}; }
+  auto offer = [&](double t, DenseKind kind, int tile, int64_t S, int64_t kc, int chain) {
+    if (t < best) { best = t; pl = DensePlan{kind, tile, S, kc, chain}; }
   };
   if (F <= 64) {
-    const int64_t blocks = (n + 127) / 128;
+    const int64_t blocks = (n + 127) / 128, least = prec == 0 ? 2 : 1;   // 4 waves: 8 chains
     for (int64_t S = 1; S <= DP_MAX_SPLIT; ++S) {
-      if (S > 1 && (!split || nc < 8 * S || S * n * ldp * 4 > ST_PART_BYTES)) break;
+      if (S > 1 && (!split || nc < 8 * S || (S > least && S * n * ldp * 4 > ST_PART_BYTES))) break;
+      if (S < least) continue;
       offer(std::max(price_rounds(blocks * S) * (unit(128, cols, prec == 0 ? 5.1e5 : 5.1e6) / S + 4.0), chip) +
                 (S > 1 ? 7.0 + 8.0 * S * dn * F / 3e6 : 0.0),
-            DK_STREAM, 0, S, 0);
+            DK_STREAM, 0, S, 0, 0);
     }
     return pl;
   }
+  int64_t need = 1;                                    // fp32: chains of additions per output
+  if (prec == 0) {
+    const int64_t few = (n + 127) / 128 * ((F + 127) / 128);
+    while (need < 8 && (F < 192 || few * need < 256) && nc >= 12 * need) need *= 2;
+  }
   for (int i = 0; nc >= 8 && i < 4; ++i) {
+    const bool chains = i >= MM_CHAIN_TILE;
     for (int64_t S = 1; S <= DP_MAX_SPLIT; ++S) {
       const int64_t kc = (nc + S - 1) / S;
-      if (S > 1 && (!split || kc < 8 || S * n * ldp * 4 > DP_PART_BYTES)) break;
-      if (nc - (S - 1) * kc < 8) continue;
-      offer(mm_price(prec, n, n, F, MM_TILES[i], S, kc), DK_MM, i, S, kc);
+      if (S > 1 && (!split || kc < 8 || (S > (chains ? 1 : need) && S * n * ldp * 4 > DP_PART_BYTES))) break;
+      if ((S < need && !chains) || nc - (S - 1) * kc < 8) continue;
+      const double t = mm_price(prec, n, n, F, MM_TILES[i], S, kc);
+      offer(S < need ? 1.02 * t : t, DK_MM, i, S, kc, S < need ? (int)(nc / need / 2 * 2) : 0);
     }
   }
   return pl;
@@ -845,7 +898,7 @@ DensePlan dense_plan(int prec, int64_t n, int64_t F, bool tiled, bool split) {
 // With less scratch than the partials of all rows need, the product takes its
 // rows in several launches, each followed by its reduction.  The k ranges stay
 // and with them every bit: the order in which an output is summed depends on the
-// ranges, not on the tile that holds it, so each launch takes the tile that is
+// ranges and chains, not on the tile that holds it, so each launch takes the tile that is
 // cheapest for its rows.  (All rows with one tile left compute units idle: n =
 // 16384, F = 512, 16-bit, two ranges through the 64 MiB of
 // gcn_layer_bwd_noalloc 400 us, 313 with the rows and tiles priced.)
@@ -857,7 +910,7 @@ int64_t dense_row_step(const DensePlan& pl) { return pl.kind == DK_MM ? 256 : 12
 int cheapest_tile(int prec, const DensePlan& pl, int64_t n, int64_t rows, int64_t F, double* price) {
   int best = pl.tile;
   *price = mm_price(prec, n, rows, F, MM_TILES[best], pl.ksplit, pl.kc);
-  for (int i = 0; i < 4; ++i) {
+  for (int i = pl.chain ? MM_CHAIN_TILE : 0; i < 4; ++i) {
     const double t = mm_price(prec, n, rows, F, MM_TILES[i], pl.ksplit, pl.kc);
     if (t < *price) { *price = t; best = i; }
   }
@@ -903,6 +956,7 @@ hipError_t launch_rows(const DensePlan& pl, const void* A, int64_t n, const T* X
     q.tiles = steps * q.cb;
     q.ksplit = pl.ksplit;
     q.kc = pl.kc;
+    q.chain = pl.chain;
     q.part = part;
     q.row0 = row0;
     q.prows = rows;
@@ -910,12 +964,21 @@ hipError_t launch_rows(const DensePlan& pl, const void* A, int64_t n, const T* X
     q.per_xcd = (q.tiles * q.ksplit + 7) / 8;
     q.epi = epi;
     const dim3 g((unsigned)(8 * q.per_xcd));
-    switch (pl.tile) {
-      case 0: hipLaunchKernelGGL((dense_mm_kernel<T, 8, 8, 4>), g, dim3(256), 0, s, q); break;
-      case 1: hipLaunchKernelGGL((dense_mm_kernel<T, 8, 6, 5>), g, dim3(256), 0, s, q); break;
-      case 2: hipLaunchKernelGGL((dense_mm_kernel<T, 8, 4, 6>), g, dim3(256), 0, s, q); break;
-      default: hipLaunchKernelGGL((dense_mm_kernel<T, 4, 4, 8>), g, dim3(256), 0, s, q); break;
+#define MM_LAUNCH(TM_, TN_, S_, C_) \
+  hipLaunchKernelGGL((dense_mm_kernel<T, TM_, TN_, S_, C_>), g, dim3(256), 0, s, q)
+    if constexpr (sizeof(T) == 4) {
+      if (pl.chain && pl.tile == MM_CHAIN_TILE) MM_LAUNCH(8, 4, 6, true);
+      else if (pl.chain) MM_LAUNCH(4, 4, 8, true);
     }
+    if (!pl.chain) {
+      switch (pl.tile) {
+        case 0: MM_LAUNCH(8, 8, 4, false); break;
+        case 1: MM_LAUNCH(8, 6, 5, false); break;
+        case 2: MM_LAUNCH(8, 4, 6, false); break;
+        default: MM_LAUNCH(4, 4, 8, false); break;
+      }
+    }
+#undef MM_LAUNCH
   } else {
     StreamParams q;
     q.A = A; q.Xt = Xt; q.n = n; q.F = F; q.nc = nc;
@@ -1039,7 +1102,7 @@ size_t dense_agg_min_bytes(int prec, int64_t n, int64_t F, bool tiled) {
   return xt_bytes(prec, n, F) + dense_part_bytes(pl, std::min(n, dense_row_step(pl)), F);
 }
 
-void dense_plan_query(int prec, int64_t n, int64_t F, int64_t out[5]) {
+void dense_plan_query(int prec, int64_t n, int64_t F, int64_t out[6]) {
   const DensePlan pl = dense_plan(prec, n, F, true, true);
   const bool mm = pl.kind == DK_MM;
   out[0] = pl.kind;
@@ -1047,6 +1110,7 @@ void dense_plan_query(int prec, int64_t n, int64_t F, int64_t out[5]) {
   out[2] = mm ? MM_TILES[pl.tile].cols : 64;
   out[3] = pl.ksplit;
   out[4] = mm ? pl.kc : (n + (prec == 0 ? 15 : 31)) / (prec == 0 ? 16 : 32);
+  out[5] = pl.chain;
 }
 
 int64_t dense_tiled_elems(int prec, int64_t n) {

@@ -137,8 +137,9 @@ hipError_t dense_agg_launch(int prec, const void* A, int64_t lda, bool tiled, in
                             int64_t F, const Epilogue& epi, void* ws, size_t ws_bytes, float* colsum, hipStream_t s,
                             bool split = true);
 // How the tiled product is cut: kernel (0: 64-row blocks, 1: streaming, 2: MFMA
-// tiles), rows and columns of a workgroup, k ranges, chunks of the longest one.
-void dense_plan_query(int prec, int64_t n, int64_t F, int64_t out[5]);
+// tiles), rows and columns of a workgroup, k ranges, chunks of the longest one
+// and of its chains (0: one chain).
+void dense_plan_query(int prec, int64_t n, int64_t F, int64_t out[6]);
 // Elements of the tiled dense A_hat (rows padded to 64, columns to the chunk).
 int64_t dense_tiled_elems(int prec, int64_t n);
 // Dense A_hat from CSR: row-major (ld) or tiled operand order.

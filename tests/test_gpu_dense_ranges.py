@@ -75,9 +75,37 @@ def test_tiled_aggregation(prec, n, F):
     assert bool(fin[:, :F - 1].all()) and not bool(fin[A[:, n - 1] > 0, F - 1].any()) and flag.item() == 1
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,F,chains", [(20928, 16, 8), (880, 80, 8), (8192, 128, 8), (8192, 100, 8), (24000, 160, 8),
+                                        (7076, 504, 2), (1433, 778, 4)])
+def test_fp32_sums_keep_to_short_chains(n, F, chains):
+    """On a full A_hat an fp32 output is the sum of several chains of additions.
+    A chain of m additions of zero-mean terms, four products each, has partial
+    sums of rms sqrt(4 k) s after k of them and a rounding error of at most 2^-24
+    of it each time: 2^-24 s sqrt(2) m in all, `chains` of them with m = n / (4
+    chains) against the result's rms sqrt(n) s: 2^-24 sqrt(n / (8 chains))."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + F)
+    A = torch.randn((n, n), generator=gen, device="cuda")
+    X = torch.randn((n, F), generator=gen, device="cuda")
+    At = tile(A, G.GCN_F32)
+    a = _adj(n, G.GCN_F32, At.data_ptr())
+    ld = (F + 7) // 8 * 8
+    X = torch.nn.functional.pad(X, (0, ld - F)).contiguous()
+    Y = torch.empty_like(X)
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(G.gcn_aggregate_workspace_size(a, F, G.GCN_F32), dtype=torch.uint8, device="cuda")
+    G.gcn_aggregate(a, F, G.GCN_F32, X, ld, None, G.GCN_ACT_NONE, 0.0, False, 0, 0, 0, Y, ld, flag, ws)
+    rows = torch.arange(0, n, 8, device="cuda")
+    want = A[rows].double() @ X[:, :F].double()
+    err = float((Y[rows, :F].double() - want).norm() / want.norm())
+    assert err <= 2.0 ** -24 * (n / (8 * chains)) ** 0.5, err
+
+
 def plan(prec, n, F):
-    """(kernel, rows, columns, k ranges, chunks of the longest range) of a tiled product."""
-    out = (ctypes.c_int64 * 5)()
+    """(kernel, rows, columns, k ranges, chunks of the longest range, chunks of its
+    chains) of a tiled product."""
+    out = (ctypes.c_int64 * 6)()
     G.lib().gcn_internal_dense_plan(ctypes.c_int32(prec), ctypes.c_int64(n), ctypes.c_int64(F), out)
     return tuple(out)
 
