@@ -368,10 +368,16 @@ __device__ __forceinline__ void row_range(int64_t n, int64_t* r0, int64_t* r1) {
   *r1 = *r0 + per < n ? *r0 + per : n;
 }
 
+// Workgroups of the two kernels over the light rows: 1024 rows each, so that the
+// global atomics, one per bucket and workgroup, stay few (a workgroup per 256
+// rows spent 20 us on them at 262144 rows), and 4096 workgroups, until each has
+// 8192 rows, two blocks of light rows: at most 258 buckets with the default
+// threshold, where LDS holds 1024.  n = 2^27 (whole gcn_schedule): 5.24 ms with 4096
+// workgroups of eight blocks, 4.45 so, 4.63 with 65536.
+unsigned light_grid(int64_t n) { return grid_for(n, 1024, std::max<int64_t>(4096, (n + 8191) / 8192)); }
+
 // Per row: its counts for the scan (counts[n] = 0), and, for a light row, its
-// bucket's histogram.  A workgroup takes 1024 rows or more, so that the global
-// atomics, one per bucket and workgroup, stay few (a workgroup per 256 rows
-// spent 20 us on them at 262144 rows).
+// bucket's histogram.
 template <typename IdxT>
 __global__ __launch_bounds__(256) void row_count_kernel(int64_t n, const IdxT* __restrict__ rowptr,
                                                         const int32_t* __restrict__ colidx, int64_t thr, int64_t seg,
@@ -487,10 +493,26 @@ struct SchedTotals {
   int64_t slots;               // most pieces on one XCD
 };
 
-// Bucket offsets from the histograms (workgroup 0: light rows, nb buckets;
-// workgroup 1: pieces), the column ranges' piece offsets and the totals.
+// The light rows' bucket counts as the operand of a grid-wide scan: off[b] =
+// hist[b], off[nb] = 0.
+__global__ void light_widen_kernel(int64_t nb, const int32_t* __restrict__ hist, int64_t* __restrict__ off) {
+  for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b <= nb; b += (int64_t)gridDim.x * blockDim.x)
+    off[b] = b < nb ? hist[b] : 0;
+}
+
+// Light-row buckets up to which one workgroup scans them, beside the one that
+// scans the pieces' buckets: each of its threads walks nb / 1024 buckets alone.
+// Above, the grid does, in four launches more: whole gcn_schedule at n = 2^20
+// with 4097 buckets 177 us by one workgroup, 183 by the grid, with 16385 162 /
+// 152, with 65537 252 / 151; n = 2^24, 528,385 buckets 2296 / 738.
+constexpr int64_t LIGHT_SCAN_ONE_WG = 1 << 14;
+
+// Bucket offsets from the histograms (workgroup 0: light rows, nb buckets,
+// unless loff holds their offsets already; workgroup 1: pieces), the column
+// ranges' piece offsets and the totals.
 __global__ __launch_bounds__(1024) void bucket_scan_kernel(int64_t nb, const int32_t* __restrict__ lhist,
-                                                           int64_t* __restrict__ loff, const int32_t* __restrict__ chist,
+                                                           int64_t* __restrict__ loff, bool scanned,
+                                                           const int32_t* __restrict__ chist,
                                                            int64_t* __restrict__ coff, int64_t parts,
                                                            int64_t* __restrict__ part_off,
                                                            const Counts4* __restrict__ rows, SchedTotals* __restrict__ out) {
@@ -498,26 +520,28 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(int64_t nb, const int
   const int32_t* hist = blockIdx.x ? chist : lhist;
   int64_t* off = blockIdx.x ? coff : loff;
   const int64_t m = blockIdx.x ? CHUNK_BUCKETS : nb;
-  const int64_t per = (m + 1023) / 1024;
-  const int64_t b0 = threadIdx.x * per < m ? threadIdx.x * per : m, b1 = b0 + per < m ? b0 + per : m;
-  int64_t sum = 0;
-  for (int64_t b = b0; b < b1; ++b) sum += hist[b];
-  int64_t run = radix_block_scan<1024, int64_t>(sum, red);
-  for (int64_t b = b0; b < b1; ++b) {
-    off[b] = run;
-    if (!blockIdx.x && b == nb - 1) out->n_multi = run;
-    run += hist[b];
+  if (blockIdx.x || !scanned) {
+    const int64_t per = (m + 1023) / 1024;
+    const int64_t b0 = threadIdx.x * per < m ? threadIdx.x * per : m, b1 = b0 + per < m ? b0 + per : m;
+    int64_t sum = 0;
+    for (int64_t b = b0; b < b1; ++b) sum += hist[b];
+    int64_t run = radix_block_scan<1024, int64_t>(sum, red);
+    for (int64_t b = b0; b < b1; ++b) {
+      off[b] = run;
+      run += hist[b];
+    }
+    if (threadIdx.x == 1023) off[m] = run;            // past the last bucket: the total
+    __syncthreads();                                  // the offsets are visible to the workgroup
   }
-  if (threadIdx.x == 1023) {                          // past the last bucket: the total
-    off[m] = run;
-    if (!blockIdx.x) {
-      out->n_light = run;
+  if (!blockIdx.x) {
+    if (threadIdx.x == 0) {
+      out->n_light = loff[nb];
+      out->n_multi = loff[nb - 1];
       out->rows_a = rows->a;
       out->rows_b = rows->b;
     }
+    return;
   }
-  if (!blockIdx.x) return;
-  __syncthreads();                                    // the offsets written above are visible to the workgroup
   for (int64_t q = threadIdx.x; q <= parts; q += 1024) part_off[q] = coff[q * (CHUNK_BUCKETS / parts)];
   if (threadIdx.x == 0) {                             // ranges x, x + 8, ... run on XCD x
     int64_t most = coff[CHUNK_BUCKETS];
@@ -733,7 +757,7 @@ struct SchedLayout {
   Counts4 *counts, *scr;
   int32_t *chist, *ccur, *hist, *cur;      // contiguous: cleared together
   size_t zero_bytes;
-  int64_t *cboff, *boff;
+  int64_t *cboff, *boff, *bscr;
   SchedTotals* totals;
   size_t bytes;
 };
@@ -764,18 +788,19 @@ SchedLayout sched_layout(int64_t n, int64_t nnz, int64_t thr, int64_t chunk, int
   L.zero_bytes = o - z0;
   L.cboff = (int64_t*)take(sizeof(int64_t) * (CHUNK_BUCKETS + 1));
   L.boff = (int64_t*)take(sizeof(int64_t) * (nb + 1));
+  L.bscr = (int64_t*)take(sizeof(int64_t) * scan_scratch_elems(nb + 1));
   L.totals = (SchedTotals*)take(sizeof(SchedTotals));
   L.bytes = o;
   return L;
 }
 
-// Ten launches and one synchronisation: nothing on the way needs a count on
+// Ten launches (more for long scans) and one synchronisation: nothing on the way needs a count on
 // the host (the kernels over the pieces read their number on the device).
 template <typename IdxT>
 hipError_t schedule_t(int64_t n, int64_t nnz, const IdxT* rowptr, const int32_t* colidx, int64_t thr, int64_t chunk,
                       int64_t parts, const SchedLayout& L, SchedTotals* host, hipStream_t s) {
   const int64_t nb = light_buckets(n, thr), blk = light_block(n);
-  const dim3 rg(grid_for(n, 1024, 4096));
+  const dim3 rg(light_grid(n));
   const dim3 cg(grid_for(max_pieces(n, nnz, thr, chunk, parts), 2048, 512));
   hipError_t e;
 #define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
@@ -790,7 +815,13 @@ hipError_t schedule_t(int64_t n, int64_t nnz, const IdxT* rowptr, const int32_t*
   GCN_TRY(hipGetLastError());
   hipLaunchKernelGGL(chunk_hist_kernel, cg, dim3(256), 0, s, n, total, colidx, L.chunk_beg, L.chist);
   GCN_TRY(hipGetLastError());
-  hipLaunchKernelGGL(bucket_scan_kernel, dim3(2), dim3(1024), 0, s, nb, L.hist, L.boff, L.chist, L.cboff, parts,
+  const bool wide = nb > LIGHT_SCAN_ONE_WG;
+  if (wide) {
+    hipLaunchKernelGGL(light_widen_kernel, dim3(grid_for(nb + 1)), dim3(256), 0, s, nb, L.hist, L.boff);
+    GCN_TRY(hipGetLastError());
+    GCN_TRY(scan_exclusive(L.boff, nb + 1, L.bscr, s));
+  }
+  hipLaunchKernelGGL(bucket_scan_kernel, dim3(2), dim3(1024), 0, s, nb, L.hist, L.boff, wide, L.chist, L.cboff, parts,
                      L.part_off, total, L.totals);
   GCN_TRY(hipGetLastError());
   hipLaunchKernelGGL(light_scatter_kernel<IdxT>, rg, dim3(256), 0, s, n, rowptr, thr, blk, nb, L.boff, L.cur, L.perm,
