@@ -627,14 +627,15 @@ struct NormLayout {
 };
 NormLayout norm_layout(int64_t n, int64_t E, void* ws) {
   const int64_t total = 2 * E + n, nu = (total + UNIQ_TILE - 1) / UNIQ_TILE;
-  const size_t kb = (2 * id_bits(n) <= 32 ? sizeof(Key32) : sizeof(Key64)) * (size_t)total;
+  const bool k32 = 2 * id_bits(n) <= 32;
+  const size_t kb = (k32 ? sizeof(Key32) : sizeof(Key64)) * (size_t)total;
   NormLayout L;
   char* base = static_cast<char*>(ws);
   size_t o = 0;
   auto take = [&](size_t bytes) { char* p = base ? base + o : nullptr; o += align256(bytes); return p; };
   L.kA = take(kb);
   L.kB = take(kb);
-  L.radix = take(radix_scratch_bytes(total));
+  L.radix = take(k32 ? radix_scratch_bytes<Key32>(total) : radix_scratch_bytes<Key64>(total));
   L.off = (int64_t*)take(sizeof(int64_t) * (nu + 2));   // the scan's total (nnz), then the flag: read back together
   L.scr = (int64_t*)take(sizeof(int64_t) * scan_scratch_elems(nu + 1));
   L.bad = base ? (int32_t*)(L.off + nu + 1) : nullptr;

@@ -692,7 +692,7 @@ PairLayout pair_layout(int64_t n, int64_t n_pairs, int64_t F, void* ws) {
   auto take = [&](size_t bytes) { char* q = base ? base + o : nullptr; o += align256(bytes); return q; };
   L.eA = (PairEnd*)take(sizeof(PairEnd) * (total > 0 ? total : 1));
   L.eB = (PairEnd*)take(sizeof(PairEnd) * (total > 0 ? total : 1));
-  L.radix = take(radix_scratch_bytes(total));
+  L.radix = take(radix_scratch_bytes<PairEnd>(total));
   L.off = (int64_t*)take(sizeof(int64_t) * (n + 1));
   L.head = (float*)take(sizeof(float) * nseg * ldp);
   L.tail = (float*)take(sizeof(float) * nseg * ldp);
@@ -765,7 +765,7 @@ MetricsLayout metrics_layout(int64_t total, void* ws) {
   auto take = [&](size_t bytes) { char* q = base ? base + o : nullptr; o += align256(bytes); return q; };
   L.iA = (ScoreItem*)take(sizeof(ScoreItem) * total);
   L.iB = (ScoreItem*)take(sizeof(ScoreItem) * total);
-  L.radix = take(radix_scratch_bytes(total));
+  L.radix = take(radix_scratch_bytes<ScoreItem>(total));
   L.scr = (int64_t*)take(sizeof(int64_t) * segment_scan_scratch_elems(total + 1));
   L.neg = (int64_t*)take(sizeof(int64_t) * (total + 1));
   L.ap_part = (double*)take(sizeof(double) * nb);

@@ -43,13 +43,18 @@ struct ItemArray {
 constexpr int RADIX_NT = 512;                        // threads per tile
 constexpr int RADIX_MAX_BITS = 9;                    // widest digit
 
-// Items per thread: 8, or 16 from 2^25 items on.  Longer digit runs write
-// fuller lines, which count once the items leave the caches (138 M 8-byte keys
-// sorted and compacted in 10.4 ms with 8, 8.8 ms with 16), but a short list
-// then fills fewer compute units (20,000 keys 95 -> 114 us, 8.7 M 387 -> 400).
-inline int radix_ipt(int64_t total) { return total < ((int64_t)1 << 25) ? 8 : 16; }
-inline int64_t radix_tiles(int64_t total) {
-  const int64_t t = RADIX_NT * radix_ipt(total);
+// Items per thread: 8, or 16 from 2^25 items of up to 8 bytes and 2^27 larger ones
+// on.  Longer digit runs write fuller lines, which count once the items leave the
+// caches (138 M 8-byte keys sorted and compacted in 10.4 ms with 8, 8.8 ms with
+// 16), but a short list then fills fewer compute units (20,000 keys 95 -> 114
+// us, 8.7 M 387 -> 400), and a tile of 12-byte items with 16 takes 104 KB of LDS,
+// one workgroup per compute unit: gcn_pair_backward, F = 8, with 8 / 16 at 2^25
+// items 1246 / 1326 us, 2^26 3.51 / 3.67 ms, 2^27 8.25 / 7.97.
+template <typename Item>
+int radix_ipt(int64_t total) { return total < ((int64_t)1 << (sizeof(Item) <= 8 ? 25 : 27)) ? 8 : 16; }
+template <typename Item>
+int64_t radix_tiles(int64_t total) {
+  const int64_t t = RADIX_NT * radix_ipt<Item>(total);
   return (total + t - 1) / t;
 }
 
@@ -64,9 +69,10 @@ inline void radix_plan(int bits, int* passes, int* width) {
 
 // Scratch of a pass over `total` items: the tiles' counts and the digit
 // totals, 32-bit while every position fits.
-inline size_t radix_scratch_bytes(int64_t total) {
+template <typename Item>
+size_t radix_scratch_bytes(int64_t total) {
   const size_t w = total < ((int64_t)1 << 32) ? sizeof(uint32_t) : sizeof(uint64_t);
-  const int64_t t = radix_tiles(total);
+  const int64_t t = radix_tiles<Item>(total);
   return ((size_t)(t > 0 ? t : 1) + 1) * ((size_t)1 << RADIX_MAX_BITS) * w;
 }
 
@@ -267,7 +273,7 @@ __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst ds
 
 template <int LOGD, int IPT, typename Src, typename Dst, typename OffT>
 hipError_t radix_pass_t(const Src& src, const Dst& dst, int64_t total, int shift, int width, void* scratch, hipStream_t s) {
-  const int64_t nt = radix_tiles(total);
+  const int64_t nt = radix_tiles<typename Src::Item>(total);
   OffT* cnt = static_cast<OffT*>(scratch);
   OffT* tot = cnt + nt * ((int64_t)1 << LOGD);
   const uint32_t mask = (1u << width) - 1u;
@@ -286,7 +292,7 @@ hipError_t radix_pass_t(const Src& src, const Dst& dst, int64_t total, int shift
 // One stable pass over digit (key >> shift) of `width` <= 9 bits; total > 0.
 template <typename Src, typename Dst>
 hipError_t radix_pass(const Src& src, const Dst& dst, int64_t total, int shift, int width, void* scratch, hipStream_t s) {
-  if (radix_ipt(total) == 8) {
+  if (radix_ipt<typename Src::Item>(total) == 8) {
     if (width <= 8) return radix_pass_t<8, 8, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
     return radix_pass_t<9, 8, Src, Dst, uint32_t>(src, dst, total, shift, width, scratch, s);
   }
