@@ -31,7 +31,8 @@
  *            ignored; columns [f, ld) of an output may be overwritten with 0.
  * Streams.   `stream` is a hipStream_t (NULL = default stream).  All calls are
  *            asynchronous on it, except gcn_normalize and gcn_schedule, which
- *            synchronise it (once each) to return sizes to the host.
+ *            synchronise it (once each; gcn_normalize from 2^31 keys, 2
+ *            num_edges + n, on several times) to return sizes to the host.
  * Errors.    Every call validates its arguments on the host before it
  *            launches anything and returns a gcn_status; a call that returns
  *            an argument error has had no effect.  GCN_ERR_DEVICE reports a
@@ -208,7 +209,9 @@ int32_t gcn_abi_version(void);
  * NULL), dinv (required), values (may be NULL), dense (may be NULL).
  * GCN_I32 requires 2 * num_edges + n < 2^31.  workspace: at least
  * gcn_normalize_workspace_size() bytes.  *nnz_out (host) receives nnz.
- * Synchronises `stream` once.  Returns GCN_ERR_GRAPH if a vertex id lies
+ * Synchronises `stream` once, with 2 * num_edges + n >= 2^31 several times
+ * (the keys are then sorted in parts, in a workspace of 4.7 bytes per key
+ * instead of 17).  Returns GCN_ERR_GRAPH if a vertex id lies
  * outside [0, n) (outputs are then undefined).  The result is bit-identical
  * from run to run.
  * ------------------------------------------------------------------------- */

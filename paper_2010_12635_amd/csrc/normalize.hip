@@ -119,6 +119,7 @@ unsigned grid_for(int64_t items, int per_block = 256, int64_t cap = 65536) {
 template <typename I>
 struct EdgeItems {
   typedef I Item;
+  static constexpr bool FILTERED = false;
   int64_t n, E;
   const int32_t* src;
   const int32_t* dst;
@@ -141,6 +142,46 @@ struct EdgeItems {
     return x;
   }
 };
+
+// The items with keys in [lo, hi].
+template <typename I>
+struct RangeItems : EdgeItems<I> {
+  static constexpr bool FILTERED = true;
+  uint64_t lo, hi;
+  __device__ __forceinline__ bool keep(const I& x) const { return x.key() >= lo && x.key() <= hi; }
+};
+
+// cnt[(key - lo) >> shift] += 1 for the keys in [lo, hi]; at most RANGE_BINS
+// bins, cleared beforehand.
+constexpr int RANGE_BITS = 10, RANGE_BINS = 1 << RANGE_BITS;
+
+template <typename I>
+__global__ __launch_bounds__(256) void range_hist_kernel(RangeItems<I> src, int64_t total, int shift,
+                                                         unsigned long long* __restrict__ cnt) {
+  constexpr int U = 8;
+  __shared__ uint32_t h[RANGE_BINS];                 // a workgroup's share: below 2^32
+  for (int b = threadIdx.x; b < RANGE_BINS; b += 256) h[b] = 0;
+  __syncthreads();
+  for (int64_t base = (int64_t)blockIdx.x * (256 * U); base < total; base += (int64_t)gridDim.x * (256 * U)) {
+    I x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = base + u * 256 + threadIdx.x;
+      x[u] = src.load(i < total ? i : total - 1);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (base + u * 256 + threadIdx.x < total && src.keep(x[u])) atomicAdd(&h[(x[u].key() - src.lo) >> shift], 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < RANGE_BINS; b += 256)
+    if (h[b]) atomicAdd(&cnt[b], (unsigned long long)h[b]);
+}
+
+template <typename I>
+__global__ void one_key_kernel(I* p, uint64_t key) {
+  p->k = (decltype(I::k))key;
+}
 
 constexpr int UNIQ_IPT = 8;
 constexpr int UNIQ_TILE = 256 * UNIQ_IPT;
@@ -187,11 +228,14 @@ __global__ __launch_bounds__(256) void uniq_count_kernel(const I* __restrict__ k
   }
 }
 
-// Distinct keys in order: colidx, the row of every entry, and rowptr where a
-// row begins (each row holds its self-loop, so each begins somewhere).
+// Distinct keys in order, from entry `first` on: colidx, the row of every entry
+// (if rows is not NULL), and rowptr where a row begins (each row holds its
+// self-loop, so each begins somewhere); the keys' first row began before if it
+// is prev_row.
 template <typename I, typename IdxT>
 __global__ __launch_bounds__(256) void uniq_write_kernel(const I* __restrict__ keys, int64_t total, int b, int64_t n,
-                                                         const int64_t* __restrict__ off, int32_t* __restrict__ colidx,
+                                                         const int64_t* __restrict__ off, int64_t first,
+                                                         int64_t prev_row, int32_t* __restrict__ colidx,
                                                          int32_t* __restrict__ rows, IdxT* __restrict__ rowptr) {
   typedef decltype(I::k) K;
   __shared__ int wsum[4];
@@ -204,7 +248,7 @@ __global__ __launch_bounds__(256) void uniq_write_kernel(const I* __restrict__ k
   for (int r = 0; r < UNIQ_IPT; ++r) a += __popcll(x.first[r]);
   if (lane == 0) wsum[wave] = a;
   __syncthreads();
-  int64_t run = off[blockIdx.x];
+  int64_t run = first + off[blockIdx.x];
   for (int w = 0; w < wave; ++w) run += wsum[w];
   const uint64_t lt = lane == 0 ? 0ull : ~0ull >> (64 - lane);
   const K cmask = (K)(((K)1 << b) - 1);
@@ -214,12 +258,12 @@ __global__ __launch_bounds__(256) void uniq_write_kernel(const I* __restrict__ k
       const int64_t pos = run + __popcll(x.first[r] & lt);
       const K row = x.k[r] >> b;
       colidx[pos] = (int32_t)(x.k[r] & cmask);
-      rows[pos] = (int32_t)row;
-      if (w0 + r * 64 + lane == 0 || row != x.prev[r] >> b) rowptr[row] = (IdxT)pos;
+      if (rows) rows[pos] = (int32_t)row;
+      if (w0 + r * 64 + lane == 0 ? (int64_t)row != prev_row : row != x.prev[r] >> b) rowptr[row] = (IdxT)pos;
     }
     run += __popcll(x.first[r]);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) rowptr[n] = (IdxT)off[gridDim.x];
+  if (blockIdx.x == 0 && threadIdx.x == 0) rowptr[n] = (IdxT)(first + off[gridDim.x]);
 }
 
 template <typename IdxT>
@@ -257,6 +301,36 @@ __global__ __launch_bounds__(256) void values_kernel(const int64_t* __restrict__
       const T v = from_f32<T>(a[u] * b[u]);
       if (values) values[k] = v;
       if (dense) dense[(int64_t)r[u] * ld_dense + c[u]] = v;
+    }
+  }
+}
+
+// The same without the rows of the entries: a workgroup finds the rows of its
+// first and last entry in rowptr, a thread the row of its own between them.
+constexpr int VALUES_TILE = 2048;
+
+template <typename T, typename IdxT>
+__global__ __launch_bounds__(256) void values_search_kernel(int64_t nnz, int64_t n, const IdxT* __restrict__ rowptr,
+                                                            const int32_t* __restrict__ colidx,
+                                                            const float* __restrict__ dinv, T* __restrict__ values,
+                                                            T* __restrict__ dense, int64_t ld_dense) {
+  auto row_of = [&](int64_t k, int64_t lo, int64_t hi) {   // the last r in [lo, hi] with rowptr[r] <= k
+    while (lo < hi) {
+      const int64_t m = hi - ((hi - lo) >> 1);
+      if ((int64_t)rowptr[m] <= k) lo = m;
+      else hi = m - 1;
+    }
+    return lo;
+  };
+  for (int64_t base = (int64_t)blockIdx.x * VALUES_TILE; base < nnz; base += (int64_t)gridDim.x * VALUES_TILE) {
+    const int64_t end = base + VALUES_TILE < nnz ? base + VALUES_TILE : nnz;
+    const int64_t ra = row_of(base, 0, n - 1), rb = row_of(end - 1, ra, n - 1);
+    for (int64_t k = base + threadIdx.x; k < end; k += 256) {
+      const int64_t r = row_of(k, ra, rb);
+      const int32_t c = colidx[k];
+      const T v = from_f32<T>(dinv[r] * dinv[c]);
+      if (values) values[k] = v;
+      if (dense) dense[r * ld_dense + c] = v;
     }
   }
 }
@@ -616,20 +690,34 @@ int id_bits(int64_t n) {
   return b;
 }
 
+// Keys from which they are sorted in ranges of a quarter of them each (and some
+// more, so that even rows make four), the ranges in turn in the same two buffers:
+// 4.6 bytes of workspace per key of 8 bytes instead of 16.5, which would be more
+// than an eighth of the memory here.  The price is that every range reads the
+// edge list twice: R-MAT scale 26, 2.2 G keys, all in one sort 172 ms and 36.0 GB,
+// in ranges 235 ms and 9.7 GB; scale 27 389 ms, 73.1 GB and 545 ms, 20.5 GB.
+constexpr int64_t NORM_RANGES_FROM = (int64_t)1 << 31;
+
 // Workspace of normalize_run: two key buffers, the sort's scratch, the
-// distinct keys per tile with their scan, the bad-id flag.
+// distinct keys per tile with their scan, the bad-id flag, the ranges' bins.
 struct NormLayout {
   char *kA, *kB;
   void* radix;
   int64_t *off, *scr;
   int32_t* bad;
+  unsigned long long* bins;
+  bool ranges;
+  int64_t most;              // keys a buffer holds
   size_t bytes;
 };
 NormLayout norm_layout(int64_t n, int64_t E, void* ws) {
-  const int64_t total = 2 * E + n, nu = (total + UNIQ_TILE - 1) / UNIQ_TILE;
-  const bool k32 = 2 * id_bits(n) <= 32;
-  const size_t kb = (k32 ? sizeof(Key32) : sizeof(Key64)) * (size_t)total;
+  const int64_t total = 2 * E + n;
   NormLayout L;
+  L.ranges = total >= NORM_RANGES_FROM;
+  L.most = L.ranges ? total / 4 + total / 128 : total;
+  const int64_t nu = (L.most + UNIQ_TILE - 1) / UNIQ_TILE;
+  const bool k32 = 2 * id_bits(n) <= 32;
+  const size_t kb = (k32 ? sizeof(Key32) : sizeof(Key64)) * (size_t)L.most;
   char* base = static_cast<char*>(ws);
   size_t o = 0;
   auto take = [&](size_t bytes) { char* p = base ? base + o : nullptr; o += align256(bytes); return p; };
@@ -639,6 +727,7 @@ NormLayout norm_layout(int64_t n, int64_t E, void* ws) {
   L.off = (int64_t*)take(sizeof(int64_t) * (nu + 2));   // the scan's total (nnz), then the flag: read back together
   L.scr = (int64_t*)take(sizeof(int64_t) * scan_scratch_elems(nu + 1));
   L.bad = base ? (int32_t*)(L.off + nu + 1) : nullptr;
+  L.bins = L.ranges ? (unsigned long long*)take(sizeof(unsigned long long) * RANGE_BINS) : nullptr;
   L.bytes = o;
   return L;
 }
@@ -653,51 +742,74 @@ struct NormOut {
   int64_t ld_dense;
 };
 
-template <typename I>
-hipError_t normalize_keys(int64_t n, int64_t E, const int32_t* src, const int32_t* dst, const NormOut& o,
-                          const NormLayout& L, hipStream_t s) {
-  const int64_t total = 2 * E + n;
-  const int b = id_bits(n);
-  hipError_t e;
 #define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
+
+// Sorts the `kept` keys that src keeps of its `total` items.
+template <typename I, typename Src>
+hipError_t sort_keys(const Src& src, int64_t total, int64_t kept, int bits, const NormLayout& L, const I** keys,
+                     I** spare, hipStream_t s) {
+  hipError_t e;
   int passes = 0, width = 0;
-  radix_plan(2 * b, &passes, &width);
-  ItemArray<I> bufA{(I*)L.kA}, bufB{(I*)L.kB}, in = bufB, out = bufA;
+  radix_plan(bits, &passes, &width);
+  ItemArray<I> in{(I*)L.kB}, out{(I*)L.kA};
   for (int ps = 0; ps < passes; ++ps) {
-    const int shift = ps * width, w = std::min(width, 2 * b - shift);
-    if (ps == 0) {
-      const EdgeItems<I> edges{n, E, src, dst, b, L.bad};
-      GCN_TRY(radix_pass(edges, out, total, shift, w, L.radix, s));
-    } else {
-      GCN_TRY(radix_pass(in, out, total, shift, w, L.radix, s));
-    }
+    const int shift = ps * width, w = std::min(width, bits - shift);
+    if (ps == 0) GCN_TRY(radix_pass(src, out, total, shift, w, L.radix, s));
+    else GCN_TRY(radix_pass(in, out, kept, shift, w, L.radix, s));
     std::swap(in, out);
   }
-  const I* keys = in.p;
-  int32_t* rows = (int32_t*)out.p;                    // the other buffer is free now
-  const int64_t nu = (total + UNIQ_TILE - 1) / UNIQ_TILE;
+  *keys = in.p;
+  *spare = out.p;
+  return hipSuccess;
+}
+
+// Distinct ones of `count` sorted keys to the CSR arrays, from entry `first` on.
+template <typename I>
+hipError_t write_distinct(const I* keys, int64_t count, int64_t n, int64_t first, int64_t prev_row, int32_t* rows,
+                          const NormOut& o, const NormLayout& L, hipStream_t s) {
+  hipError_t e;
+  const int b = id_bits(n);
+  const int64_t nu = (count + UNIQ_TILE - 1) / UNIQ_TILE;
   const dim3 ug((unsigned)nu);
-  hipLaunchKernelGGL(uniq_count_kernel<I>, ug, dim3(256), 0, s, keys, total, L.off);
+  hipLaunchKernelGGL(uniq_count_kernel<I>, ug, dim3(256), 0, s, keys, count, L.off);
   GCN_TRY(hipGetLastError());
   GCN_TRY(scan_exclusive(L.off, nu + 1, L.scr, s));
-  if (o.idx64) {
-    hipLaunchKernelGGL((uniq_write_kernel<I, int64_t>), ug, dim3(256), 0, s, keys, total, b, n, L.off, o.colidx, rows,
-                       (int64_t*)o.rowptr);
-    GCN_TRY(hipGetLastError());
+  if (o.idx64)
+    hipLaunchKernelGGL((uniq_write_kernel<I, int64_t>), ug, dim3(256), 0, s, keys, count, b, n, L.off, first, prev_row,
+                       o.colidx, rows, (int64_t*)o.rowptr);
+  else
+    hipLaunchKernelGGL((uniq_write_kernel<I, int32_t>), ug, dim3(256), 0, s, keys, count, b, n, L.off, first, prev_row,
+                       o.colidx, rows, (int32_t*)o.rowptr);
+  return hipGetLastError();
+}
+
+hipError_t degrees(int64_t n, const NormOut& o, hipStream_t s) {
+  if (o.idx64)
     hipLaunchKernelGGL(degree_kernel<int64_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int64_t*)o.rowptr, o.deg,
                        o.dinv);
-  } else {
-    hipLaunchKernelGGL((uniq_write_kernel<I, int32_t>), ug, dim3(256), 0, s, keys, total, b, n, L.off, o.colidx, rows,
-                       (int32_t*)o.rowptr);
-    GCN_TRY(hipGetLastError());
+  else
     hipLaunchKernelGGL(degree_kernel<int32_t>, dim3(grid_for(n)), dim3(256), 0, s, n, (const int32_t*)o.rowptr, o.deg,
                        o.dinv);
-  }
-  GCN_TRY(hipGetLastError());
+  return hipGetLastError();
+}
+
+// All keys in one sort; the values from the entries' rows, which go to the
+// other key buffer.
+template <typename I>
+hipError_t normalize_keys(const EdgeItems<I>& edges, const NormOut& o, const NormLayout& L, int64_t* nnz_out,
+                          int32_t* bad_ids, hipStream_t s) {
+  const int64_t n = edges.n, total = 2 * edges.E + n;
+  const I* keys;
+  I* spare;
+  hipError_t e;
+  GCN_TRY(sort_keys(edges, total, total, 2 * edges.b, L, &keys, &spare, s));
+  int32_t* rows = (int32_t*)spare;
+  GCN_TRY(write_distinct(keys, total, n, 0, -1, rows, o, L, s));
+  GCN_TRY(degrees(n, o, s));
+  const int64_t* nnz = L.off + (total + UNIQ_TILE - 1) / UNIQ_TILE;
   if (o.dense) GCN_TRY(fill_zero(o.dense, (size_t)n * (size_t)o.ld_dense * (o.value_prec == 0 ? 4 : 2), s));
   if (o.values || o.dense) {
     const dim3 g(grid_for(total, 1024, 8192));
-    const int64_t* nnz = L.off + nu;
     switch (o.value_prec) {
       case 0: hipLaunchKernelGGL(values_kernel<float>, g, dim3(256), 0, s, nnz, rows, o.colidx, o.dinv, (float*)o.values, (float*)o.dense, o.ld_dense); break;
       case 1: hipLaunchKernelGGL(values_kernel<f16>, g, dim3(256), 0, s, nnz, rows, o.colidx, o.dinv, (f16*)o.values, (f16*)o.dense, o.ld_dense); break;
@@ -706,13 +818,134 @@ hipError_t normalize_keys(int64_t n, int64_t E, const int32_t* src, const int32_
     }
     GCN_TRY(hipGetLastError());
   }
-#undef GCN_TRY
+  // the one synchronisation: nnz and the bad-id flag back to the host
+  int64_t host[2] = {0, 0};
+  GCN_TRY(hipMemcpyAsync(host, nnz, sizeof(host), hipMemcpyDeviceToHost, s));
+  GCN_TRY(hipStreamSynchronize(s));
+  *nnz_out = host[0];
+  *bad_ids = (int32_t)host[1];
   return hipSuccess;
+}
+
+// The keys range by range in ascending order.
+template <typename I>
+struct RangedKeys {
+  const EdgeItems<I>& edges;
+  const NormOut& o;
+  const NormLayout& L;
+  hipStream_t s;
+  int64_t nnz = 0, prev_row = -1;           // entries written, the row of the last
+  int32_t bad = 0;
+
+  RangeItems<I> items(uint64_t lo, uint64_t hi) const {
+    RangeItems<I> r;
+    static_cast<EdgeItems<I>&>(r) = edges;
+    r.lo = lo;
+    r.hi = hi;
+    return r;
+  }
+
+  // The `count` > 0 keys in [lo, hi], sorted in the buffers unless they are all one.
+  hipError_t write(uint64_t lo, uint64_t hi, int64_t count) {
+    const int64_t total = 2 * edges.E + edges.n;
+    hipError_t e;
+    const I* keys = (const I*)L.kA;
+    I* spare;
+    if (lo == hi) {
+      count = 1;
+      hipLaunchKernelGGL(one_key_kernel<I>, dim3(1), dim3(1), 0, s, (I*)L.kA, lo);
+      GCN_TRY(hipGetLastError());
+    } else {
+      GCN_TRY(sort_keys(items(lo, hi), total, count, 2 * edges.b, L, &keys, &spare, s));
+    }
+    GCN_TRY(write_distinct(keys, count, edges.n, nnz, prev_row, (int32_t*)nullptr, o, L, s));
+    int64_t added = 0;
+    I last{};
+    GCN_TRY(hipMemcpyAsync(&added, L.off + (count + UNIQ_TILE - 1) / UNIQ_TILE, sizeof(added), hipMemcpyDeviceToHost, s));
+    GCN_TRY(hipMemcpyAsync(&last, keys + count - 1, sizeof(last), hipMemcpyDeviceToHost, s));
+    GCN_TRY(hipStreamSynchronize(s));
+    nnz += added;
+    prev_row = (int64_t)(last.k >> edges.b);
+    return hipSuccess;
+  }
+
+  // The keys in [lo, lo + 2^bits): counted in up to RANGE_BINS bins, neighbouring
+  // bins together as long as they fit a buffer, larger bins split again.
+  hipError_t run(uint64_t lo, int bits) {
+    const int64_t total = 2 * edges.E + edges.n;
+    const int shift = bits > RANGE_BITS ? bits - RANGE_BITS : 0;
+    unsigned long long cnt[RANGE_BINS];
+    hipError_t e;
+    GCN_TRY(fill_zero(L.bins, sizeof(cnt), s));
+    hipLaunchKernelGGL(range_hist_kernel<I>, dim3(grid_for(total, 2048, 4096)), dim3(256), 0, s,
+                       items(lo, lo + (((uint64_t)1 << bits) - 1)), total, shift, L.bins);
+    GCN_TRY(hipGetLastError());
+    GCN_TRY(hipMemcpyAsync(cnt, L.bins, sizeof(cnt), hipMemcpyDeviceToHost, s));
+    GCN_TRY(hipMemcpyAsync(&bad, L.bad, sizeof(bad), hipMemcpyDeviceToHost, s));
+    GCN_TRY(hipStreamSynchronize(s));
+    if (bad) return hipSuccess;
+    uint64_t from = lo;                     // keys of the open range, which ends before bin d
+    int64_t held = 0;
+    for (int d = 0; d < 1 << (bits - shift); ++d) {
+      const uint64_t at = lo + ((uint64_t)d << shift);
+      const int64_t c = (int64_t)cnt[d];
+      if (held + c <= L.most) {
+        held += c;
+        continue;
+      }
+      if (held) GCN_TRY(write(from, at - 1, held));
+      from = at;
+      held = c;
+      if (c <= L.most) continue;
+      if (shift) GCN_TRY(run(at, shift));
+      else GCN_TRY(write(at, at, c));
+      from = at + ((uint64_t)1 << shift);
+      held = 0;
+    }
+    if (held) GCN_TRY(write(from, lo + (((uint64_t)1 << bits) - 1), held));
+    return hipSuccess;
+  }
+};
+
+template <typename T, typename IdxT>
+hipError_t values_by_search(int64_t nnz, int64_t n, const NormOut& o, hipStream_t s) {
+  hipLaunchKernelGGL((values_search_kernel<T, IdxT>), dim3(grid_for(nnz, VALUES_TILE)), dim3(256), 0, s, nnz, n,
+                     (const IdxT*)o.rowptr, o.colidx, o.dinv, (T*)o.values, (T*)o.dense, o.ld_dense);
+  return hipGetLastError();
+}
+
+template <typename I>
+hipError_t normalize_ranges(const EdgeItems<I>& edges, const NormOut& o, const NormLayout& L, int64_t* nnz_out,
+                            int32_t* bad_ids, hipStream_t s) {
+  const int64_t n = edges.n;
+  RangedKeys<I> r{edges, o, L, s};
+  hipError_t e;
+  GCN_TRY(r.run(0, 2 * edges.b));
+  *nnz_out = r.nnz;
+  *bad_ids = r.bad;
+  if (r.bad) return hipSuccess;
+  GCN_TRY(degrees(n, o, s));
+  if (o.dense) GCN_TRY(fill_zero(o.dense, (size_t)n * (size_t)o.ld_dense * (o.value_prec == 0 ? 4 : 2), s));
+  if (!o.values && !o.dense) return hipSuccess;
+  if (!o.idx64) return hipErrorInvalidValue;        // 32-bit row pointers end before the ranges begin
+  switch (o.value_prec) {
+    case 0: return values_by_search<float, int64_t>(r.nnz, n, o, s);
+    case 1: return values_by_search<f16, int64_t>(r.nnz, n, o, s);
+    case 2: return values_by_search<bf16, int64_t>(r.nnz, n, o, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename I>
+hipError_t normalize_t(const EdgeItems<I>& edges, const NormOut& o, const NormLayout& L, int64_t* nnz_out,
+                       int32_t* bad_ids, hipStream_t s) {
+  return L.ranges ? normalize_ranges(edges, o, L, nnz_out, bad_ids, s)
+                  : normalize_keys(edges, o, L, nnz_out, bad_ids, s);
 }
 }  // namespace
 
 // Measured (MI355X, R-MAT scale 18, 8.65 M keys of 36 bits, four passes of 9
-// bits): gcn_normalize + gcn_schedule 6.33 -> 0.74 ms; a pass 64 us (counts
+// bits): gcn_normalize + gcn_schedule 6.33 -> 0.50 ms; a pass 64 us (counts
 // 14, scan 12, scatter 38: 3.5 TB/s of keys read and written), distinct keys
 // 32 us, values 36 us.
 size_t normalize_workspace_bytes(int64_t n, int64_t E) { return norm_layout(n, E, nullptr).bytes; }
@@ -723,22 +956,14 @@ hipError_t normalize_run(int64_t n, int64_t E, const int32_t* src, const int32_t
                          void* ws, size_t ws_bytes, hipStream_t s) {
   const NormLayout L = norm_layout(n, E, ws);
   if (L.bytes > ws_bytes) return hipErrorInvalidValue;
-  const int64_t nu = (2 * E + n + UNIQ_TILE - 1) / UNIQ_TILE;
   const NormOut o{rowptr, idx64, colidx, deg, dinv, value_prec, values, dense, ld_dense};
+  const int b = id_bits(n);
   hipError_t e;
-#define GCN_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
   GCN_TRY(fill_zero(L.bad, sizeof(int64_t), s));
-  if (2 * id_bits(n) <= 32) GCN_TRY(normalize_keys<Key32>(n, E, src, dst, o, L, s));
-  else GCN_TRY(normalize_keys<Key64>(n, E, src, dst, o, L, s));
-  // the one synchronisation: nnz and the bad-id flag back to the host
-  int64_t host[2] = {0, 0};
-  GCN_TRY(hipMemcpyAsync(host, L.off + nu, sizeof(host), hipMemcpyDeviceToHost, s));
-  GCN_TRY(hipStreamSynchronize(s));
-  *nnz_out = host[0];
-  *bad_ids = (int32_t)host[1];
-#undef GCN_TRY
-  return hipSuccess;
+  if (2 * b <= 32) return normalize_t(EdgeItems<Key32>{n, E, src, dst, b, L.bad}, o, L, nnz_out, bad_ids, s);
+  return normalize_t(EdgeItems<Key64>{n, E, src, dst, b, L.bad}, o, L, nnz_out, bad_ids, s);
 }
+#undef GCN_TRY
 
 // Most pieces a schedule can hold: every heavy row (more than thr entries,
 // so at most nnz / (thr + 1) of them) has at most one piece per column range

@@ -234,6 +234,7 @@ struct PairEnd {
 // The unsorted endpoints, in pair order.
 struct PairEnds {
   typedef PairEnd Item;
+  static constexpr bool FILTERED = false;
   int64_t n;
   const int32_t* pu;
   const int32_t* pv;
@@ -530,6 +531,7 @@ struct ScoreItem {
 };
 struct ScoreItems {
   typedef ScoreItem Item;
+  static constexpr bool FILTERED = false;
   const float* scores;
   int64_t P;
   __device__ __forceinline__ ScoreItem load(int64_t i) const { return ScoreItem{score_key(scores[i]), i < P ? 1 : 0}; }

@@ -31,10 +31,12 @@ struct Key64 {
   __device__ __forceinline__ uint64_t key() const { return k; }
 };
 
-// Plain array of items, source or destination of a pass.
+// Plain array of items, source or destination of a pass.  (A source with
+// FILTERED set has a keep(item): the pass leaves the other items out.)
 template <typename I>
 struct ItemArray {
   typedef I Item;
+  static constexpr bool FILTERED = false;
   I* p;
   __device__ __forceinline__ I load(int64_t i) const { return p[i]; }
   __device__ __forceinline__ void store(int64_t i, const I& x) const { p[i] = x; }
@@ -78,6 +80,12 @@ size_t radix_scratch_bytes(int64_t total) {
 
 namespace {
 
+template <typename Src, typename Item>
+__device__ __forceinline__ bool radix_keeps(const Src& src, const Item& x) {
+  if constexpr (Src::FILTERED) return src.keep(x);
+  else return true;
+}
+
 // cnt[tile][d] = items of the tile with digit d.
 template <int LOGD, int RADIX_IPT, typename Src, typename OffT>
 __global__ __launch_bounds__(RADIX_NT) void radix_hist_kernel(Src src, int64_t total, int shift, uint32_t mask,
@@ -92,11 +100,12 @@ __global__ __launch_bounds__(RADIX_NT) void radix_hist_kernel(Src src, int64_t t
 #pragma unroll
   for (int r = 0; r < RADIX_IPT; ++r) {              // every load before the first count
     const int64_t i = base + r * RADIX_NT + threadIdx.x;
-    d[r] = (uint32_t)(src.load(i < total ? i : total - 1).key() >> shift) & mask;
+    const auto x = src.load(i < total ? i : total - 1);
+    d[r] = radix_keeps(src, x) ? (uint32_t)(x.key() >> shift) & mask : ~0u;
   }
 #pragma unroll
   for (int r = 0; r < RADIX_IPT; ++r)
-    if (base + r * RADIX_NT + threadIdx.x < total) atomicAdd(&h[wave][d[r]], 1u);
+    if (base + r * RADIX_NT + threadIdx.x < total && (!Src::FILTERED || d[r] != ~0u)) atomicAdd(&h[wave][d[r]], 1u);
   __syncthreads();
   for (int i = threadIdx.x; i < D; i += RADIX_NT) {
     uint32_t a = 0;
@@ -187,6 +196,7 @@ __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst ds
   __shared__ uint16_t wc[NW][D];                     // items of the digit in the wave's earlier rounds; then its slot base
   __shared__ OffT gb[D];                             // global position of the digit's first item minus its tile slot
   __shared__ OffT red[NW];
+  __shared__ int kept;                               // FILTERED: items of the tile
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t base = (int64_t)blockIdx.x * RADIX_TILE;
   const int64_t wbase = base + wave * (64 * RADIX_IPT);
@@ -206,7 +216,7 @@ __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst ds
   uint32_t rank[RADIX_IPT];
 #pragma unroll
   for (int r = 0; r < RADIX_IPT; ++r) {
-    const bool valid = wbase + r * 64 + lane < total;
+    const bool valid = wbase + r * 64 + lane < total && radix_keeps(src, it[r]);
     const uint32_t d = (uint32_t)(it[r].key() >> shift) & mask;
     uint64_t m = __ballot(valid);
 #pragma unroll
@@ -233,6 +243,7 @@ __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst ds
       sum += c[w];
     }
     const uint32_t slot0 = (uint32_t)radix_block_scan<RADIX_NT, OffT>((OffT)sum, red);
+    if (Src::FILTERED && dt == RADIX_NT - 1) kept = (int)(slot0 + sum);
     if (dt < D) {
       gb[dt] = dstart + dbefore - slot0;
       uint32_t run = slot0;
@@ -246,7 +257,7 @@ __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst ds
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < RADIX_IPT; ++r) {
-    if (wbase + r * 64 + lane < total) {
+    if (wbase + r * 64 + lane < total && radix_keeps(src, it[r])) {
       const uint32_t d = (uint32_t)(it[r].key() >> shift) & mask;
       const uint32_t slot = wc[wave][d] + rank[r];
       const uint32_t* w = reinterpret_cast<const uint32_t*>(&it[r]);
@@ -256,7 +267,7 @@ __global__ __launch_bounds__(RADIX_NT) void radix_scatter_kernel(Src src, Dst ds
   }
   __syncthreads();
   const int64_t rest = total - base;
-  const int tile_n = rest < RADIX_TILE ? (int)rest : RADIX_TILE;
+  const int tile_n = Src::FILTERED ? kept : rest < RADIX_TILE ? (int)rest : RADIX_TILE;
 #pragma unroll
   for (int r = 0; r < RADIX_IPT; ++r) {
     const int j = r * RADIX_NT + (int)threadIdx.x;
@@ -289,7 +300,8 @@ hipError_t radix_pass_t(const Src& src, const Dst& dst, int64_t total, int shift
   return hipGetLastError();
 }
 
-// One stable pass over digit (key >> shift) of `width` <= 9 bits; total > 0.
+// One stable pass over digit (key >> shift) of `width` <= 9 bits of the `total` > 0
+// items of src.
 template <typename Src, typename Dst>
 hipError_t radix_pass(const Src& src, const Dst& dst, int64_t total, int shift, int width, void* scratch, hipStream_t s) {
   if (radix_ipt<typename Src::Item>(total) == 8) {
