@@ -26,12 +26,12 @@ def tile(A, prec):
 
 
 CASES = [
-    # 16-bit: 64-row blocks, several ranges, 128-row blocks over the whole range
+    # 16-bit: 64-row blocks (the first two), several ranges, 128-row blocks over the whole range
     (1, 300, 64), (1, 2048, 33), (1, 6001, 64), (2, 8200, 17), (1, 9000, 48), (2, 20000, 50), (1, 32768, 64),
-    # fp32: from ranges of a few chunks up
+    # fp32: 64-row blocks (n = 140 and F = 1), ranges of 69 to 1250 chunks
     (0, 140, 64), (0, 1100, 64), (0, 2049, 1), (0, 2048, 32), (0, 3001, 16), (0, 6001, 48), (0, 8191, 63),
     (0, 20000, 64),
-    # wide: 64-row blocks, then 128 x 128, 256 x 128, 256 x 192 and 256 x 256 tiles
+    # wide: 64-row blocks (n up to 1100; n = 2529), 128 x 128, 256 x 128, 256 x 192 and 256 x 256 tiles
     (1, 257, 70), (1, 1100, 100), (2, 1100, 520), (1, 2500, 130), (2, 2529, 200), (1, 4096, 1000), (2, 6000, 250),
     (1, 6001, 2040), (1, 8200, 380), (2, 12000, 129), (1, 12001, 1000), (1, 16384, 100), (2, 16384, 512),
     (0, 257, 70), (0, 700, 300), (0, 2500, 192), (0, 4100, 200), (0, 5001, 1030),
