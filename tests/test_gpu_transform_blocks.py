@@ -68,3 +68,42 @@ def test_input_gradient(prec, n, f_in, f_out, relu):
     # the sums of what was stored, n fp32 terms in some order
     assert bool(((dbb[:f_in].double() - got.sum(0)).abs() <= n * 2.0 ** -24 * got.abs().sum(0)).all())
     assert bool((dbb[f_in:] == 0).all()) and flag.item() == 0
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("n,f_in,f_out", [(1024, 17, 40), (3001, 128, 64), (20011, 200, 33), (2048, 72, 256),
+                                          (70003, 130, 16)])
+@pytest.mark.parametrize("relu", [True, False])
+def test_column_sums_of_whole_numbers(prec, n, f_in, f_out, relu):
+    """Operands of -1, 0 and 1 make dZ_below whole numbers, times 2 under the
+    mask, and its column sums whole numbers below 2^24: exact in every order, so
+    that a row, step or tile left out of a sum shows (the rounding bound above is
+    wider than one tile's part where workgroups take several)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + f_out)
+    dt = G.torch_dtype(prec)
+
+    def whole(rows, cols):
+        t = torch.full((rows, round8(cols)), 3.0, dtype=dt, device="cuda")
+        t[:, :cols] = torch.randint(-1, 2, (rows, cols), generator=gen, device="cuda").to(dt)
+        return t
+
+    dg = DeviceGraph(n, [], [], prec=prec)
+    H, W, dZ = whole(n, f_in), whole(f_in, f_out), whole(n, f_out)
+    L = G.GcnLayer(f_in, f_out, H.shape[1], W.shape[1], G.GCN_ACT_NONE, 0.0, 1, 0)
+    GS, dZb = torch.empty_like(dZ), torch.empty_like(H)
+    dW = torch.empty((f_in, W.shape[1]), device="cuda")
+    db, dbb = torch.empty(W.shape[1], device="cuda"), torch.empty(H.shape[1], device="cuda")
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(G.gcn_layer_workspace_size(dg.adj, L, prec), dtype=torch.uint8, device="cuda")
+    G.gcn_layer_bwd(dg.adj, L, prec, H, W, dZ, G.GCN_ACT_RELU if relu else G.GCN_ACT_NONE, 0.5 if relu else 0.0, dW, db,
+                    dZb, GS, flag, ws, dbias_below=dbb)
+    want = dZ[:, :f_out].double() @ W[:, :f_out].double().T
+    if relu:
+        want = want * 2 * (H[:, :f_in] > 0)
+    assert float(want.abs().max()) <= (512 if relu else 256) and float(want.abs().sum(0).max()) < 2 ** 24
+    assert torch.equal(dZb[:, :f_in].double(), want)
+    assert torch.equal(dbb[:f_in].double(), want.sum(0))
+    assert torch.equal(db[:f_out].double(), dZ[:, :f_out].double().sum(0))
+    assert torch.equal(dW[:, :f_out].double(), H[:, :f_in].double().T @ dZ[:, :f_out].double())
+    assert flag.item() == 0
