@@ -506,21 +506,24 @@ constexpr int MM_LDR = 128 + 4;   // LDS stride (floats) of a staged strip
 // the reads of another (measured 2-5 % faster at F = 512 and 1024).
 #define MM_SYNC() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
 
+// Up to 256 bytes, four lines of the scalar cache: with a fifth, which the
+// epilogue alone reads, n = 8192, F = 512 in bf16 took 92.0 us instead of 90.6.
 struct MmParams {
   const void* A;      // tiled A_hat
   const void* Xt;     // tiled X^T
   int64_t n, F, nc;   // vertices, features, k chunks
-  int64_t rblocks;    // 64-row blocks of A_hat
-  int64_t fblocks;    // 64-row blocks of X^T
-  int64_t tr0;        // first row of tiles of this launch
-  int64_t tiles, cb, per_xcd;
-  int64_t ksplit, kc; // k ranges of kc chunks (the last one shorter), one per workgroup of a tile
+  int rblocks;        // 64-row blocks of A_hat
+  int fblocks;        // 64-row blocks of X^T
+  int tr0;            // first row of tiles of this launch
+  int tiles, cb, per_xcd;
+  int ksplit, kc;     // k ranges of kc chunks (the last one shorter), one per workgroup of a tile
   int chain;          // CHAINS: chunks (even) added to an accumulator before it is added to the sums
   float* part;        // ksplit > 1: fp32 partial products [ksplit][prows][ldp] of the launch's rows
   int64_t row0, prows;
   int64_t ldp;        // F rounded up to a whole output vector
   Epilogue epi;
 };
+static_assert(sizeof(MmParams) <= 256, "kernel arguments");
 
 // Rows row0 .. row0 + 15, columns col0 .. col0 + W - 1 of the output from a
 // staged strip (16 x W fp32, stride MM_LDR), through the fused epilogue.
@@ -619,11 +622,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int64_t b = blockIdx.x;
   // units are (k range, tile), k range outermost, so that the workgroups of
   // one die (consecutive units) share rows of A_hat as before
+  const int64_t tiles = p.tiles, cb = p.cb, rblocks = p.rblocks, fblocks = p.fblocks;
   const int64_t u = (b & 7) * p.per_xcd + (b >> 3);
-  if (u >= p.tiles * p.ksplit) return;
-  const int64_t split = u / p.tiles;
-  const int64_t t = u - split * p.tiles;
-  const int64_t tr = p.tr0 + t / p.cb, tc = t - (t / p.cb) * p.cb;
+  if (u >= tiles * p.ksplit) return;
+  const int64_t split = u / tiles;
+  const int64_t t = u - split * tiles;
+  const int64_t tr = p.tr0 + t / cb, tc = t - (t / cb) * cb;
   const int64_t c_lo = split * p.kc;                  // this workgroup's k chunks: [c_lo, c_lo + nc)
   const int nc = (int)(min(p.nc, c_lo + p.kc) - c_lo);
   const int64_t blk = p.nc * 4 * PIECE;               // elements of one 64-row block
@@ -637,7 +641,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int pc = wave * LPW + j;
     const bool isa = pc < 4 * RB;
     const int q = isa ? pc : pc - 4 * RB;
-    const int64_t bi = isa ? min(tr * RB + q / 4, p.rblocks - 1) : min(tc * CB + q / 4, p.fblocks - 1);
+    const int64_t bi = isa ? min(tr * RB + q / 4, rblocks - 1) : min(tc * CB + q / 4, fblocks - 1);
     src[j] = (isa ? A : Xt) + bi * blk + c_lo * 4 * PIECE + (q % 4) * PIECE;
   }
   const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
@@ -947,21 +951,24 @@ hipError_t launch_rows(const DensePlan& pl, const void* A, int64_t n, const T* X
   const int64_t ldp = (F + Vec<T>::N - 1) / Vec<T>::N * Vec<T>::N;
   const int64_t step = pl.kind == DK_MM ? MM_TILES[pl.tile].rows : 128, steps = (rows + step - 1) / step;
   if (pl.kind == DK_MM) {
+    const int64_t cb = (F + MM_TILES[pl.tile].cols - 1) / MM_TILES[pl.tile].cols;
+    const int64_t units = steps * cb * pl.ksplit;
+    if (units > INT32_MAX / 2) return hipErrorInvalidValue;      // more than 8 TB of A_hat or X
     MmParams q;
     q.A = A; q.Xt = Xt; q.n = n; q.F = F; q.nc = nc;
-    q.rblocks = (n + 63) / 64;
-    q.fblocks = (F + 63) / 64;
-    q.tr0 = row0 / step;
-    q.cb = (F + MM_TILES[pl.tile].cols - 1) / MM_TILES[pl.tile].cols;
-    q.tiles = steps * q.cb;
-    q.ksplit = pl.ksplit;
-    q.kc = pl.kc;
+    q.rblocks = (int)((n + 63) / 64);
+    q.fblocks = (int)((F + 63) / 64);
+    q.tr0 = (int)(row0 / step);
+    q.cb = (int)cb;
+    q.tiles = (int)(steps * cb);
+    q.ksplit = (int)pl.ksplit;
+    q.kc = (int)pl.kc;
     q.chain = pl.chain;
     q.part = part;
     q.row0 = row0;
     q.prows = rows;
     q.ldp = ldp;
-    q.per_xcd = (q.tiles * q.ksplit + 7) / 8;
+    q.per_xcd = (int)((units + 7) / 8);
     q.epi = epi;
     const dim3 g((unsigned)(8 * q.per_xcd));
 #define MM_LAUNCH(TM_, TN_, S_, C_) \
