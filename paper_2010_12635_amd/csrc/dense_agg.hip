@@ -798,7 +798,9 @@ size_t xt_bytes(int prec, int64_t n, int64_t F) {
 //    workgroups, F = 16 and 64 alike), or works at the matrix rate; the chip is
 //    held to the stream rate of A_hat, once per column block of 64;
 //  * dense_mm_kernel, 16-bit: a k chunk takes `near` us while A_hat fits the 256
-//    MB cache behind the L2s (up to NEAR_BYTES), else `far` + `s` / (column
+//    MB cache behind the L2s (up to NEAR_BYTES) and is there from the call
+//    before, as from layer to layer of an epoch (a matrix just written, or called
+//    for the first time, comes from HBM and takes longer), else `far` + `s` / (column
 //    tiles), column tiles sharing a chunk of A_hat in L2, and at least `h` /
 //    (column tiles), the rate at which the bytes that the LDS ring keeps in
 //    flight come from HBM; fp32: `w32`, the matrix instructions;

@@ -15,6 +15,8 @@
 //  * the distinct keys of every tile are counted and scanned, then written
 //    out in order: columns, row pointers (where a row begins; no row is
 //    empty) and the entry's row, which the values need;
+//  * from 2^31 keys on all of this range by range of the keys (RangedKeys), so
+//    that the workspace stays below 5 bytes per key;
 //  * degrees and dinv = fp32(1 / sqrt(fp64(deg))); values dinv[row] *
 //    dinv[col] in the value precision, one thread per entry; optional dense.
 #include "radix.h"

@@ -217,7 +217,7 @@ hipError_t pair_loss_t(const PairLossParams& p, int lpr, hipStream_t s, int64_t*
 // stable radix sort by key (radix.h) puts each row's entries together in
 // increasing k without atomics.  2^21 pairs, n = 2^17: two passes of 9 bits
 // instead of three of 8, no workgroup barrier between the rounds of a tile:
-// 215 -> 113 us.  The
+// 215 -> 97 us.  The
 // sorted entries are cut into segments of SEG entries; a lane group per
 // segment sums the rows that lie inside it and leaves partial sums for the
 // rows that cross its ends, which a fix-up pass adds in segment order.
